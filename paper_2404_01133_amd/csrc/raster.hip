@@ -30,6 +30,7 @@ struct FwdLds {
   float4 w0[BATCH], w1[BATCH], w2[BATCH];
   float4 f[BATCH];  // footprint as floats: i0, j0, i1 - i0, j1 - j0
   uint8_t list[(TW * TH) / 64][kFwdGroups][kListStride<BATCH>];
+  uint8_t cand[(TW * TH) / 64][BATCH];
 };
 
 template <int TW, int TH, int BATCH>
@@ -64,9 +65,11 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     const int nb = (int)min((uint32_t)BATCH, end - b);
     for (int k = threadIdx.x; k < nb; k += NT) {
       const float4* r = reinterpret_cast<const float4*>(&records[pair_records[b + k]]);
-      const float4 a = r[0];
+      float4 a = r[0];
+      const float4 w1 = r[1];
+      a.y = q_limit(w1.w);
       s_w0[k] = a;
-      s_w1[k] = r[1];
+      s_w1[k] = w1;
       s_w2[k] = r[2];
       const uint32_t px = __float_as_uint(a.z), py = __float_as_uint(a.w);
       s_f[k] = make_float4((float)(px & 0xFFFFu), (float)(py & 0xFFFFu), (float)(px >> 16), (float)(py >> 16));
@@ -75,7 +78,7 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     // unstaged slots: their colour must be finite (it is multiplied by 0)
     for (int k = nb + threadIdx.x; k < BATCH; k += NT) s_w2[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     __syncthreads();
-    const Counts8 cnt = wave_compact8<BATCH>(s_w0, nb, qb.x0, qb.y0, lists);
+    const Counts8 cnt = wave_compact8<BATCH>(s_w0, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
     const int max_cnt = cnt.max();
     const int my_cnt = cnt.of(qb.g);
     const int base_idx = (int)(b - start);

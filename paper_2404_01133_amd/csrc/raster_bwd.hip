@@ -67,6 +67,7 @@ struct BwdLds {
   uint32_t rec[BATCH];
   float grad[kQuads * BATCH * kG];
   uint8_t list[(TW * TH) / 64][4][kListStride<BATCH>];
+  uint8_t cand[(TW * TH) / 64][BATCH];
   int wave_last[(TW * TH) / 64];
 };
 
@@ -146,8 +147,11 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     for (int k = threadIdx.x; k < nb; k += NT) {
       const uint32_t rid = pair_records[b + k];
       const float4* rp = reinterpret_cast<const float4*>(&records[rid]);
-      s_w0[k] = rp[0];
-      s_w1[k] = rp[1];
+      float4 a = rp[0];
+      const float4 w1 = rp[1];
+      a.y = q_limit(w1.w);
+      s_w0[k] = a;
+      s_w1[k] = w1;
       s_w2[k] = rp[2];
       s_rec[k] = rid;
     }
@@ -155,7 +159,8 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     __syncthreads();
     const int base_idx = (int)(b - start);
     const int kmax = min(nb, wave_last - base_idx);  // entries past every lane's n_last are not needed
-    const Counts4 cnt = kmax > 0 ? wave_compact4<BATCH>(s_w0, kmax, qb.x0, qb.y0, lists) : Counts4{0, 0, 0, 0};
+    const Counts4 cnt = kmax > 0 ? wave_compact4<BATCH>(s_w0, s_w1, s_w2, kmax, qb.x0, qb.y0, lds.cand[wid], lists)
+                                 : Counts4{0, 0, 0, 0};
     const int max_cnt = cnt.max();
     const int my_cnt = cnt.of(qb.g);
     // one entry of each quadrant's list: the four quadrants step (possibly

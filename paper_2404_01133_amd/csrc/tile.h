@@ -81,10 +81,10 @@ struct LaneMap {
 template <int BATCH>
 constexpr int kListStride = BATCH + 4;
 
-// Per-group ballot compaction: list[g][0 .. cnt[g]) receives, in ascending
-// (= depth) order, the staged records whose footprint rectangle meets group g
-// of the wave's block.  The counts are a struct of named scalars (arrays of
-// them end up in scratch memory).
+// Per-group lists: list[g][0 .. cnt[g]) receives, in ascending (= depth) order,
+// the staged records that may contribute to a pixel of group g of the wave's
+// block.  The counts are a struct of named scalars (arrays of them end up in
+// scratch memory).
 struct Counts4 {
   int c0, c1, c2, c3;
   __device__ __forceinline__ int max() const { return ::max(::max(c0, c1), ::max(c2, c3)); }
@@ -102,68 +102,129 @@ struct Counts8 {
   }
 };
 
-template <int BATCH>
 __device__ __forceinline__ void append_if(bool h, uint8_t* list, int& c, int k) {
   const uint64_t m = __ballot(h);
   if (h) list[c + (int)lanemask_lt_count(m)] = (uint8_t)k;
   c += (int)__popcll(m);
 }
 
-// rectangle of staged record k; past the batch one that meets no pixel (every
-// overlap test "i0 <= hi && i1 >= lo" with lo, hi >= 0 fails on it)
-__device__ __forceinline__ void staged_rect(const float4* s_w0, int k, int nb, int& i0, int& i1, int& j0, int& j1) {
-  i0 = j0 = 1 << 30;
-  i1 = j1 = -1;
-  if (k < nb) {
-    const uint32_t px = __float_as_uint(s_w0[k].z), py = __float_as_uint(s_w0[k].w);
+// Largest exponent Q = p1^2 + p2^2 at which a record of this opacity can reach
+// the alpha threshold: opac * exp2(-Q) >= 1/255 <=> Q <= log2(255 opac).  The
+// slack (0.7 % in alpha) covers the rounding of the logarithm here and of Q and
+// exp2 in evaluate_at.
+__device__ __forceinline__ float q_limit(float opac) { return __builtin_amdgcn_logf(255.0f * opac) + 0.01f; }
+
+// Whether a staged record may contribute to a group: its footprint rectangle
+// meets the group, and the smallest Q over the group can stay within q_limit.
+// Q = p1^2 + p2^2 with p1 = ca dx + cb dy and p2 = cc dy, both linear, so over a
+// GW x GH group |p1| is at least its value at the centre less its half range
+// (|ca| (GW-1) + |cb| (GH-1)) / 2, and likewise p2; the sum of the two squared
+// minima bounds Q from below.  Every pixel of a group rejected here has
+// alpha < 1/255 (the compositing skips such entries), so the result is the same
+// bit for bit.  The margins cover the rounding of this estimate (a few ulp of
+// the summed terms, FP32) hundreds of times over; a NaN keeps the record.
+struct GroupTest {
+  int i0, i1, j0, j1;
+  float p1, m1, sx, sy;  // p1 at the centre of the block's first group, half range, steps per pixel
+  float p2, m2, sy2;
+  float q;
+  template <int GW, int GH>
+  __device__ __forceinline__ void load(const float4& w0, const float4& w1, float dv, int x0, int y0) {
+    const uint32_t px = __float_as_uint(w0.z), py = __float_as_uint(w0.w);
     i0 = (int)(px & 0xFFFFu), i1 = i0 + (int)(px >> 16);
     j0 = (int)(py & 0xFFFFu), j1 = j0 + (int)(py >> 16);
+    q = w0.y;
+    const float dx = ((float)(x0 - i0) + 0.5f * (GW - 1)) - w0.x;
+    const float dy = ((float)(y0 - j0) + 0.5f * (GH - 1)) - dv;
+    sx = w1.x, sy = w1.y, sy2 = w1.z;
+    p1 = fmaf(sx, dx, sy * dy);
+    p2 = sy2 * dy;
+    const float ax = fabsf(sx), ay = fabsf(sy), a2 = fabsf(sy2);
+    const float ex = fabsf(dx) + 8.0f, ey = fabsf(dy) + 8.0f;  // largest offsets over the 8x8 block
+    m1 = fmaf(0.5f * (GW - 1), ax, fmaf(0.5f * (GH - 1), ay, fmaf(1e-5f, fmaf(ax, ex, ay * ey), 1e-3f)));
+    m2 = fmaf(0.5f * (GH - 1), a2, fmaf(1e-5f, a2 * ey, 1e-3f));
   }
-}
+  // squared lower bound of |p2| over the rows of groups `r` (in pixels from the first)
+  __device__ __forceinline__ float row(float r) const {
+    const float a = fmaxf(fabsf(fmaf(sy2, r, p2)) - m2, 0.0f);
+    return a * a;
+  }
+  __device__ __forceinline__ bool reach(float c, float r, float row2) const {
+    const float a = fmaxf(fabsf(fmaf(sx, c, fmaf(sy, r, p1))) - m1, 0.0f);
+    return !(fmaf(a, a, row2) > q);
+  }
+};
 
-// 4x4 quadrants (groups 0..3 row-major over the 8x8 block)
+// First step of a wave's lists: the staged records whose footprint meets the
+// wave's 8x8 block (about two in five of a 16x16 tile's), so the per-group tests
+// run on full lanes of candidates only.
 template <int BATCH>
-__device__ __forceinline__ Counts4 wave_compact4(const float4* s_w0, int nb, int x0, int y0,
-                                                 uint8_t (*list)[kListStride<BATCH>]) {
+__device__ __forceinline__ int wave_candidates(const float4* s_w0, int nb, int x0, int y0, uint8_t* cand) {
   static_assert(BATCH <= 256, "record indices are bytes");
   const int lane = threadIdx.x & 63;
-  Counts4 c{0, 0, 0, 0};
+  int c = 0;
   for (int base = 0; base < nb; base += 64) {
     const int k = base + lane;
-    int i0, i1, j0, j1;
-    staged_rect(s_w0, k, nb, i0, i1, j0, j1);
-    const bool xa = i0 <= x0 + 3 && i1 >= x0, xb = i0 <= x0 + 7 && i1 >= x0 + 4;
-    const bool ya = j0 <= y0 + 3 && j1 >= y0, yb = j0 <= y0 + 7 && j1 >= y0 + 4;
-    append_if<BATCH>(xa && ya, list[0], c.c0, k);
-    append_if<BATCH>(xb && ya, list[1], c.c1, k);
-    append_if<BATCH>(xa && yb, list[2], c.c2, k);
-    append_if<BATCH>(xb && yb, list[3], c.c3, k);
+    bool h = false;
+    if (k < nb) {
+      const uint32_t px = __float_as_uint(s_w0[k].z), py = __float_as_uint(s_w0[k].w);
+      const int i0 = (int)(px & 0xFFFFu), j0 = (int)(py & 0xFFFFu);
+      h = i0 <= x0 + 7 && i0 + (int)(px >> 16) >= x0 && j0 <= y0 + 7 && j0 + (int)(py >> 16) >= y0;
+    }
+    append_if(h, cand, c, k);
+  }
+  return c;
+}
+
+// 4x4 quadrants (groups 0..3 row-major over the 8x8 block).  s_w0[k].y holds
+// q_limit of the record (its view is not needed once staged).
+template <int BATCH>
+__device__ __forceinline__ Counts4 wave_compact4(const float4* s_w0, const float4* s_w1, const float4* s_w2, int nb,
+                                                 int x0, int y0, uint8_t* cand,
+                                                 uint8_t (*list)[kListStride<BATCH>]) {
+  const int lane = threadIdx.x & 63;
+  const int nc = wave_candidates<BATCH>(s_w0, nb, x0, y0, cand);
+  Counts4 c{0, 0, 0, 0};
+  for (int base = 0; base < nc; base += 64) {
+    const bool in = base + lane < nc;
+    const int k = in ? (int)cand[base + lane] : 0;
+    GroupTest t;
+    t.load<4, 4>(s_w0[k], s_w1[k], s_w2[k].w, x0, y0);
+    const bool xa = in && t.i0 <= x0 + 3, xb = in && t.i1 >= x0 + 4;
+    const bool ya = t.j0 <= y0 + 3, yb = t.j1 >= y0 + 4;
+    const float r0 = t.row(0.0f), r1 = t.row(4.0f);
+    append_if(xa && ya && t.reach(0.0f, 0.0f, r0), list[0], c.c0, k);
+    append_if(xb && ya && t.reach(4.0f, 0.0f, r0), list[1], c.c1, k);
+    append_if(xa && yb && t.reach(0.0f, 4.0f, r1), list[2], c.c2, k);
+    append_if(xb && yb && t.reach(4.0f, 4.0f, r1), list[3], c.c3, k);
   }
   return c;
 }
 
 // 4x2 groups (two columns of four pixels, four rows of two; row-major)
 template <int BATCH>
-__device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, int nb, int x0, int y0,
+__device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float4* s_w1, const float4* s_w2, int nb,
+                                                 int x0, int y0, uint8_t* cand,
                                                  uint8_t (*list)[kListStride<BATCH>]) {
-  static_assert(BATCH <= 256, "record indices are bytes");
   const int lane = threadIdx.x & 63;
+  const int nc = wave_candidates<BATCH>(s_w0, nb, x0, y0, cand);
   Counts8 c{0, 0, 0, 0, 0, 0, 0, 0};
-  for (int base = 0; base < nb; base += 64) {
-    const int k = base + lane;
-    int i0, i1, j0, j1;
-    staged_rect(s_w0, k, nb, i0, i1, j0, j1);
-    const bool xa = i0 <= x0 + 3 && i1 >= x0, xb = i0 <= x0 + 7 && i1 >= x0 + 4;
-    const bool y0r = j0 <= y0 + 1 && j1 >= y0, y1r = j0 <= y0 + 3 && j1 >= y0 + 2;
-    const bool y2r = j0 <= y0 + 5 && j1 >= y0 + 4, y3r = j0 <= y0 + 7 && j1 >= y0 + 6;
-    append_if<BATCH>(xa && y0r, list[0], c.c0, k);
-    append_if<BATCH>(xb && y0r, list[1], c.c1, k);
-    append_if<BATCH>(xa && y1r, list[2], c.c2, k);
-    append_if<BATCH>(xb && y1r, list[3], c.c3, k);
-    append_if<BATCH>(xa && y2r, list[4], c.c4, k);
-    append_if<BATCH>(xb && y2r, list[5], c.c5, k);
-    append_if<BATCH>(xa && y3r, list[6], c.c6, k);
-    append_if<BATCH>(xb && y3r, list[7], c.c7, k);
+  for (int base = 0; base < nc; base += 64) {
+    const bool in = base + lane < nc;
+    const int k = in ? (int)cand[base + lane] : 0;
+    GroupTest t;
+    t.load<4, 2>(s_w0[k], s_w1[k], s_w2[k].w, x0, y0);
+    const bool xa = in && t.i0 <= x0 + 3, xb = in && t.i1 >= x0 + 4;  // a candidate meets the block
+    auto rows = [&](int r, uint8_t* la, int& ca, uint8_t* lb, int& cb) {
+      const bool y = t.j0 <= y0 + r + 1 && t.j1 >= y0 + r;
+      const float r2 = t.row((float)r);
+      append_if(xa && y && t.reach(0.0f, (float)r, r2), la, ca, k);
+      append_if(xb && y && t.reach(4.0f, (float)r, r2), lb, cb, k);
+    };
+    rows(0, list[0], c.c0, list[1], c.c1);
+    rows(2, list[2], c.c2, list[3], c.c3);
+    rows(4, list[4], c.c4, list[5], c.c5);
+    rows(6, list[6], c.c6, list[7], c.c7);
   }
   return c;
 }
