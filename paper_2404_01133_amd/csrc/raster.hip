@@ -71,14 +71,13 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
       s_w0[k] = a;
       s_w1[k] = w1;
       s_w2[k] = r[2];
-      const uint32_t px = __float_as_uint(a.z), py = __float_as_uint(a.w);
-      s_f[k] = make_float4((float)(px & 0xFFFFu), (float)(py & 0xFFFFu), (float)(px >> 16), (float)(py >> 16));
+      s_f[k] = footprint_floats(a);
     }
     // list entries past a group's count read stale indices that may land on
     // unstaged slots: their colour must be finite (it is multiplied by 0)
     for (int k = nb + threadIdx.x; k < BATCH; k += NT) s_w2[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     __syncthreads();
-    const Counts8 cnt = wave_compact8<BATCH>(s_w0, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
+    const Counts8 cnt = wave_compact8<BATCH>(s_w0, s_f, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
     const int max_cnt = cnt.max();
     const int my_cnt = cnt.of(qb.g);
     const int base_idx = (int)(b - start);

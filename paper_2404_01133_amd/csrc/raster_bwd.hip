@@ -4,72 +4,134 @@
 // Compositing adjoint: the forward's walk on 4x4 quadrants of 16 lanes, front
 // to back, bounded by each pixel's n_last, with the blend state recomputed
 // (colour in front is accumulated, colour behind = final colour - accumulated),
-// so nothing per (pixel, Gaussian) is stored.  The nine per-Gaussian partial
-// gradients of a quadrant are summed with DPP row operations, added into LDS
-// across the tile's waves, and flushed with one FP32 atomic per (tile,
+// so nothing per (pixel, Gaussian) is stored.  Per round a thread per staged
+// record finds the quadrants it may reach; every (record, quadrant) hit owns a
+// slot of nine sums in LDS, a record's slots side by side.  The nine partial
+// gradients of a quadrant are summed with DPP row operations and stored to the
+// slot (one plain LDS store for the wave's four quadrants), and the slots of a
+// record are added in quadrant order and flushed with one FP32 atomic per (tile,
 // Gaussian, quantity).  Then the projection adjoint chains each record's 2D
 // partials back to the Gaussian's parameters.
+//
+// Why slots: the sums used to be added into one row per record with LDS float
+// atomics, and those bounded the kernel (about 50 LDS cycles for the 36 lanes of a
+// step, LDS busy 92 % of the time; a store takes two).  Now VALU issue bounds it.
+// Measured, 16 views of a 2M-Gaussian block at 1600x900: 5.16 ms with LDS atomics,
+// 3.88 with slots; 4096 Gaussians at 256x256 76 -> 66 us (one work-group per CU:
+// the chain of steps); one 1M-Gaussian 1920x1080 view 102 -> 73 us.  Six waves per
+// SIMD (a few spills outside the loop) against five: 3.88 against 4.12 ms.
 #include "tile.h"
 
 namespace gs {
 namespace {
 
 // ---------------------------------------------------------------------------
-// Sums of nine per-lane values over each 16-lane quadrant, all at once.  At
-// butterfly level k (partner lane = lane ^ 2^k, k = 0..3) two quantities share
-// one register: lanes with bit k clear keep the first, lanes with bit k set the
-// second, and each lane adds the partner's copy of the quantity it keeps.  Nine
-// registers become one after the four levels; on return lane 16p + r of
-// quadrant p holds the quadrant's total of value min(r, 8).
+// Sums of nine per-lane values over each 16-lane quadrant (a DPP row), all at
+// once.  At each of four levels (partner lane ^ 15, ^ 7, ^ 3, ^ 1) two quantities
+// share one register: lanes with bit 3 (2, 1, 0) clear keep the first, the others
+// the second, and each lane adds the partner's copy of the quantity it keeps.
+// Lanes l, l^15, l^7, l^8, ... of the four levels are the sixteen of the row, and
+// a partner agrees in every bit already used, so it keeps the same quantities.
+// The first two levels pick by banks of four lanes: two masked DPP adds write
+// the two halves of one register, with no selects.  On return lane r of a row
+// holds the row's total of value quad_value(r).  (Issue bound: 21 VALU and no LDS
+// traffic; butterflies by selects and ds_swizzle took 27 and three LDS trips.)
+// Every lane of the wave must be active.
 // ---------------------------------------------------------------------------
 template <int CTRL>
 __device__ __forceinline__ float dpp_mov(float v) {
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), CTRL, 0xF, 0xF, false));
 }
-template <int PATTERN>
-__device__ __forceinline__ float swz(float v) {
-  return __int_as_float(__builtin_amdgcn_ds_swizzle(__float_as_int(v), PATTERN));
-}
-__device__ __forceinline__ float pack_add1(bool hi, float a, float b) {  // partner lane ^ 1
-  return (hi ? b : a) + dpp_mov<0xB1>(hi ? a : b);                      // quad_perm [1,0,3,2]
-}
-__device__ __forceinline__ float pack_add2(bool hi, float a, float b) {  // partner lane ^ 2
-  return (hi ? b : a) + dpp_mov<0x4E>(hi ? a : b);                      // quad_perm [2,3,0,1]
-}
 
 __device__ __forceinline__ float quad_sum9(const float v[9], int lane) {
-  const bool b0 = lane & 1, b1 = lane & 2, b2 = lane & 4, b3 = lane & 8;
-  const float r0 = pack_add1(b0, v[0], v[1]);
-  const float r1 = pack_add1(b0, v[2], v[3]);
-  const float r2 = pack_add1(b0, v[4], v[5]);
-  const float r3 = pack_add1(b0, v[6], v[7]);
-  const float r4 = v[8] + dpp_mov<0xB1>(v[8]);
-  const float s0 = pack_add2(b1, r0, r1);
-  const float s1 = pack_add2(b1, r2, r3);
-  const float s2 = r4 + dpp_mov<0x4E>(r4);
-  // ds_swizzle bit-mask mode (and 0x1F, xor m) exchanges with lane ^ m inside 32 lanes
-  const float u0 = (b2 ? s1 : s0) + swz<0x101F>(b2 ? s0 : s1);
-  const float u1 = s2 + swz<0x101F>(s2);
-  return (b3 ? u1 : u0) + swz<0x201F>(b3 ? u0 : u1);
+  float r0, r1, r2, r3, r4, s0, s1, s2;
+  // a DPP source must have been written at least two instructions before
+  asm("s_nop 1\n\t"
+      "v_add_f32_dpp %4, %16, %16 row_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %0, %8, %8 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %0, %9, %9 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %1, %10, %10 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %1, %11, %11 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %2, %12, %12 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %2, %13, %13 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %3, %14, %14 row_mirror row_mask:0xf bank_mask:0x3\n\t"
+      "v_add_f32_dpp %3, %15, %15 row_mirror row_mask:0xf bank_mask:0xc\n\t"
+      "v_add_f32_dpp %7, %4, %4 row_half_mirror row_mask:0xf bank_mask:0xf\n\t"
+      "v_add_f32_dpp %5, %0, %0 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %5, %1, %1 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "v_add_f32_dpp %6, %2, %2 row_half_mirror row_mask:0xf bank_mask:0x5\n\t"
+      "v_add_f32_dpp %6, %3, %3 row_half_mirror row_mask:0xf bank_mask:0xa\n\t"
+      "s_nop 1"
+      : "=&v"(r0), "=&v"(r1), "=&v"(r2), "=&v"(r3), "=&v"(r4), "=&v"(s0), "=&v"(s1), "=&v"(s2)
+      : "v"(v[0]), "v"(v[1]), "v"(v[2]), "v"(v[3]), "v"(v[4]), "v"(v[5]), "v"(v[6]), "v"(v[7]), "v"(v[8]));
+  const bool b1 = lane & 2, b0 = lane & 1;
+  const float u0 = (b1 ? s1 : s0) + dpp_mov<0x1B>(b1 ? s0 : s1);  // quad_perm [3,2,1,0]
+  const float u1 = s2 + dpp_mov<0x1B>(s2);
+  return (b0 ? u1 : u0) + dpp_mov<0xB1>(b0 ? u0 : u1);  // quad_perm [1,0,3,2]
 }
 
-constexpr int kG = 9;  // partials per Gaussian: r, g, b, opacity, A1, A2, Axx, Axy, Ayy
+// value held by lane r of a row after quad_sum9, and whether the lane is the one that writes it
+__device__ __forceinline__ int quad_value(int r) {
+  return (r & 1) ? 8 : ((r & 2) << 1) | ((r & 4) >> 1) | ((r & 8) >> 3);
+}
+__device__ __forceinline__ bool quad_writes(int r) { return !(r & 1) || r == 1; }
+
+// Partials per Gaussian: r, g, b, opacity, A1, A2, Axx, Axy, Ayy.  The last five
+// are derivatives by the exponent Q; inside a tile they are summed without their
+// common factor -ln2 opac (dG/dQ = -ln2 G), which the flush applies once.
+constexpr int kG = 9;
+constexpr int kGQ = 4;  // first partial with that factor
+__device__ __forceinline__ float q_scale(int q, float opac) { return q >= kGQ ? -0.69314718055994531f * opac : 1.0f; }
 constexpr int kBwdLdsOffsets = 1024;  // segment offsets staged in LDS by the view-major adjoint up to this many
 
-// DET: each quadrant of the tile stores its sums for the staged records in its
-// own slots (grad[quadrant][record][9], plain stores: a quadrant's list holds a
-// record at most once); the slots are then summed in quadrant order.
-// Otherwise grad[record][9] receives LDS atomic adds.
-template <int TW, int TH, int BATCH, bool DET>
+// LDS of one tile.  Up to BATCH - 1 records are staged at a time (the last place is
+// the null record) and walked in rounds of as many as have room for all their hits
+// in the pool: small splats reach three to six of a 16x16 tile's sixteen
+// quadrants, so about a hundred records share a round; splats that cover the tile
+// take rounds of 25.  The pool is sized so that five work-groups of a 16x16 tile
+// fit a CU.
+template <int TW, int TH, int BATCH>
 struct BwdLds {
-  static constexpr int kQuads = DET ? (TW * TH) / 16 : 1;
-  float4 w0[BATCH], w1[BATCH], w2[BATCH];
+  static constexpr int kQuads = (TW * TH) / 16;
+  static constexpr int kWaves = (TW * TH) / 64;
+  static constexpr int kBatchBits = BATCH == 128 ? 7 : 6;
+  static constexpr int kPool = kQuads * 25 < 511 ? kQuads * 25 : 511;  // + one slot for the null record
+  static constexpr int kStride = BATCH + 2;  // list entries (u16); the odd dword count spreads the lists over banks
+  static constexpr int kMaskBytes = kQuads <= 8 ? 1 : kQuads / 8;
+  static_assert(BATCH == 64 || BATCH == 128, "records per round");
+  static_assert(kPool >= kQuads, "a record always fits an empty pool");
+  static_assert(((kPool + 1) << kBatchBits) <= 65536, "a list entry holds a record and a slot in 16 bits");
+  static_assert(4 * kStride * 2 % 16 == 0, "whole 16-byte words");
+  float4 w1[BATCH], w2[BATCH];
+  float4 f[BATCH];  // footprint as floats: i0, j0, i1 - i0, j1 - j0
+  alignas(16) float pool[((kPool + 1) * kG + 3) / 4 * 4];
+  alignas(16) uint16_t list[kWaves][4][kStride];  // record | slot << kBatchBits
+  float du[BATCH];
   uint32_t rec[BATCH];
-  float grad[kQuads * BATCH * kG];
-  uint8_t list[(TW * TH) / 64][4][kListStride<BATCH>];
-  uint8_t cand[(TW * TH) / 64][BATCH];
-  int wave_last[(TW * TH) / 64];
+  alignas(4) uint8_t mask[BATCH * kMaskBytes];  // quadrants a record may reach, bit wave * 4 + quadrant
+  uint16_t end[BATCH];                          // hits of the staged records up to and with this one
+  int quad_last[kQuads < 8 ? 8 : kQuads];  // entries that each quadrant must walk
+
+  __device__ __forceinline__ uint32_t hits(int k) const {
+    if constexpr (kMaskBytes == 1) return mask[k];
+    else if constexpr (kMaskBytes == 2) return reinterpret_cast<const uint16_t*>(mask)[k];
+    else return reinterpret_cast<const uint32_t*>(mask)[k];
+  }
 };
+
+// inclusive prefix sum over the wave (DPP: within rows, then across)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);  // row_bcast 15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);  // row_bcast 31 into rows 2 and 3
+}
 
 // Deterministic mode: per-(tile, record) partials are stored at slot
 // base[record] + (the tile's row-major index within the record's footprint
@@ -82,31 +144,30 @@ struct DetArgs {
 };
 
 template <int TW, int TH>
-__device__ __forceinline__ int64_t det_slot(const DetArgs& d, uint32_t rid, uint32_t px, uint32_t py, int txi,
+__device__ __forceinline__ int64_t det_slot(const DetArgs& d, uint32_t rid, int i0, int i1, int j0, int txi,
                                             int tyi) {
-  const int i0 = (int)(px & 0xFFFFu), i1 = i0 + (int)(px >> 16);
-  const int j0 = (int)(py & 0xFFFFu);
   const int tx0 = i0 / TW, ntx = i1 / TW - tx0 + 1, ty0 = j0 / TH;
   return (int64_t)d.base[rid] + (int64_t)(tyi - ty0) * ntx + (txi - tx0);
 }
 
 template <int TW, int TH, int BATCH, bool DET>
-__device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, TH, BATCH, DET>& lds, int tile_g,
+__device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, TH, BATCH>& lds, int tile_g,
                                                 const float* __restrict__ rgb, const float* __restrict__ T_final,
                                                 const int32_t* __restrict__ n_last, const float* __restrict__ d_rgb,
                                                 float* __restrict__ grad2d, const DetArgs& det) {
+  using Lds = BwdLds<TW, TH, BATCH>;
   constexpr int NT = TW * TH;
-  constexpr int NW = NT / 64;
+  constexpr int KB = Lds::kBatchBits;
   const Record* __restrict__ records = ta.records;
   const uint32_t* __restrict__ pair_records = ta.pair_records;
   const uint32_t* __restrict__ ranges = ta.ranges;
   const int W = ta.W, H = ta.H, tiles_x_n = ta.tiles_x_n, tiles_per_view = ta.tiles_per_view;
-  float4* s_w0 = lds.w0;
   float4* s_w1 = lds.w1;
   float4* s_w2 = lds.w2;
+  float4* s_f = lds.f;
+  float* s_du = lds.du;
   uint32_t* s_rec = lds.rec;
-  float* s_grad = lds.grad;
-  int* s_wave_last = lds.wave_last;
+  float* s_pool = lds.pool;
   const int view = tile_g / tiles_per_view;
   const int tile = tile_g - view * tiles_per_view;
   const int tyi = tile / tiles_x_n, txi = tile - tyi * tiles_x_n;
@@ -130,108 +191,181 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     out2 = rgb[o + 2 * plane];
     last = n_last[(int64_t)view * plane + pix];
   }
-  // entries this wave / the tile must walk
-  int wl = last;
-  for (int off = 32; off > 0; off >>= 1) wl = max(wl, __shfl_xor(wl, off, 64));
-  if (lane == 0) s_wave_last[wid] = wl;
+  // entries each quadrant / the tile must walk
+  int ql = last;
+  for (int off = 8; off > 0; off >>= 1) ql = max(ql, __shfl_xor(ql, off, 64));
+  if ((lane & 15) == 0) lds.quad_last[threadIdx.x >> 4] = ql;
+  if (threadIdx.x == 0) {
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s_du[BATCH - 1] = 0.0f;
+    s_f[BATCH - 1] = s_w1[BATCH - 1] = s_w2[BATCH - 1] = zero;
+  }
   __syncthreads();
   int tile_last = 0;
-  for (int w = 0; w < NW; ++w) tile_last = max(tile_last, s_wave_last[w]);
-  const int wave_last = __builtin_amdgcn_readfirstlane(s_wave_last[wid]);
-  uint8_t(*lists)[kListStride<BATCH>] = lds.list[wid];
-  const uint8_t* my_list = lists[qb.g];
+  for (int q = 0; q < Lds::kQuads; ++q) tile_last = max(tile_last, lds.quad_last[q]);
+  const float fi = (float)i, fj = (float)j;
   const int r = lane & 15;  // lane within the quadrant
-  float T = 1.0f, A0 = 0.f, A1c = 0.f, A2c = 0.f;  // transmittance and colour accumulated in front
-  for (uint32_t b = start; b < start + (uint32_t)tile_last; b += BATCH) {
-    const int nb = (int)min((uint32_t)BATCH, start + (uint32_t)tile_last - b);
+  const bool writes = quad_writes(r);
+  float* const my_pool = s_pool + quad_value(r);
+  const uint16_t* my_list = lds.list[wid][qb.g];
+  // transmittance and colour in front of the next entry, by the forward's own operations: the colour
+  // behind (final colour less colour in front) then carries none of the roundings in front
+  float T = 1.0f, A0 = 0.f, A1 = 0.f, A2 = 0.f;
+  const uint32_t stop = start + (uint32_t)tile_last;
+  for (uint32_t b = start; b < stop; b += BATCH - 1) {
+    const int nb = (int)min((uint32_t)(BATCH - 1), stop - b);
     for (int k = threadIdx.x; k < nb; k += NT) {
       const uint32_t rid = pair_records[b + k];
       const float4* rp = reinterpret_cast<const float4*>(&records[rid]);
-      float4 a = rp[0];
-      const float4 w1 = rp[1];
-      a.y = q_limit(w1.w);
-      s_w0[k] = a;
-      s_w1[k] = w1;
+      const float4 w0 = rp[0];
+      s_w1[k] = rp[1];
       s_w2[k] = rp[2];
+      s_du[k] = w0.x;
+      s_f[k] = footprint_floats(w0);
       s_rec[k] = rid;
     }
-    for (int k = threadIdx.x; k < lds.kQuads * BATCH * kG; k += NT) s_grad[k] = 0.0f;
     __syncthreads();
     const int base_idx = (int)(b - start);
-    const int kmax = min(nb, wave_last - base_idx);  // entries past every lane's n_last are not needed
-    const Counts4 cnt = kmax > 0 ? wave_compact4<BATCH>(s_w0, s_w1, s_w2, kmax, qb.x0, qb.y0, lds.cand[wid], lists)
-                                 : Counts4{0, 0, 0, 0};
-    const int max_cnt = cnt.max();
-    const int my_cnt = cnt.of(qb.g);
+    // quadrants that walk each record and that it may reach, eight (two waves' blocks, 16x8 pixels) per thread
+    for (int it = threadIdx.x; it < BATCH * Lds::kMaskBytes; it += NT) {
+      const int k = it & (BATCH - 1), part = it >> KB;
+      if (k >= nb) continue;
+      constexpr int kCols = TW >= 16 ? 4 : 2;
+      const int x0 = txi * TW + (2 * part % (TW / 8)) * 8, y0 = tyi * TH + (2 * part / (TW / 8)) * 8;
+      const float4 f = s_f[k], w1 = s_w1[k];
+      GroupTest t;
+      t.load<4, 4>(f, s_du[k], s_w2[k].w, w1, q_limit(w1.w), x0, y0);
+      uint32_t m = 0;
+#pragma unroll
+      for (int ry = 0; ry < 2; ++ry) {
+        const float r2 = t.row(4.0f * ry);
+#pragma unroll
+        for (int cx = 0; cx < kCols; ++cx) {
+          const int g = (cx >> 1) * 4 + ry * 2 + (cx & 1);
+          if (t.meets<4, 4>(4.0f * cx, 4.0f * ry) & t.reach(4.0f * cx, 4.0f * ry, r2) &
+              (base_idx + k < lds.quad_last[part * 8 + g]))
+            m |= 1u << g;
+        }
+      }
+      lds.mask[k * Lds::kMaskBytes + part] = (uint8_t)m;
+    }
+    __syncthreads();
+    const int my_last = last - base_idx;  // staged entries that the lane's pixel walks
+    // slots by prefix sum over the records' hits (every wave for itself)
+    int hit_end[BATCH / 64];
+    uint32_t hits[BATCH / 64];
+    {
+      int carry = 0;
+#pragma unroll
+      for (int h = 0; h < BATCH / 64; ++h) {
+        const int k = h * 64 + lane;
+        hits[h] = k < nb ? lds.hits(k) : 0u;
+        hit_end[h] = wave_incl_scan((int)__popc(hits[h])) + carry;
+        carry = __builtin_amdgcn_readlane(hit_end[h], 63);
+        if (wid == 0) lds.end[k] = (uint16_t)hit_end[h];
+      }
+    }
     // one entry of each quadrant's list: the four quadrants step (possibly
-    // different) records side by side; partials are summed per quadrant and
-    // added into the record's LDS slots (two quadrants on one record add twice)
-    auto step = [&](int k, bool valid, const float4& w0, const float4& w1, const float4& w2) {
-      int di, dj;
-      const bool in_fp = in_footprint(i, j, __float_as_uint(w0.z), __float_as_uint(w0.w), di, dj);
+    // different) records side by side, each storing its sums to the hit's slot
+    auto step = [&](uint32_t k, uint32_t slot, float du, const float4& f, const float4& w1, const float4& w2) {
       Eval e;
-      evaluate(w0, w1, w2, di, dj, e);
-      const bool use = valid && (base_idx + k < last) && in_fp && (e.alpha >= kAlphaMin);
-      if (__ballot(use) == 0) return;
-      const float aT = e.alpha * T;
-      const float nA0 = fmaf(w2.x, aT, A0), nA1 = fmaf(w2.y, aT, A1c), nA2 = fmaf(w2.z, aT, A2c);
+      const bool in_fp = evaluate_f(fi, fj, f, du, w2.w, w1, e);
+      const bool use = ((int)k < my_last) & in_fp & (e.alpha >= kAlphaMin);
+      // an entry that is not used leaves T and the colour in front as they are (colours are finite)
+      const float alpha = use ? e.alpha : 0.0f;
+      const float aT = alpha * T;
+      A0 = fmaf(w2.x, aT, A0);
+      A1 = fmaf(w2.y, aT, A1);
+      A2 = fmaf(w2.z, aT, A2);
+      const float gc = fmaf(g0, w2.x, fmaf(g1, w2.y, g2 * w2.z));
+      const float gb = fmaf(g0, out0 - A0, fmaf(g1, out1 - A1, g2 * (out2 - A2)));
       // hardware reciprocal (1 ulp): a correctly rounded division costs ~10 instructions
       // here and the gradient is not bit-compared
-      const float inv1ma = __builtin_amdgcn_rcpf(1.0f - e.alpha);
-      // dL/dalpha = sum_c g_c (colour_c T - (colour behind)_c / (1 - alpha))
-      const float dalpha = g0 * (w2.x * T - (out0 - nA0) * inv1ma) + g1 * (w2.y * T - (out1 - nA1) * inv1ma) +
-                           g2 * (w2.z * T - (out2 - nA2) * inv1ma);
-      const bool unclamped = use && (w1.w * e.G <= kAlphaMax);
-      // dL/dQ with G = exp2(-Q): dG/dQ = -ln2 G
-      const float gQ = unclamped ? -0.69314718055994531f * dalpha * w1.w * e.G : 0.0f;
+      const float one_a = 1.0f - alpha;
+      const float inv1ma = __builtin_amdgcn_rcpf(one_a);
+      // dL/dalpha = g . (colour T - (colour behind) / (1 - alpha))
+      const float dalpha = fmaf(-gb, inv1ma, T * gc);
+      const bool unclamped = use & (w1.w * e.G <= kAlphaMax);
       float c[kG];
+      // (selected, not multiplied by 0: an unused entry adds nothing to its record even where the
+      // loss gradient of the pixel is not finite)
       c[0] = use ? aT * g0 : 0.0f;
       c[1] = use ? aT * g1 : 0.0f;
       c[2] = use ? aT * g2 : 0.0f;
       c[3] = unclamped ? dalpha * e.G : 0.0f;
-      c[4] = gQ * e.p1;
-      c[5] = gQ * e.p2;
-      c[6] = gQ * e.dx * e.dx;
-      c[7] = gQ * e.dx * e.dy;
-      c[8] = gQ * e.dy * e.dy;
-      A0 = use ? nA0 : A0;
-      A1c = use ? nA1 : A1c;
-      A2c = use ? nA2 : A2c;
-      T = use ? T * (1.0f - e.alpha) : T;
+      c[4] = c[3] * e.p1;
+      c[5] = c[3] * e.p2;
+      const float cx = c[3] * e.dx, cy = c[3] * e.dy;
+      c[6] = cx * e.dx;
+      c[7] = cx * e.dy;
+      c[8] = cy * e.dy;
+      T *= one_a;
       const float sum = quad_sum9(c, lane);
-      if constexpr (DET) {
-        if (valid && r < kG) s_grad[((wid * 4 + qb.g) * BATCH + k) * kG + r] = sum;
-      } else {
-        if (valid && r < kG && sum != 0.0f) atomicAdd(&s_grad[k * kG + r], sum);
-      }
+      if (writes) my_pool[slot * kG] = sum;
     };
-    // two entries of the lane's quadrant list per trip, byte indices in one LDS
-    // read (entries past the quadrant's count: stale bytes, masked, not used)
-    for (int t = 0; t < max_cnt; t += 2) {
-      const uint32_t pk = *reinterpret_cast<const uint16_t*>(&my_list[t]);
-      const int ka = (int)(pk & (BATCH - 1)), kb = (int)((pk >> 8) & (BATCH - 1));
-      const float4 a0 = s_w0[ka], a1 = s_w1[ka], a2 = s_w2[ka];
-      const float4 b0 = s_w0[kb], b1 = s_w1[kb], b2 = s_w2[kb];
-      step(ka, t < my_cnt, a0, a1, a2);
-      step(kb, t + 1 < my_cnt, b0, b1, b2);
-    }
-    __syncthreads();
-    if constexpr (DET) {
-      for (int t = threadIdx.x; t < nb * kG; t += NT) {
+    // rounds over the staged records: as many of the next ones as the pool has room for
+    for (int k0 = 0, used = 0; k0 < nb;) {
+      constexpr uint32_t kNull = (uint32_t)(BATCH - 1) | ((uint32_t)Lds::kPool << KB);
+      uint4* lp = reinterpret_cast<uint4*>(&lds.list[wid][0][0]);
+      for (int k = lane; k < 4 * Lds::kStride * 2 / 16; k += 64)
+        lp[k] = make_uint4(kNull * 0x10001u, kNull * 0x10001u, kNull * 0x10001u, kNull * 0x10001u);
+      int k1 = 0;  // end of the round's records
+      int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
+#pragma unroll
+      for (int h = 0; h < BATCH / 64; ++h) {
+        const int k = h * 64 + lane;
+        const int first = hit_end[h] - (int)__popc(hits[h]) - used;
+        const bool fits = hit_end[h] - used <= Lds::kPool;
+        k1 += (int)__popcll(__ballot(fits));
+        const uint32_t mine = (fits & (k >= k0)) ? (hits[h] >> (4 * wid)) & 15u : 0u;
+        const int slot = first + (int)__popc(hits[h] & ((1u << (4 * wid)) - 1u));
+        auto append = [&](int g, int& c) {
+          const bool hit = (mine >> g) & 1u;
+          const uint64_t m = __ballot(hit);
+          if (hit)
+            lds.list[wid][g][c + (int)lanemask_lt_count(m)] =
+                (uint16_t)(k | ((slot + (int)__popc(mine & ((1u << g) - 1u))) << KB));
+          c += (int)__popcll(m);
+        };
+        append(0, c0);
+        append(1, c1);
+        append(2, c2);
+        append(3, c3);
+      }
+      k1 = min(k1, nb);
+      const int max_cnt = max(max(c0, c1), max(c2, c3));
+      // two entries of the lane's quadrant list per trip, in one LDS read (past the quadrant's count:
+      // the null record and its slot)
+      for (int t = 0; t < max_cnt; t += 2) {
+        const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
+        const uint32_t ka = pk & (BATCH - 1), kb = (pk >> 16) & (BATCH - 1);
+        const uint32_t sa = (pk & 0xFFFFu) >> KB, sb = pk >> (16 + KB);
+        const float a0 = s_du[ka], b0 = s_du[kb];
+        const float4 af = s_f[ka], a1 = s_w1[ka], a2 = s_w2[ka];
+        const float4 bf = s_f[kb], b1 = s_w1[kb], b2 = s_w2[kb];
+        step(ka, sa, a0, af, a1, a2);
+        step(kb, sb, b0, bf, b1, b2);
+      }
+      __syncthreads();
+      const int end_used = lds.end[k1 - 1];
+      for (uint32_t t = threadIdx.x; t < (uint32_t)((k1 - k0) * kG); t += NT) {
+        const uint32_t kk = t / kG, q = t - kk * kG, k = (uint32_t)k0 + kk;
+        const int n = (int)__popc(lds.hits((int)k));
+        const float* p = s_pool + (uint32_t)((int)lds.end[k] - n - used) * kG + q;
         float v = 0.0f;
-        for (int q = 0; q < lds.kQuads; ++q) v += s_grad[q * BATCH * kG + t];
-        const int k = t / kG;
-        const int64_t slot = det_slot<TW, TH>(det, s_rec[k], __float_as_uint(s_w0[k].z),
-                                              __float_as_uint(s_w0[k].w), txi, tyi);
-        if (slot < det.slots) det.partial[slot * kG + (t - k * kG)] = v;
+        for (int h = 0; h < n; ++h, p += kG) v += *p;
+        if constexpr (DET) {
+          const float4 f = s_f[k];
+          const int64_t slot = det_slot<TW, TH>(det, s_rec[k], (int)f.x, (int)(f.x + f.z), (int)f.y, txi, tyi);
+          if (slot < det.slots) det.partial[slot * kG + q] = v * q_scale((int)q, s_w1[k].w);
+        } else {
+          if (v != 0.0f) unsafeAtomicAdd(&grad2d[(int64_t)s_rec[k] * kG + q], v * q_scale((int)q, s_w1[k].w));
+        }
       }
-    } else {
-      for (int t = threadIdx.x; t < nb * kG; t += NT) {
-        const float v = s_grad[t];
-        if (v != 0.0f) unsafeAtomicAdd(&grad2d[(int64_t)s_rec[t / kG] * kG + (t % kG)], v);
-      }
+      used = end_used;
+      k0 = k1;
+      __syncthreads();
     }
-    __syncthreads();
   }
   if constexpr (DET) {
     // entries behind every pixel's last one were not walked: their slots get zeros
@@ -239,7 +373,8 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     for (uint32_t k = (uint32_t)tile_last + threadIdx.x; k < len; k += NT) {
       const uint32_t rid = pair_records[start + k];
       const uint4 w0 = *reinterpret_cast<const uint4*>(&records[rid]);
-      const int64_t slot = det_slot<TW, TH>(det, rid, w0.z, w0.w, txi, tyi);
+      const int64_t slot = det_slot<TW, TH>(det, rid, (int)(w0.z & 0xFFFFu),
+                                            (int)((w0.z & 0xFFFFu) + (w0.z >> 16)), (int)(w0.w & 0xFFFFu), txi, tyi);
       if (slot < det.slots)
 #pragma unroll
         for (int q = 0; q < kG; ++q) det.partial[slot * kG + q] = 0.0f;
@@ -248,13 +383,14 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
 }
 
 template <int TW, int TH, int BATCH, bool DET>
-__global__ void __launch_bounds__(TW* TH) raster_bwd_kernel(TileArgs ta, uint32_t* queue,
+__global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(TW * TH >= 128 ? 6 : 1)))
+raster_bwd_kernel(TileArgs ta, uint32_t* queue,
                                                             const float* __restrict__ rgb,
                                                             const float* __restrict__ T_final,
                                                             const int32_t* __restrict__ n_last,
                                                             const float* __restrict__ d_rgb,
                                                             float* __restrict__ grad2d, DetArgs det) {
-  __shared__ BwdLds<TW, TH, BATCH, DET> lds;
+  __shared__ BwdLds<TW, TH, BATCH> lds;
   for_each_tile(ta, queue, 1, [&](int tile_g) {
     raster_bwd_tile<TW, TH, BATCH, DET>(ta, lds, tile_g, rgb, T_final, n_last, d_rgb, grad2d, det);
   });
@@ -789,21 +925,12 @@ void launch_bwd(int batch, bool det, const TileArgs& ta, uint32_t* queue, hipStr
                 const float* T, const int32_t* nl, const float* drgb, float* g2d, const DetArgs& d) {
   constexpr int NT = TW * TH;
   const dim3 grid = tile_grid(ta.n_tiles, queue != nullptr);
-  if (det) {
-    // per-quadrant slots: 64 staged records per round (32 for the largest tile), under 40 KB of LDS
-    constexpr int DB = TW * TH > 256 ? 32 : 64;
-    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, DB, true>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb, g2d,
-                       d);
-  } else if (batch == 64) {
-    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 64, false>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
-                       g2d, d);
-  } else if (batch == 128) {
-    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 128, false>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
-                       g2d, d);
-  } else {
-    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 256, false>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
-                       g2d, d);
-  }
+  // at most 128 records per round: a larger batch would only wait for room in the pool
+  auto launch = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb, g2d, d);
+  };
+  if (batch == 64) launch(det ? raster_bwd_kernel<TW, TH, 64, true> : raster_bwd_kernel<TW, TH, 64, false>);
+  else launch(det ? raster_bwd_kernel<TW, TH, 128, true> : raster_bwd_kernel<TW, TH, 128, false>);
 }
 
 // workspace: grad2d [rc][kG]; deterministic mode adds cnt [rc], base [rc], a

@@ -1,7 +1,7 @@
 // Pieces shared by the per-tile compositing kernels (forward and adjoint):
 // evaluation of a record at a pixel, the lane -> pixel map, per-group record
 // lists, the tile arguments and the work distribution over tiles.  Included by
-// translation units compiled with -ffp-contract=off: evaluate() is the
+// translation units compiled with -ffp-contract=off: evaluate_f() is the
 // operation order both kernels must share.
 #pragma once
 
@@ -15,12 +15,6 @@ struct Eval {
   float dx, dy, p1, p2, G, alpha;
 };
 
-__device__ __forceinline__ bool in_footprint(int i, int j, uint32_t px, uint32_t py, int& di, int& dj) {
-  di = i - (int)(px & 0xFFFFu);
-  dj = j - (int)(py & 0xFFFFu);
-  return ((uint32_t)di <= (px >> 16)) && ((uint32_t)dj <= (py >> 16));
-}
-
 // Gaussian and alpha at offset (dx, dy) from the projected mean
 __device__ __forceinline__ void evaluate_at(const float4& w1, Eval& e) {
   e.p1 = fmaf(w1.x, e.dx, w1.y * e.dy);
@@ -29,18 +23,12 @@ __device__ __forceinline__ void evaluate_at(const float4& w1, Eval& e) {
   e.alpha = fminf(kAlphaMax, w1.w * e.G);
 }
 
-__device__ __forceinline__ void evaluate(const float4& w0, const float4& w1, const float4& w2, int di, int dj,
-                                         Eval& e) {
-  e.dx = (float)di - w0.x;  // w0.x = u - i0 - 1/2
-  e.dy = (float)dj - w2.w;  // w2.w = v - j0 - 1/2
-  evaluate_at(w1, e);
-}
-
-// The same with the footprint given as floats f = (i0, j0, i1 - i0, j1 - j0),
-// for a pixel (fi, fj) as floats: fi - i0 is exact (integers below 2^24), so dx
-// equals the value above bit for bit, and the footprint test is one unsigned
-// compare of float bits per axis (a non-negative float's bits grow with its
-// value; a negative difference has the sign bit set and fails).
+// Evaluation at pixel (fi, fj) of a record with footprint f = (i0, j0, i1 - i0,
+// j1 - j0), all as floats, du = u - i0 - 1/2 and dv likewise; true if the
+// footprint holds the pixel.  fi - i0 is exact (integers below 2^24), so dx has
+// one rounding, and the footprint test is one unsigned compare of float bits per
+// axis (a non-negative float's bits grow with its value; a negative difference
+// has the sign bit set and fails).
 __device__ __forceinline__ bool evaluate_f(float fi, float fj, const float4& f, float du, float dv,
                                            const float4& w1, Eval& e) {
   const float fdi = fi - f.x, fdj = fj - f.y;
@@ -49,7 +37,6 @@ __device__ __forceinline__ bool evaluate_f(float fi, float fj, const float4& f, 
   evaluate_at(w1, e);
   return (__float_as_uint(fdi) <= __float_as_uint(f.z)) && (__float_as_uint(fdj) <= __float_as_uint(f.w));
 }
-
 
 // Lane -> pixel map of the tile kernels: the tile is cut into 8x8 pixel
 // blocks, one per wave (wave w is block (w mod TW/8, w div TW/8)); each block
@@ -81,15 +68,15 @@ struct LaneMap {
 template <int BATCH>
 constexpr int kListStride = BATCH + 4;
 
+__device__ __forceinline__ float4 footprint_floats(const float4& w0) {
+  const uint32_t px = __float_as_uint(w0.z), py = __float_as_uint(w0.w);
+  return make_float4((float)(px & 0xFFFFu), (float)(py & 0xFFFFu), (float)(px >> 16), (float)(py >> 16));
+}
+
 // Per-group lists: list[g][0 .. cnt[g]) receives, in ascending (= depth) order,
 // the staged records that may contribute to a pixel of group g of the wave's
 // block.  The counts are a struct of named scalars (arrays of them end up in
 // scratch memory).
-struct Counts4 {
-  int c0, c1, c2, c3;
-  __device__ __forceinline__ int max() const { return ::max(::max(c0, c1), ::max(c2, c3)); }
-  __device__ __forceinline__ int of(int g) const { return g == 0 ? c0 : g == 1 ? c1 : g == 2 ? c2 : c3; }
-};
 struct Counts8 {
   int c0, c1, c2, c3, c4, c5, c6, c7;
   __device__ __forceinline__ int max() const {
@@ -124,27 +111,34 @@ __device__ __forceinline__ float q_limit(float opac) { return __builtin_amdgcn_l
 // bit for bit.  The margins cover the rounding of this estimate (a few ulp of
 // the summed terms, FP32) hundreds of times over; a NaN keeps the record.
 struct GroupTest {
-  int i0, i1, j0, j1;
-  float p1, m1, sx, sy;  // p1 at the centre of the block's first group, half range, steps per pixel
+  float i0, i1, j0, j1;  // footprint relative to the first group's first pixel
+  float p1, m1, sx, sy;  // p1 at the centre of the first group, half range, steps per pixel
   float p2, m2, sy2;
   float q;
+  // f, du, dv: as for evaluate_f; (x0, y0): first pixel of the first group; the groups tested lie
+  // within 32 pixels of it
   template <int GW, int GH>
-  __device__ __forceinline__ void load(const float4& w0, const float4& w1, float dv, int x0, int y0) {
-    const uint32_t px = __float_as_uint(w0.z), py = __float_as_uint(w0.w);
-    i0 = (int)(px & 0xFFFFu), i1 = i0 + (int)(px >> 16);
-    j0 = (int)(py & 0xFFFFu), j1 = j0 + (int)(py >> 16);
-    q = w0.y;
-    const float dx = ((float)(x0 - i0) + 0.5f * (GW - 1)) - w0.x;
-    const float dy = ((float)(y0 - j0) + 0.5f * (GH - 1)) - dv;
+  __device__ __forceinline__ void load(const float4& f, float du, float dv, const float4& w1, float q_lim, int x0,
+                                       int y0) {
+    i0 = f.x - (float)x0, i1 = i0 + f.z;
+    j0 = f.y - (float)y0, j1 = j0 + f.w;
+    q = q_lim;
+    const float dx = (0.5f * (GW - 1) - i0) - du;
+    const float dy = (0.5f * (GH - 1) - j0) - dv;
     sx = w1.x, sy = w1.y, sy2 = w1.z;
     p1 = fmaf(sx, dx, sy * dy);
     p2 = sy2 * dy;
     const float ax = fabsf(sx), ay = fabsf(sy), a2 = fabsf(sy2);
-    const float ex = fabsf(dx) + 8.0f, ey = fabsf(dy) + 8.0f;  // largest offsets over the 8x8 block
+    const float ex = fabsf(dx) + 32.0f, ey = fabsf(dy) + 32.0f;  // largest offsets tested
     m1 = fmaf(0.5f * (GW - 1), ax, fmaf(0.5f * (GH - 1), ay, fmaf(1e-5f, fmaf(ax, ex, ay * ey), 1e-3f)));
     m2 = fmaf(0.5f * (GH - 1), a2, fmaf(1e-5f, a2 * ey, 1e-3f));
   }
-  // squared lower bound of |p2| over the rows of groups `r` (in pixels from the first)
+  // the footprint meets the group whose first pixel is (c, r) from (x0, y0)
+  template <int GW, int GH>
+  __device__ __forceinline__ bool meets(float c, float r) const {
+    return (i0 <= c + (GW - 1)) & (i1 >= c) & (j0 <= r + (GH - 1)) & (j1 >= r);
+  }
+  // squared lower bound of |p2| over the groups of row r
   __device__ __forceinline__ float row(float r) const {
     const float a = fmaxf(fabsf(fmaf(sy2, r, p2)) - m2, 0.0f);
     return a * a;
@@ -176,35 +170,11 @@ __device__ __forceinline__ int wave_candidates(const float4* s_w0, int nb, int x
   return c;
 }
 
-// 4x4 quadrants (groups 0..3 row-major over the 8x8 block).  s_w0[k].y holds
-// q_limit of the record (its view is not needed once staged).
+// 4x2 groups (two columns of four pixels, four rows of two; row-major).  s_w0[k].y
+// holds q_limit of the record (its view is not needed once staged).
 template <int BATCH>
-__device__ __forceinline__ Counts4 wave_compact4(const float4* s_w0, const float4* s_w1, const float4* s_w2, int nb,
-                                                 int x0, int y0, uint8_t* cand,
-                                                 uint8_t (*list)[kListStride<BATCH>]) {
-  const int lane = threadIdx.x & 63;
-  const int nc = wave_candidates<BATCH>(s_w0, nb, x0, y0, cand);
-  Counts4 c{0, 0, 0, 0};
-  for (int base = 0; base < nc; base += 64) {
-    const bool in = base + lane < nc;
-    const int k = in ? (int)cand[base + lane] : 0;
-    GroupTest t;
-    t.load<4, 4>(s_w0[k], s_w1[k], s_w2[k].w, x0, y0);
-    const bool xa = in && t.i0 <= x0 + 3, xb = in && t.i1 >= x0 + 4;
-    const bool ya = t.j0 <= y0 + 3, yb = t.j1 >= y0 + 4;
-    const float r0 = t.row(0.0f), r1 = t.row(4.0f);
-    append_if(xa && ya && t.reach(0.0f, 0.0f, r0), list[0], c.c0, k);
-    append_if(xb && ya && t.reach(4.0f, 0.0f, r0), list[1], c.c1, k);
-    append_if(xa && yb && t.reach(0.0f, 4.0f, r1), list[2], c.c2, k);
-    append_if(xb && yb && t.reach(4.0f, 4.0f, r1), list[3], c.c3, k);
-  }
-  return c;
-}
-
-// 4x2 groups (two columns of four pixels, four rows of two; row-major)
-template <int BATCH>
-__device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float4* s_w1, const float4* s_w2, int nb,
-                                                 int x0, int y0, uint8_t* cand,
+__device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float4* s_f, const float4* s_w1,
+                                                 const float4* s_w2, int nb, int x0, int y0, uint8_t* cand,
                                                  uint8_t (*list)[kListStride<BATCH>]) {
   const int lane = threadIdx.x & 63;
   const int nc = wave_candidates<BATCH>(s_w0, nb, x0, y0, cand);
@@ -212,19 +182,20 @@ __device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float
   for (int base = 0; base < nc; base += 64) {
     const bool in = base + lane < nc;
     const int k = in ? (int)cand[base + lane] : 0;
+    const float4 w0 = s_w0[k];
     GroupTest t;
-    t.load<4, 2>(s_w0[k], s_w1[k], s_w2[k].w, x0, y0);
-    const bool xa = in && t.i0 <= x0 + 3, xb = in && t.i1 >= x0 + 4;  // a candidate meets the block
-    auto rows = [&](int r, uint8_t* la, int& ca, uint8_t* lb, int& cb) {
-      const bool y = t.j0 <= y0 + r + 1 && t.j1 >= y0 + r;
-      const float r2 = t.row((float)r);
-      append_if(xa && y && t.reach(0.0f, (float)r, r2), la, ca, k);
-      append_if(xb && y && t.reach(4.0f, (float)r, r2), lb, cb, k);
+    t.load<4, 2>(s_f[k], w0.x, s_w2[k].w, s_w1[k], w0.y, x0, y0);
+    const bool xa = in & (t.i0 <= 3.0f), xb = in & (t.i1 >= 4.0f);  // a candidate meets the block
+    auto rows = [&](float r, uint8_t* la, int& ca, uint8_t* lb, int& cb) {
+      const bool y = (t.j0 <= r + 1.0f) & (t.j1 >= r);
+      const float r2 = t.row(r);
+      append_if(xa & y & t.reach(0.0f, r, r2), la, ca, k);
+      append_if(xb & y & t.reach(4.0f, r, r2), lb, cb, k);
     };
-    rows(0, list[0], c.c0, list[1], c.c1);
-    rows(2, list[2], c.c2, list[3], c.c3);
-    rows(4, list[4], c.c4, list[5], c.c5);
-    rows(6, list[6], c.c6, list[7], c.c7);
+    rows(0.0f, list[0], c.c0, list[1], c.c1);
+    rows(2.0f, list[2], c.c2, list[3], c.c3);
+    rows(4.0f, list[4], c.c4, list[5], c.c5);
+    rows(6.0f, list[6], c.c6, list[7], c.c7);
   }
   return c;
 }
