@@ -17,9 +17,11 @@
 // atomics, and those bounded the kernel (about 50 LDS cycles for the 36 lanes of a
 // step, LDS busy 92 % of the time; a store takes two).  Now VALU issue bounds it.
 // Measured, 16 views of a 2M-Gaussian block at 1600x900: 5.16 ms with LDS atomics,
-// 3.88 with slots; 4096 Gaussians at 256x256 76 -> 66 us (one work-group per CU:
-// the chain of steps); one 1M-Gaussian 1920x1080 view 102 -> 73 us.  Six waves per
-// SIMD (a few spills outside the loop) against five: 3.88 against 4.12 ms.
+// 3.75 with slots and the moments below; 4096 Gaussians at 256x256 76 -> 64 us
+// (one work-group per CU: the chain of steps); one 1M-Gaussian 1920x1080 view 102 ->
+// 73 us.  Six waves per SIMD (a few spills outside the loop) against five: 3.88
+// against 4.12 ms.
+#include "scan.h"
 #include "tile.h"
 
 namespace gs {
@@ -76,9 +78,13 @@ __device__ __forceinline__ int quad_value(int r) {
 }
 __device__ __forceinline__ bool quad_writes(int r) { return !(r & 1) || r == 1; }
 
-// Partials per Gaussian: r, g, b, opacity, A1, A2, Axx, Axy, Ayy.  The last five
-// are derivatives by the exponent Q; inside a tile they are summed without their
-// common factor -ln2 opac (dG/dQ = -ln2 G), which the flush applies once.
+// Partials per Gaussian: r, g, b, opacity, and with w = dL/dQ per pixel the sums
+// of w p1, w p2, w p1^2, w p1 p2, w p2^2 (p = F d: the pixel's offset in the
+// coordinates in which the Gaussian is round, Q = p1^2 + p2^2).  The second moments
+// are taken of p and not of the offset d because dL/dSigma = -K (sum w d d^T) K
+// with K ~ F^T F: for an elongated splat the moments of d cancel in it, those of p
+// do not.  The sums over w leave out the factor -ln2 opac inside a tile
+// (dG/dQ = -ln2 G); the flush applies it once.
 constexpr int kG = 9;
 constexpr int kGQ = 4;  // first partial with that factor
 __device__ __forceinline__ float q_scale(int q, float opac) { return q >= kGQ ? -0.69314718055994531f * opac : 1.0f; }
@@ -118,20 +124,6 @@ struct BwdLds {
     else return reinterpret_cast<const uint32_t*>(mask)[k];
   }
 };
-
-// inclusive prefix sum over the wave (DPP: within rows, then across)
-template <int CTRL, int ROWS>
-__device__ __forceinline__ int dpp_add(int v) {
-  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
-}
-__device__ __forceinline__ int wave_incl_scan(int v) {
-  v = dpp_add<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
-  v = dpp_add<0x112, 0xF>(v);
-  v = dpp_add<0x114, 0xF>(v);
-  v = dpp_add<0x118, 0xF>(v);
-  v = dpp_add<0x142, 0xA>(v);  // row_bcast 15 into rows 1 and 3
-  return dpp_add<0x143, 0xC>(v);  // row_bcast 31 into rows 2 and 3
-}
 
 // Deterministic mode: per-(tile, record) partials are stored at slot
 // base[record] + (the tile's row-major index within the record's footprint
@@ -295,10 +287,9 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
       c[3] = unclamped ? dalpha * e.G : 0.0f;
       c[4] = c[3] * e.p1;
       c[5] = c[3] * e.p2;
-      const float cx = c[3] * e.dx, cy = c[3] * e.dy;
-      c[6] = cx * e.dx;
-      c[7] = cx * e.dy;
-      c[8] = cy * e.dy;
+      c[6] = c[4] * e.p1;
+      c[7] = c[4] * e.p2;
+      c[8] = c[5] * e.p2;
       T *= one_a;
       const float sum = quad_sum9(c, lane);
       if (writes) my_pool[slot * kG] = sum;
@@ -693,7 +684,7 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
   const float n0 = M[0][0] * M[0][0] + M[0][1] * M[0][1] + M[0][2] * M[0][2];
   const float n1 = M[1][0] * M[1][0] + M[1][1] * M[1][1] + M[1][2] * M[1][2];
   const float sb = M[0][0] * M[1][0] + M[0][1] * M[1][1] + M[0][2] * M[1][2];
-  const float sa = n0 + 0.3f, sc2 = n1 + 0.3f;
+  const float sc2 = n1 + 0.3f;
   const float cr0 = M[0][1] * M[1][2] - M[0][2] * M[1][1];
   const float cr1 = M[0][2] * M[1][0] - M[0][0] * M[1][2];
   const float cr2 = M[0][0] * M[1][1] - M[0][1] * M[1][0];
@@ -705,15 +696,14 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
   const float cc = kS / sqrtf(sc2);
   const float gu = -2.0f * ca * p2[4];
   const float gv = -2.0f * (cb * p2[4] + cc * p2[5]);
-  const float gA = kS2 * p2[6], gB = 2.0f * kS2 * p2[7], gC = kS2 * p2[8];
-  // conic K = Sigma2D^-1;  dL/dSigma = -K Gk K with Gk = [[gA, gB/2], [gB/2, gC]]
-  const float KA = sc2 / det, KB = -sb / det, KC = sa / det;
-  const float h = 0.5f * gB;
-  const float t00 = gA * KA + h * KB, t01 = gA * KB + h * KC;
-  const float t10 = h * KA + gC * KB, t11 = h * KB + gC * KC;
-  const float S00 = -(KA * t00 + KB * t10);
-  const float S01 = -(KA * t01 + KB * t11);
-  const float S11 = -(KB * t01 + KC * t11);
+  // conic K = Sigma2D^-1 = F^T F / kS2, F = [[ca, cb], [0, cc]]:
+  // dL/dSigma = -K (kS2 sum w d d^T) K = -F^T P F / kS2 with P the second moments of p = F d
+  const float P11 = p2[6], P12 = p2[7], P22 = p2[8];
+  const float h2 = fmaf(cb, P11, cc * P12);
+  const float h3 = fmaf(cb, P12, cc * P22);
+  const float S00 = -ca * ca * P11 / kS2;
+  const float S01 = -ca * h2 / kS2;
+  const float S11 = -fmaf(cb, h2, cc * h3) / kS2;
   // Sigma2D = M M^T + 0.3 I -> dL/dM = 2 Gs M; M = J WL; WL = R_cam Rq diag(s), one column at a time
   float dJ00 = 0.f, dJ02 = 0.f, dJ11 = 0.f, dJ12 = 0.f;
   float ds[3], dRq[3][3];
@@ -925,12 +915,19 @@ void launch_bwd(int batch, bool det, const TileArgs& ta, uint32_t* queue, hipStr
                 const float* T, const int32_t* nl, const float* drgb, float* g2d, const DetArgs& d) {
   constexpr int NT = TW * TH;
   const dim3 grid = tile_grid(ta.n_tiles, queue != nullptr);
-  // at most 128 records per round: a larger batch would only wait for room in the pool
-  auto launch = [&](auto kernel) {
-    hipLaunchKernelGGL(kernel, grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb, g2d, d);
-  };
-  if (batch == 64) launch(det ? raster_bwd_kernel<TW, TH, 64, true> : raster_bwd_kernel<TW, TH, 64, false>);
-  else launch(det ? raster_bwd_kernel<TW, TH, 128, true> : raster_bwd_kernel<TW, TH, 128, false>);
+  // at most 128 staged records: a larger batch would only wait for room in the pool
+  if (batch == 64 && det)
+    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 64, true>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb, g2d,
+                       d);
+  else if (batch == 64)
+    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 64, false>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
+                       g2d, d);
+  else if (det)
+    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 128, true>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
+                       g2d, d);
+  else
+    hipLaunchKernelGGL((raster_bwd_kernel<TW, TH, 128, false>), grid, dim3(NT), 0, s, ta, queue, rgb, T, nl, drgb,
+                       g2d, d);
 }
 
 // workspace: grad2d [rc][kG]; deterministic mode adds cnt [rc], base [rc], a

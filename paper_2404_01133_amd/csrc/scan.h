@@ -16,6 +16,20 @@ __device__ __forceinline__ void raise_flag(int64_t* counts, int64_t bit) {
   atomicOr((unsigned long long*)&counts[GS_COUNT_FLAGS], (unsigned long long)bit);
 }
 
+// inclusive prefix sum over a wave, every lane active (DPP: within rows of 16, then across)
+template <int CTRL, int ROWS>
+__device__ __forceinline__ int dpp_add(int v) {
+  return v + __builtin_amdgcn_update_dpp(0, v, CTRL, ROWS, 0xF, false);
+}
+__device__ __forceinline__ int wave_incl_scan(int v) {
+  v = dpp_add<0x111, 0xF>(v);  // row_shr 1, 2, 4, 8
+  v = dpp_add<0x112, 0xF>(v);
+  v = dpp_add<0x114, 0xF>(v);
+  v = dpp_add<0x118, 0xF>(v);
+  v = dpp_add<0x142, 0xA>(v);     // row_bcast 15 into rows 1 and 3
+  return dpp_add<0x143, 0xC>(v);  // row_bcast 31 into rows 2 and 3
+}
+
 // 64-bit status word of one scan tile: 2 flag bits (none / aggregate /
 // inclusive prefix) over a 62-bit value.  Zero means "not published yet".
 constexpr uint64_t kFlagAgg64 = 1ull << 62;
