@@ -180,7 +180,7 @@ PartWs part_ws_layout(char* base, int64_t n) {
     off += (bytes + 255) & ~(size_t)255;
     return p;
   };
-  const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
+  const int64_t ntiles = radix_tiles(n);
   w.n_words = 8 + 2 * kRadix + 2 * ntiles * kRadix;
   w.words = (uint32_t*)take(4 * (size_t)w.n_words);
   w.hist = w.words ? w.words + 8 : nullptr;
@@ -240,24 +240,23 @@ extern "C" gs_status gs_partition(const float* means, int64_t n, const double* x
   PartWs w = part_ws_layout((char*)ws, n);
   a.zr = w.words;
   const int passes = B > kRadix ? 2 : 1;
-  const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
+  const int64_t ntiles = radix_tiles(n);
   hipLaunchKernelGGL(part_clear_kernel, dim3(grid_of(w.n_words, 2048)), dim3(256), 0, s, w.words, w.n_words,
                      w.counts, n);
   hipLaunchKernelGGL(zrange_kernel, dim3(grid_of(n, 1024)), dim3(256), 0, s, means + 2 * n, n, w.words);
   hipLaunchKernelGGL(part_ids_kernel, dim3(grid_of(n, 2048)), dim3(kThreads), 0, s, a, w.k0, w.v0, block_id, passes,
                      w.hist);
   GS_LAUNCH_CHECK();
-  const unsigned rgrid = (unsigned)(ntiles < 1024 ? ntiles : 1024);
   const uint32_t* kin = w.k0;
   const uint32_t* vin = w.v0;
   for (int p = 0; p < passes; ++p) {
     const bool last = p == passes - 1;
     uint32_t* kout = (p % 2 == 0) ? w.k1 : w.k0;
     uint32_t* vout = last ? perm : ((p % 2 == 0) ? w.v1 : w.v0);
-    hipLaunchKernelGGL((radix_pass_kernel<kPassPlain>), dim3(rgrid), dim3(kThreads), 0, s, kin, vin, kout, vout,
-                       (const int64_t*)w.counts, GS_COUNT_RECORDS, n, 8 * p, w.hist + p * kRadix,
-                       w.status + (int64_t)p * ntiles * kRadix, (int64_t)kRadix, w.words + 2 + p, w.counts,
-                       PairPass{});
+    const RadixPass ra{kin, vin, kout, vout, w.counts, GS_COUNT_RECORDS, GS_COUNT_RECORDS, n, 8 * p, 8,
+                       w.hist + p * kRadix, nullptr, 0, 0, w.status + (int64_t)p * ntiles * kRadix, (int64_t)kRadix,
+                       w.words + 2 + p, w.counts, nullptr};
+    hipLaunchKernelGGL((radix_pass_kernel<8, false>), radix_grid(n), dim3(kRadixThreads), 0, s, ra);
     GS_LAUNCH_CHECK();
     kin = kout;
     vin = vout;

@@ -1,9 +1,22 @@
-// Stable single-pass LSD radix pass over 8-bit digits (onesweep style), shared
-// by the tile binning and the block partition.  Work-groups take tiles of
-// kRadixTile keys from an atomic counter in launch order, rank their keys with
-// wave64 ballot multisplit, publish per-digit tile counts and walk back over
-// the predecessors' published counts (decoupled look-back), then scatter
-// through LDS so the global writes of each digit run are contiguous.
+// Stable single-pass LSD radix pass (onesweep style), shared by the tile binning
+// and the block partition.  Work-groups take tiles of keys from an atomic counter
+// in launch order, rank their keys with wave64 ballot multisplit, publish
+// per-digit tile counts and walk back over the predecessors' published counts
+// (decoupled look-back), then scatter through LDS so the global writes of each
+// digit run are contiguous.
+//
+// A work-group is 1024 threads with one tile in LDS (up to 16384 keys, 150 KB):
+// one per CU.  What bounds a pass is the serial part of a tile and the look-back
+// chain, not the bytes: 256-thread work-groups with 4096-key tiles took 12.7 us for
+// a single tile (sixteen items ranked one after the other), and a pass over 4M keys
+// had a chain of 980 tiles that all publish at about the same time.  Here a small
+// input is cut into tiles of four items per thread, and a large one into tiles of
+// sixteen, 245 for 4M keys, whose look-back reads 32 predecessors at a time.
+// Mean per pass, us, before -> now: 4096 keys 12.7 -> 7.9; 0.5M to 0.8M keys
+// 19.2 -> 15.9; 4M to 6.3M keys 52.5 -> 41.1; 12.6M 91 -> 76 (tiles of the old
+// shape, ranking by 64-bit selects, against this).  Reading 64 predecessors at a
+// time spilled registers (49 at 4M); a run-time item count made the loads of a
+// thread wait for one another (66).
 #pragma once
 
 #include "scan.h"
@@ -12,45 +25,44 @@ namespace gs {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kItems = 8;
-constexpr int kTile = kThreads * kItems;  // 2048 elements per scan tile
-constexpr int kRadixItems = 16;
-constexpr int kRadixTile = kThreads * kRadixItems;  // 4096 keys per radix tile
 constexpr int kRadix = 256;
 constexpr uint32_t kFlagAgg = 1u << 30;
 constexpr uint32_t kFlagInc = 2u << 30;
 constexpr uint32_t kValMask = (1u << 30) - 1;
-constexpr int kLookWindow = 8;  // look-back words read per round by one digit's thread
 
-// ---------------------------------------------------------------------------
-// block-level exclusive scan of one u32 per thread (256 threads, 4 waves)
-// ---------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t block_excl_scan(uint32_t x, uint32_t* s_wave, uint32_t* total) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  uint32_t inc = x;
-  for (int off = 1; off < 64; off <<= 1) {
-    const uint32_t y = __shfl_up(inc, off, 64);
-    if (lane >= off) inc += y;
-  }
-  if (lane == 63) s_wave[wid] = inc;
-  __syncthreads();
-  uint32_t wave_base = 0, tot = 0;
-  for (int w = 0; w < kThreads / 64; ++w) {
-    const uint32_t s = s_wave[w];
-    if (w < wid) wave_base += s;
-    tot += s;
-  }
-  *total = tot;
-  __syncthreads();
-  return wave_base + inc - x;
-}
+constexpr int kRadixThreads = 1024;
+constexpr int kRadixWaves = kRadixThreads / 64;
+constexpr int kRadixMaxItems = 16;
+constexpr int kRadixBlocks = 256;  // one work-group per CU (its LDS is nearly the CU's)
+constexpr int kRadixMaxCopies = 7;  // partial histograms beside `hist`
+constexpr int kLookWindow = 8;     // look-back words read per round by one thread
 
-// saturating u32 sum (values past 2^32 - 1 only ever mean "beyond every capacity")
-__device__ __forceinline__ uint32_t sat_add(uint32_t a, uint32_t b) {
-  const uint32_t c = a + b;
-  return c < a ? 0xFFFFFFFFu : c;
+// Keys per thread of a pass over n keys: 4, 8, 12 or 16.  A small input spreads
+// over the chip, up to 4M keys there is one tile per work-group; beyond that, as
+// few rounds of tiles per work-group as their size allows, of equal size (6.3M
+// keys: two rounds of twelve keys per thread, not one and a half of sixteen).
+__host__ __device__ constexpr int radix_items(int64_t n) {
+  const int64_t rows = (n + kRadixThreads - 1) / kRadixThreads;
+  if (rows <= 128) return 4;
+  if (rows <= 1024) return 8;
+  if (rows <= (int64_t)kRadixBlocks * kRadixMaxItems) return kRadixMaxItems;
+  const int64_t rounds = (rows + kRadixBlocks * kRadixMaxItems - 1) / (kRadixBlocks * kRadixMaxItems);
+  return (int)((rows + 4 * kRadixBlocks * rounds - 1) / (4 * kRadixBlocks * rounds)) * 4;
 }
-__device__ __forceinline__ uint32_t sat_u32(uint64_t v) { return v > 0xFFFFFFFFull ? 0xFFFFFFFFu : (uint32_t)v; }
+__host__ __device__ constexpr int64_t radix_tiles(int64_t n) {
+  const int64_t t = (int64_t)kRadixThreads * radix_items(n);
+  return (n + t - 1) / t;
+}
+// upper bound of radix_tiles(m) over all m <= n
+__host__ __device__ constexpr int64_t radix_tiles_bound(int64_t n) {
+  const int64_t rows = (n + kRadixThreads - 1) / kRadixThreads;
+  if (rows <= 128) return (rows + 3) / 4;
+  if (rows <= 256) return 32;
+  if (rows <= 1024) return (rows + 7) / 8;
+  if (rows <= 2048) return 128;
+  if (rows <= (int64_t)kRadixBlocks * kRadixMaxItems) return (rows + kRadixMaxItems - 1) / kRadixMaxItems;
+  return (rows + kRadixBlocks * kRadixMaxItems - 1) / (kRadixBlocks * kRadixMaxItems) * kRadixBlocks;
+}
 
 // block-level exclusive scan of one u64 per thread (256 threads, 4 waves)
 __device__ __forceinline__ uint64_t block_excl_scan64(uint64_t x, uint64_t* s_wave64, uint64_t* total) {
@@ -73,360 +85,311 @@ __device__ __forceinline__ uint64_t block_excl_scan64(uint64_t x, uint64_t* s_wa
   return wave_base + inc - x;
 }
 
-// Variants of a pass (template argument MODE):
-//   kPassPlain    sort (key, value) pairs
-//   kPassPairs    the most significant depth pass of the binning: besides the
-//                 sorted record ids it writes each record's first pair slot, the
-//                 exclusive prefix of tiles_touched in the sorted order
-//                 (saturating at 2^32 - 1).  Per (radix tile, digit) one 64-bit
-//                 look-back word carries both the record count (bits 32..61) and
-//                 the pair sum (bits 0..31, saturating).  whist holds `copies`
-//                 partial histograms of tiles_touched by this digit (u64).
-//                 A record's tile rectangle comes from its footprint word (the
-//                 first 16 bytes of its record, gathered once here): the pass
-//                 also writes, in the sorted order, its first tile id (view *
-//                 tiles per view + row * tiles_x + column) and its extent in
-//                 tiles (columns | rows << 16), so the emission reads them in
-//                 order instead of gathering every record again.
-//   kPassCompact  the least significant depth pass: reads every selected record's
-//                 depth key, keeps those with tiles_touched > 0 (values = record
-//                 index, in index order) and writes the visible count.
-// hist_extra: `hist_copies` further partial copies of the digit histogram
-// (stride hist_stride) that the pass adds to `hist` itself.
-constexpr int kPassPlain = 0;
-constexpr int kPassPairs = 1;
-constexpr int kPassCompact = 2;
-struct PairPass {
-  const int32_t* tiles_touched;  // kPassCompact
-  const uint4* rec_words;        // kPassPairs: records as 16-byte words, kRecordWords per record
-  int tw_shift, th_shift;        // log2 of the tile shape (every supported shape is a power of two)
-  int tiles_x, tiles_per_view;
-  uint32_t* tile_first;          // [visible] first tile id, sorted order
-  uint32_t* tile_extent;         // [visible] columns | rows << 16, sorted order
-  const uint64_t* whist;
-  int copies;
-  uint64_t* status;  // [radix tiles][256]
-  uint32_t* pair_off;
-  int64_t pair_cap;
-  const uint32_t* hist_extra;
+// ---------------------------------------------------------------------------
+// one stable LSD pass over a digit of up to RB bits; the digit histogram of the
+// whole input was accumulated by the kernel that produced the keys
+// ---------------------------------------------------------------------------
+struct RadixPass {
+  const uint32_t* keys_in;
+  const uint32_t* vals_in;  // (unused by the compacting pass)
+  uint32_t* keys_out;
+  uint32_t* vals_out;
+  const int64_t* counts_in;
+  int count_idx;   // number of keys
+  int size_idx;    // count whose value picks the tile size (the number of keys, or an upper bound
+                   // of it for which the look-back words were cleared)
+  int64_t cap;
+  int shift, bits;              // digit = (key >> shift) & (2^bits - 1)
+  const uint32_t* hist;         // digit histogram: `hist` plus
+  const uint32_t* hist_extra;   // `hist_copies` (<= kRadixMaxCopies) partial copies, hist_stride words apart
   int hist_copies;
   int64_t hist_stride;
+  uint32_t* status;             // look-back words, zeroed: [tile][status_stride >= 2^RB], one per digit
+  int64_t status_stride;
+  uint32_t* tile_counter;       // zeroed
+  int64_t* counts;              // flags; the visible count (compacting pass)
+  const int32_t* tiles_touched;  // compacting pass
 };
-constexpr uint64_t kPFlagAgg = 1ull << 62;
-constexpr uint64_t kPFlagInc = 2ull << 62;
-constexpr uint64_t kPFlagMask = 3ull << 62;
 
-// ---------------------------------------------------------------------------
-// one stable LSD pass over 8 bits; the digit histogram of the whole input was
-// accumulated by the kernel that produced the keys
-// ---------------------------------------------------------------------------
-template <int MODE = kPassPlain>
-__global__ void __launch_bounds__(kThreads) radix_pass_kernel(
-    const uint32_t* __restrict__ keys_in, const uint32_t* __restrict__ vals_in, uint32_t* __restrict__ keys_out,
-    uint32_t* __restrict__ vals_out, const int64_t* counts_in, int count_idx, int64_t cap, int shift,
-    const uint32_t* __restrict__ hist, uint32_t* status, int64_t status_stride, uint32_t* tile_counter,
-    int64_t* counts, PairPass pp) {
-  __shared__ uint32_t s_keys[kRadixTile];
-  __shared__ uint32_t s_vals[kRadixTile];
-  __shared__ uint32_t s_wave_hist[kThreads / 64][kRadix];
-  __shared__ uint32_t s_tile_excl[kRadix];
-  __shared__ uint32_t s_digit_base[kRadix];
-  __shared__ uint32_t s_wave[kThreads / 64];
-  __shared__ uint32_t s_tile;
-  __shared__ uint32_t s_goff[kRadix];
-  // kPassPairs only (sized 1 otherwise): tiles_touched, then its exclusive prefix, in LDS
-  // order; the first pair slot of each digit's run of this tile; the prefix at each run start
-  __shared__ uint32_t s_pfx[MODE == kPassPairs ? kRadixTile : 1];
-  __shared__ uint32_t s_pbase[MODE == kPassPairs ? kRadix : 1];
-  __shared__ uint32_t s_pfx_start[MODE == kPassPairs ? kRadix : 1];
-  __shared__ uint64_t s_wave64[MODE == kPassPairs ? kThreads / 64 : 1];
-  __shared__ uint32_t s_ptotal;
-  constexpr bool PAIRS = MODE == kPassPairs;
-  constexpr bool COMPACT = MODE == kPassCompact;
+template <int RB>
+struct RadixLds {
+  static constexpr int kDigits = 1 << RB;
+  static constexpr int kSegs = kRadixThreads / kDigits;  // look-back threads per digit
+  static constexpr int kMaxTile = kRadixThreads * kRadixMaxItems;
+  union {
+    struct {
+      uint32_t keys[kMaxTile], vals[kMaxTile];
+    } s;
+    struct {  // during the look-back, before the scatter
+      uint32_t sum[kSegs][kDigits];
+      uint32_t code[kSegs][kDigits];
+      int32_t at[kDigits];
+    } look;
+  } u;
+  uint16_t wave_hist[kRadixWaves][kDigits];  // counts (at most 1024 keys of a wave), then positions in the tile
+  uint32_t delta[kDigits];                   // output position less tile position of a digit
+  uint32_t goff[kDigits];                    // keys of the whole input with a smaller digit
+  uint32_t wave_tot[kRadixWaves];
+  uint32_t tile;
+};
+
+// exclusive prefix over the digits, held by threads 0 .. kDigits - 1 (every thread calls it); total in *total
+template <int RB>
+__device__ __forceinline__ uint32_t digit_excl_scan(RadixLds<RB>& lds, uint32_t x, uint32_t* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-  const int64_t n = count_clamped(counts_in, count_idx, cap);
-  const int64_t ntiles = (n + kRadixTile - 1) / kRadixTile;
-  // this digit's count over the whole input: `hist` plus the partial copies
-  uint32_t hist_d = hist[threadIdx.x];
-  for (int c = 0; c < pp.hist_copies; ++c) hist_d += pp.hist_extra[c * pp.hist_stride + threadIdx.x];
-  if constexpr (COMPACT) {
-    // the visible count = the digit histogram's total (taken by the later passes)
-    if (blockIdx.x == 0) {
-      uint32_t tot;
-      block_excl_scan(hist_d, s_wave, &tot);
-      if (threadIdx.x == 0) counts[GS_COUNT_VISIBLE] = (int64_t)tot;
-    }
+  const uint32_t inc = (uint32_t)wave_incl_scan((int)x);
+  if (lane == 63) lds.wave_tot[wid] = inc;
+  __syncthreads();
+  uint32_t base = 0, tot = 0;
+#pragma unroll
+  for (int w = 0; w < (1 << RB) / 64; ++w) {
+    const uint32_t s = lds.wave_tot[w];
+    base += w < wid ? s : 0u;
+    tot += s;
   }
-  if constexpr (PAIRS) {
-    // the pair count M = sum of tiles_touched over the visible records, from the weighted histogram
-    if (blockIdx.x == 0) {
-      uint64_t w = 0;
-      for (int c = 0; c < pp.copies; ++c) w += pp.whist[c * kRadix + threadIdx.x];
-      uint64_t tot;
-      block_excl_scan64(w, s_wave64, &tot);
-      if (threadIdx.x == 0) {
-        counts[GS_COUNT_PAIRS] = (int64_t)tot;
-        if ((int64_t)tot > pp.pair_cap) raise_flag(counts, GS_FLAG_PAIRS);
-      }
-    }
-  }
-  if ((int64_t)blockIdx.x >= ntiles) return;
-  {
-    uint32_t tot;
-    s_goff[threadIdx.x] = block_excl_scan(hist_d, s_wave, &tot);  // global digit offsets
-  }
-  uint32_t pair_goff = 0;  // PAIRS: pairs of all records with a smaller digit (saturating)
-  if constexpr (PAIRS) {
-    uint64_t w = 0;
-    for (int c = 0; c < pp.copies; ++c) w += pp.whist[c * kRadix + threadIdx.x];
-    uint64_t tot;
-    pair_goff = sat_u32(block_excl_scan64(w, s_wave64, &tot));
-  }
+  *total = tot;
+  __syncthreads();
+  return base + inc - x;
+}
+
+// Look-back of tile t over the published digit counts, all threads: kSegs
+// threads per digit read kLookWindow words each per round (independent loads in
+// flight), nearest predecessors first; the words are consumed in order up to the
+// first inclusive prefix or the first one not published yet.  Positions before
+// tile 0 read as an inclusive prefix of 0.  Returns the exclusive count to the
+// threads of segment 0.
+template <int RB>
+__device__ __forceinline__ uint32_t radix_lookback(RadixLds<RB>& lds, const RadixPass& a, int64_t t) {
+  using Lds = RadixLds<RB>;
+  const int d = threadIdx.x & (Lds::kDigits - 1), seg = threadIdx.x >> RB;
+  uint32_t excl = 0;
+  bool open = seg == 0;  // segment 0 keeps the digit's state
+  if (seg == 0) lds.u.look.at[d] = (int32_t)(t - 1);
+  int64_t spins = 0;
+  __syncthreads();
   for (;;) {
-    if (threadIdx.x == 0) s_tile = atomicAdd(tile_counter, 1u);
-    for (int i = threadIdx.x; i < (kThreads / 64) * kRadix; i += kThreads) (&s_wave_hist[0][0])[i] = 0u;
-    __syncthreads();
-    const int64_t t = s_tile;
-    if (t >= ntiles) break;
-    const int64_t tile_base = t * kRadixTile;
-    const int tile_n = (int)((n - tile_base) < kRadixTile ? (n - tile_base) : kRadixTile);
-    // wave w owns the contiguous slice [w*64*kRadixItems, (w+1)*64*kRadixItems) of the tile;
-    // item k of lane l is element k*64 + l of that slice (coalesced loads)
-    uint32_t key[kRadixItems], val[kRadixItems], rank[kRadixItems];
-    uint32_t ttv[PAIRS ? kRadixItems : 1];
-    bool valid[kRadixItems];
-    const int slice = wid * 64 * kRadixItems;
+    const int at = lds.u.look.at[d];  // -2: done
+    uint32_t sum = 0, used = 0, done = 0;
+    if (at != -2) {
+      uint32_t sv[kLookWindow];
+      const int64_t k = (int64_t)at - seg * kLookWindow;
 #pragma unroll
-    for (int k = 0; k < kRadixItems; ++k) {
-      const int li = slice + k * 64 + lane;
-      if constexpr (COMPACT) {
-        // both loads issued together (a culled record's key is read and dropped)
-        const bool in_tile = li < tile_n;
-        const int32_t tt = in_tile ? pp.tiles_touched[tile_base + li] : 0;
-        key[k] = in_tile ? keys_in[tile_base + li] : 0u;
-        valid[k] = tt > 0;
-        val[k] = (uint32_t)(tile_base + li);
-      } else {
-        valid[k] = li < tile_n;
-        key[k] = valid[k] ? keys_in[tile_base + li] : 0u;
-        val[k] = valid[k] ? vals_in[tile_base + li] : 0u;
-      }
-    }
-    uint32_t tfirst[PAIRS ? kRadixItems : 1], textent[PAIRS ? kRadixItems : 1];
-    if constexpr (PAIRS) {
+      for (int i = 0; i < kLookWindow; ++i)
+        sv[i] = k - i >= 0 ? load_agent(a.status + (k - i) * a.status_stride + d) : kFlagInc;
+      bool stop = false;
 #pragma unroll
-      for (int k = 0; k < kRadixItems; ++k) {
-        uint4 w0 = make_uint4(0u, 0u, 0u, 0u);
-        if (valid[k]) w0 = pp.rec_words[(size_t)kRecordWords * val[k]];
-        const uint32_t i0 = w0.z & 0xFFFFu, i1 = i0 + (w0.z >> 16);
-        const uint32_t j0 = w0.w & 0xFFFFu, j1 = j0 + (w0.w >> 16);
-        const uint32_t tx0 = i0 >> pp.tw_shift, ty0 = j0 >> pp.th_shift;
-        const uint32_t ntx = (i1 >> pp.tw_shift) - tx0 + 1u, nty = (j1 >> pp.th_shift) - ty0 + 1u;
-        ttv[k] = valid[k] ? ntx * nty : 0u;
-        tfirst[k] = w0.y * (uint32_t)pp.tiles_per_view + ty0 * (uint32_t)pp.tiles_x + tx0;
-        textent[k] = ntx | (nty << 16);
-      }
-    }
-    // stable rank inside the wave: items in order k, lanes in order within an item
-#pragma unroll
-    for (int k = 0; k < kRadixItems; ++k) {
-      const uint32_t d = (key[k] >> shift) & 255u;
-      uint64_t peers = __ballot(valid[k]);
-      if (peers == 0) {  // no valid item in the wave (the compacting pass: a run of culled records)
-        rank[k] = 0;
-        continue;
-      }
-#pragma unroll
-      for (int bit = 0; bit < 8; ++bit) {
-        const bool b = (d >> bit) & 1u;
-        const uint64_t m = __ballot(b);
-        peers &= b ? m : ~m;
-      }
-      uint32_t prev = 0;
-      if (valid[k]) prev = s_wave_hist[wid][d];
-      const uint32_t below = (uint32_t)lanemask_lt_count(peers);
-      rank[k] = prev + below;
-      if (valid[k] && below == 0) s_wave_hist[wid][d] = prev + (uint32_t)__popcll(peers);
-      __builtin_amdgcn_wave_barrier();
-    }
-    __syncthreads();
-    // per digit: exclusive prefix over waves, tile count, tile-local digit prefix
-    const int d = threadIdx.x;
-    uint32_t run = 0;
-#pragma unroll
-    for (int w = 0; w < kThreads / 64; ++w) {
-      const uint32_t c = s_wave_hist[w][d];
-      s_wave_hist[w][d] = run;
-      run += c;
-    }
-    const uint32_t tile_cnt = run;
-    uint32_t tile_total;
-    const uint32_t tile_excl = block_excl_scan(tile_cnt, s_wave, &tile_total);
-    s_tile_excl[d] = tile_excl;
-    uint32_t excl = 0;
-    if constexpr (PAIRS) {
-      // local scatter of tiles_touched into the tile's digit order, then its
-      // exclusive prefix there (16 consecutive positions per thread)
-      __syncthreads();  // s_tile_excl of every digit
-#pragma unroll
-      for (int k = 0; k < kRadixItems; ++k) {
-        if (valid[k]) {
-          const uint32_t dd = (key[k] >> shift) & 255u;
-          s_pfx[s_tile_excl[dd] + s_wave_hist[wid][dd] + rank[k]] = ttv[k];
-        }
-      }
-      __syncthreads();
-      uint32_t loc[kRadixItems];
-      uint64_t mine = 0;
-#pragma unroll
-      for (int k = 0; k < kRadixItems; ++k) {
-        const int i = threadIdx.x * kRadixItems + k;
-        loc[k] = i < (int)tile_total ? s_pfx[i] : 0u;
-        mine += loc[k];
-      }
-      uint64_t tsum;
-      uint64_t run64 = block_excl_scan64(mine, s_wave64, &tsum);
-#pragma unroll
-      for (int k = 0; k < kRadixItems; ++k) {
-        const int i = threadIdx.x * kRadixItems + k;
-        if (i < (int)tile_total) s_pfx[i] = sat_u32(run64);
-        run64 += loc[k];
-      }
-      if (threadIdx.x == 0) s_ptotal = sat_u32(tsum);
-      __syncthreads();
-      // pairs of this tile's digit-d run; one 64-bit look-back word per digit
-      // carries the record count (bits 32..61) and the pair sum (bits 0..31)
-      const uint32_t rs = tile_excl, re = tile_excl + tile_cnt;
-      const uint32_t ps = rs < tile_total ? s_pfx[rs] : s_ptotal;
-      const uint32_t pe = re < tile_total ? s_pfx[re] : s_ptotal;
-      const uint32_t tpairs = pe - ps;
-      s_pfx_start[d] = ps;
-      uint32_t excl_pairs = 0;
-      uint64_t* st = pp.status + t * kRadix + d;
-      if (t == 0) {
-        store_agent(st, kPFlagInc | ((uint64_t)tile_cnt << 32) | tpairs);
-      } else {
-        store_agent(st, kPFlagAgg | ((uint64_t)tile_cnt << 32) | tpairs);
-        int64_t k = t - 1;
-        int64_t spins = 0;
-        for (;;) {
-          uint64_t sv[kLookWindow];
-#pragma unroll
-          for (int i = 0; i < kLookWindow; ++i)
-            sv[i] = (k - i >= 0) ? load_agent(pp.status + (k - i) * kRadix + d) : kPFlagInc;
-          int used = 0;
-          bool done = false, stalled = false;
-#pragma unroll
-          for (int i = 0; i < kLookWindow; ++i) {
-            if (done || stalled) continue;
-            const uint64_t flag = sv[i] & kPFlagMask;
-            if (flag == 0) {
-              stalled = true;
-              continue;
-            }
-            excl += (uint32_t)(sv[i] >> 32) & kValMask;
-            excl_pairs = sat_add(excl_pairs, (uint32_t)sv[i]);
-            ++used;
-            done = flag == kPFlagInc;
-          }
-          if (done) break;
-          k -= used;
-          if (stalled) {
-            if (++spins > kSpinLimit) {
-              raise_flag(counts, GS_FLAG_WAIT);
-              break;
-            }
-            __builtin_amdgcn_s_sleep(1);
-          }
-        }
-        store_agent(st, kPFlagInc | ((uint64_t)(excl + tile_cnt) << 32) | sat_add(excl_pairs, tpairs));
-      }
-      s_pbase[d] = sat_add(pair_goff, excl_pairs);
-    } else {
-    // decoupled look-back for digit d
-    uint32_t* st = status + t * status_stride + d;
-    if (t == 0) {
-      store_agent(st, kFlagInc | tile_cnt);
-    } else {
-      store_agent(st, kFlagAgg | tile_cnt);
-      // the predecessors' words are read kLookWindow at a time (independent
-      // loads in flight) and consumed in order up to the first inclusive
-      // prefix; positions before tile 0 read as an inclusive prefix of 0
-      int64_t k = t - 1;
-      int64_t spins = 0;
-      for (;;) {
-        uint32_t sv[kLookWindow];
-#pragma unroll
-        for (int i = 0; i < kLookWindow; ++i)
-          sv[i] = (k - i >= 0) ? load_agent(status + (k - i) * status_stride + d) : kFlagInc;
-        int used = 0;
-        bool done = false, stalled = false;
-#pragma unroll
-        for (int i = 0; i < kLookWindow; ++i) {
-          if (done || stalled) continue;
-          const uint32_t flag = sv[i] & ~kValMask;
-          if (flag == 0) {
-            stalled = true;
-            continue;
-          }
-          excl += sv[i] & kValMask;
+      for (int i = 0; i < kLookWindow; ++i) {
+        const uint32_t flag = sv[i] & ~kValMask;
+        stop |= flag == 0u;
+        if (!stop && !done) {
+          sum += sv[i] & kValMask;
           ++used;
           done = flag == kFlagInc;
         }
-        if (done) break;
-        k -= used;
-        if (stalled) {
-          if (++spins > kSpinLimit) {
-            raise_flag(counts, GS_FLAG_WAIT);
-            break;
-          }
-          __builtin_amdgcn_s_sleep(1);
-        }
       }
-      store_agent(st, kFlagInc | (excl + tile_cnt));
-    }
-    }
-    s_digit_base[d] = s_goff[d] + excl;
-    __syncthreads();
-    if constexpr (PAIRS) {
-      // each item's tile rectangle straight to its sorted slot: for one item k, the
-      // lanes of a digit land on consecutive slots (and the top depth digit takes
-      // few values), so these stores stay close to contiguous
-#pragma unroll
-      for (int k = 0; k < kRadixItems; ++k) {
-        if (valid[k]) {
-          const uint32_t dd = (key[k] >> shift) & 255u;
-          const uint32_t out = s_digit_base[dd] + s_wave_hist[wid][dd] + rank[k];
-          pp.tile_first[out] = tfirst[k];
-          pp.tile_extent[out] = textent[k];
-        }
-      }
-    }
-    // local scatter by digit, then coalesced write-out
-#pragma unroll
-    for (int k = 0; k < kRadixItems; ++k) {
-      if (valid[k]) {
-        const uint32_t dd = (key[k] >> shift) & 255u;
-        const uint32_t pos = s_tile_excl[dd] + s_wave_hist[wid][dd] + rank[k];
-        s_keys[pos] = key[k];
-        s_vals[pos] = val[k];
-      }
+      lds.u.look.sum[seg][d] = sum;
+      lds.u.look.code[seg][d] = used | (done << 8);
     }
     __syncthreads();
-    // (valid items only: tile_total = tile_n except in the compacting pass)
-    for (int i = threadIdx.x; i < (int)tile_total; i += kThreads) {
-      const uint32_t kk = s_keys[i];
-      const uint32_t dd = (kk >> shift) & 255u;
-      const uint32_t out = s_digit_base[dd] + ((uint32_t)i - s_tile_excl[dd]);
-      vals_out[out] = s_vals[i];
-      if constexpr (PAIRS) {
-        pp.pair_off[out] = sat_add(s_pbase[dd], s_pfx[i] - s_pfx_start[dd]);
-      } else {
-        keys_out[out] = kk;
+    if (open) {
+      int32_t next = at;
+      bool stalled = false;
+      for (int s = 0; s < Lds::kSegs; ++s) {
+        const uint32_t c = lds.u.look.code[s][d];
+        excl += lds.u.look.sum[s][d];
+        next -= (int32_t)(c & 255u);
+        if (c >> 8) {
+          open = false;
+          break;
+        }
+        if ((c & 255u) < (uint32_t)kLookWindow) {
+          stalled = true;
+          break;
+        }
       }
+      if (stalled && ++spins > kSpinLimit) {
+        raise_flag(a.counts, GS_FLAG_WAIT);
+        open = false;
+      }
+      lds.u.look.at[d] = open ? next : -2;
     }
+    if (!__syncthreads_or(open)) return excl;
+  }
+}
+
+// Lanes of `valid` whose digit equals the calling lane's (a wave's multisplit).
+// Per bit one ballot m and the lane's bit as a mask s: lanes differ where m ^ s,
+// a three-input boolean operation per 32 lanes.  (Written out with 32-bit masks:
+// as 64-bit selects the compiler spent 13 VALU per bit instead of 4, and the
+// ranking was most of a pass's time.)
+template <int RB>
+__device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t valid) {
+  uint32_t lo = 0, hi = 0;  // lanes that differ
+#pragma unroll
+  for (int bit = 0; bit < RB; ++bit) {
+    const int s = __builtin_amdgcn_sbfe((int)d, bit, 1);
+    const uint64_t m = __ballot(s != 0);
+    lo = __builtin_amdgcn_bitop3_b32(lo, (uint32_t)m, (uint32_t)s, 0xF6);  // lo | (m ^ s)
+    hi = __builtin_amdgcn_bitop3_b32(hi, (uint32_t)(m >> 32), (uint32_t)s, 0xF6);
+  }
+  return valid & ~(((uint64_t)hi << 32) | lo);
+}
+
+// element i of an array of fewer than 2^30 words (a 32-bit byte offset beside a uniform base)
+__device__ __forceinline__ uint32_t& word_at(uint32_t* p, uint32_t i) {
+  return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p) + (uint32_t)(i << 2));
+}
+
+template <int RB, int ITEMS, bool COMPACT>
+__device__ __forceinline__ void radix_tile(RadixLds<RB>& lds, const RadixPass& a, int64_t n, int64_t t) {
+  using Lds = RadixLds<RB>;
+  constexpr int kTileKeys = kRadixThreads * ITEMS;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+  const int64_t tile_base = t * kTileKeys;
+  const uint32_t tile_n = (uint32_t)((n - tile_base) < kTileKeys ? (n - tile_base) : kTileKeys);
+  const uint32_t* keys = a.keys_in + tile_base;
+  const uint32_t* vals = COMPACT ? nullptr : a.vals_in + tile_base;
+  const int32_t* tt = COMPACT ? a.tiles_touched + tile_base : nullptr;
+  // wave w owns the contiguous slice [w*64*ITEMS, (w+1)*64*ITEMS) of the tile; item k of lane l is
+  // element k*64 + l of that slice (coalesced loads)
+  uint32_t key[ITEMS], val[ITEMS], rank[ITEMS];
+  bool valid[ITEMS];
+  const uint32_t slice = (uint32_t)(wid * 64 * ITEMS + lane);
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t li = slice + k * 64;
+    const bool in_tile = li < tile_n;
+    key[k] = in_tile ? keys[li] : 0u;
+    if constexpr (COMPACT) {
+      // (a culled record's key is read and dropped)
+      valid[k] = (in_tile ? tt[li] : 0) > 0;
+      val[k] = (uint32_t)tile_base + li;
+    } else {
+      valid[k] = in_tile;
+      val[k] = in_tile ? vals[li] : 0u;
+    }
+  }
+  auto digit = [&](uint32_t x) { return __builtin_amdgcn_ubfe(x, (uint32_t)a.shift, (uint32_t)a.bits); };
+  // stable rank inside the wave: items in order k, lanes in order within an item
+  uint16_t* hist = lds.wave_hist[wid];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint64_t vm = __ballot(valid[k]);
+    if (vm == 0) {  // no valid item in the wave (a run of culled records, the end of the input)
+      rank[k] = 0;
+      continue;
+    }
+    const uint32_t d = digit(key[k]);
+    const uint32_t prev = hist[d];
+    const uint64_t peers = match_digit<RB>(d, vm);
+    const uint32_t below = (uint32_t)lanemask_lt_count(peers);
+    rank[k] = prev + below;
+    if (valid[k] & (below == 0)) hist[d] = (uint16_t)(prev + (uint32_t)__popcll(peers));
+    __builtin_amdgcn_wave_barrier();
+  }
+  __syncthreads();
+  // per digit: count of the tile, published at once; prefix over the waves
+  const int d = threadIdx.x & (Lds::kDigits - 1);
+  uint32_t cnt = 0;
+  uint32_t c[kRadixWaves];
+  uint32_t* st = a.status + t * a.status_stride + d;
+  if (threadIdx.x < Lds::kDigits) {
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) c[w] = lds.wave_hist[w][d];
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) {
+      const uint32_t x = c[w];
+      c[w] = cnt;
+      cnt += x;
+    }
+    store_agent(st, (t == 0 ? kFlagInc : kFlagAgg) | cnt);
+  }
+  uint32_t tile_total;
+  const uint32_t tile_excl = digit_excl_scan<RB>(lds, cnt, &tile_total);
+  if (threadIdx.x < Lds::kDigits) {  // position of a wave's first key of the digit in the tile
+#pragma unroll
+    for (int w = 0; w < kRadixWaves; ++w) lds.wave_hist[w][d] = (uint16_t)(tile_excl + c[w]);
+  }
+  uint32_t excl = 0;
+  if (t > 0) {
+    excl = radix_lookback<RB>(lds, a, t);
+    if (threadIdx.x < Lds::kDigits) store_agent(st, kFlagInc | (excl + cnt));
+  }
+  if (threadIdx.x < Lds::kDigits) lds.delta[d] = lds.goff[d] + excl - tile_excl;
+  __syncthreads();  // (and the look-back's use of the key and value arrays is over)
+  // local scatter by digit, then coalesced write-out
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    if (valid[k]) {
+      const uint32_t pos = hist[digit(key[k])] + rank[k];
+      lds.u.s.keys[pos] = key[k];
+      lds.u.s.vals[pos] = val[k];
+    }
+  }
+  __syncthreads();
+  // (valid items only: tile_total = tile_n except in the compacting pass)
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t i = (uint32_t)k * kRadixThreads + threadIdx.x;
+    if (i < tile_total) {
+      const uint32_t kk = lds.u.s.keys[i];
+      const uint32_t out = lds.delta[digit(kk)] + i;
+      word_at(a.vals_out, out) = lds.u.s.vals[i];
+      word_at(a.keys_out, out) = kk;
+    }
+  }
+}
+
+// COMPACT: the least significant depth pass of the binning: reads every selected
+// record's depth key, keeps those with tiles_touched > 0 (values = record index,
+// in index order) and writes the visible count.
+template <int RB, bool COMPACT>
+__global__ void __launch_bounds__(kRadixThreads) radix_pass_kernel(RadixPass a) {
+  using Lds = RadixLds<RB>;
+  __shared__ Lds lds;
+  const int64_t n = count_clamped(a.counts_in, a.count_idx, a.cap);
+  const int items = radix_items(count_clamped(a.counts_in, a.size_idx, a.cap));
+  const int64_t ntiles = (n + (int64_t)kRadixThreads * items - 1) / ((int64_t)kRadixThreads * items);
+  if ((int64_t)blockIdx.x >= ntiles && !(COMPACT && blockIdx.x == 0)) return;
+  uint32_t claimed = 0;  // (asked for before the histograms, and before a tile's end: it takes a round trip)
+  if (threadIdx.x == 0) claimed = atomicAdd(a.tile_counter, 1u);
+  // this digit's count over the whole input: `hist` plus the partial copies
+  uint32_t hist_d = 0;
+  if (threadIdx.x < Lds::kDigits && threadIdx.x < (1u << a.bits)) {
+    hist_d = a.hist[threadIdx.x];
+    uint32_t part[kRadixMaxCopies];
+#pragma unroll
+    for (int c = 0; c < kRadixMaxCopies; ++c) part[c] = c < a.hist_copies ? a.hist_extra[c * a.hist_stride + threadIdx.x] : 0u;
+#pragma unroll
+    for (int c = 0; c < kRadixMaxCopies; ++c) hist_d += part[c];
+  }
+  uint32_t total;
+  const uint32_t goff = digit_excl_scan<RB>(lds, hist_d, &total);
+  if (threadIdx.x < Lds::kDigits) lds.goff[threadIdx.x] = goff;
+  if constexpr (COMPACT) {
+    // the visible count = the digit histogram's total (taken by the later passes)
+    if (blockIdx.x == 0 && threadIdx.x == 0) a.counts[GS_COUNT_VISIBLE] = (int64_t)total;
+  }
+  for (;;) {
+    if (threadIdx.x == 0) lds.tile = claimed;
+    for (int i = threadIdx.x; i < kRadixWaves * Lds::kDigits / 2; i += kRadixThreads)
+      reinterpret_cast<uint32_t*>(&lds.wave_hist[0][0])[i] = 0u;
+    __syncthreads();
+    const int64_t t = lds.tile;
+    if (t >= ntiles) break;
+    if (items == 4) radix_tile<RB, 4, COMPACT>(lds, a, n, t);
+    else if (items == 8) radix_tile<RB, 8, COMPACT>(lds, a, n, t);
+    else if (items == 12) radix_tile<RB, 12, COMPACT>(lds, a, n, t);
+    else radix_tile<RB, kRadixMaxItems, COMPACT>(lds, a, n, t);
+    if (threadIdx.x == 0) claimed = atomicAdd(a.tile_counter, 1u);
     __syncthreads();
   }
+}
+
+inline dim3 radix_grid(int64_t cap) {
+  const int64_t g = radix_tiles_bound(cap);
+  return dim3((unsigned)(g < 1 ? 1 : (g > kRadixBlocks ? kRadixBlocks : g)));
 }
 
 }  // namespace

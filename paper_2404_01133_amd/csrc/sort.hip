@@ -4,17 +4,15 @@
 // least-significant-digit radix sort.  Its low (depth) digits do not depend on
 // the tile, so those passes run once per visible record, before the pairs are
 // duplicated; only the tile digits run over the pairs.  Stages:
-//   1. hist      digit histograms of the visible records' depth keys, and the
-//                pairs (tiles_touched) per top digit
+//   1. hist      digit histograms of the visible records' depth keys
 //   2. 4 passes  stable radix sort by the 32-bit depth key (ties keep record order);
 //                the first one reads every selected record and keeps the visible
-//                ones (compaction), the last one gathers each record's footprint
-//                word, writes its tile rectangle (first tile id, extent) and the
-//                pair offsets, the exclusive prefix of the tile counts in depth
-//                order (its look-back carries both sums)
-//   3. emit      one (view*tiles + tile, record) pair per tile of each footprint,
-//                reading the rectangles in depth order
-//   4. passes    stable radix sort by tile id (ceil(bits / 8) passes)
+//                ones (compaction)
+//   3. emit      the sorted records' footprint words gathered, their tile counts
+//                scanned (one look-back word per work-group tile) and one
+//                (view*tiles + tile, record) pair written per tile of each
+//                footprint, with the histograms of the tile digits
+//   4. passes    stable radix sort by tile id (ceil(bits / 9) passes)
 //   5. ranges    [start, end) of every tile
 // The result equals a sort by (tile, depth, record id).
 //
@@ -33,9 +31,10 @@
 namespace gs {
 namespace {
 
-constexpr int kMaxPasses = 8;
-constexpr int kPersistentBlocks = 1024;
-constexpr int kBigFootprint = 16;  // records touching more tiles are emitted cooperatively
+constexpr int kMaxTilePasses = 4;       // digits of a tile id (below 2^31) at up to 9 bits
+constexpr int kTileDigits = 512;        // words of one tile-digit histogram
+constexpr int kHistItems = 8;           // records per thread of the depth histogram
+constexpr uint32_t kBigFootprint = 16;  // records touching more tiles are emitted cooperatively
 // emit_kernel's work-groups all finish at about the same time and each adds its
 // tile-digit histogram to device memory, so a single copy would take ~2000
 // same-address atomics per word in a row.  They add into kTileHistCopies
@@ -43,33 +42,64 @@ constexpr int kBigFootprint = 16;  // records touching more tiles are emitted co
 // histogram the radix passes read), and emit_big_kernel, which runs next, folds
 // copies 1.. into copy 0.
 constexpr int kTileHistCopies = 8;
-constexpr int64_t kTileHistWords = kMaxPasses * kRadix;  // one copy
+constexpr int64_t kTileHistWords = kMaxTilePasses * kTileDigits;  // one copy
 
-// ---------------------------------------------------------------------------
-// zero fill of the small fixed state (counters, histograms) and of the look-back
-// words of the four depth passes, sized by the selected records (the compacting
-// first pass runs over all of them; the later ones over the visible ones):
-// u32 [radix tiles][4][256] and the last pass's u64 [radix tiles][256]
-__global__ void clear_front_kernel(uint32_t* __restrict__ fixed, int64_t fixed_words, const int64_t* counts,
-                                   int64_t cap, uint32_t* __restrict__ dstatus, uint64_t* __restrict__ pstatus) {
-  const int64_t n = count_clamped(counts, GS_COUNT_RECORDS, cap);
-  const int64_t rt = (n + kRadixTile - 1) / kRadixTile;
-  const int64_t dwords = rt * 4 * kRadix, pwords = rt * kRadix;
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < fixed_words + dwords + pwords; i += stride) {
-    if (i < fixed_words) fixed[i] = 0u;
-    else if (i < fixed_words + dwords) dstatus[i - fixed_words] = 0u;
-    else pstatus[i - fixed_words - dwords] = 0ull;
-  }
+// Records per thread of the emission: a small input still spreads over the chip (records with many
+// tiles make a work-group's share long), a large one keeps the look-back short.
+constexpr int kEmitMaxItems = 8;
+__host__ __device__ constexpr int emit_items(int64_t n) {
+  return n <= (int64_t)1 << 16 ? 1 : n <= (int64_t)1 << 19 ? 4 : kEmitMaxItems;
+}
+__host__ __device__ constexpr int64_t emit_tiles(int64_t n) {
+  const int64_t t = (int64_t)kThreads * emit_items(n);
+  return (n + t - 1) / t;
+}
+// upper bound of emit_tiles(m) over all m <= n
+__host__ __device__ constexpr int64_t emit_tiles_bound(int64_t n) {
+  int64_t t = emit_tiles(n);
+  const int64_t b = emit_tiles(n < ((int64_t)1 << 19) ? n : (int64_t)1 << 19);
+  const int64_t c = emit_tiles(n < ((int64_t)1 << 16) ? n : (int64_t)1 << 16);
+  t = b > t ? b : t;
+  return c > t ? c : t;
 }
 
 // ---------------------------------------------------------------------------
-// 1. histograms of the visible records' depth digits (all four passes) and of
-//    their pairs by the top digit; the work-groups finish together, so their
-//    device atomics are spread over kDepthHistCopies partial copies (copy 0 is
-//    the histogram itself; each pass adds the others to its digit)
+// zero fill of the small fixed state (counters, histograms), of the look-back
+// words of the depth passes and the emission (sized by the selected records) and
+// of the tile passes (sized by the pair capacity: the pair count is not known
+// yet), and of the tile ranges
+// ---------------------------------------------------------------------------
+struct ClearArgs {
+  uint32_t* fixed;
+  int64_t fixed_words;
+  uint32_t* dstatus;  // [tile][4][256]
+  uint64_t* estatus;  // [tile]
+  uint32_t* pstatus;
+  int64_t pstatus_words;
+  uint32_t* ranges;
+  int64_t range_words;
+};
+__global__ void clear_front_kernel(ClearArgs a, int64_t* counts, int64_t cap) {
+  const int64_t n = count_clamped(counts, GS_COUNT_RECORDS, cap);
+  const int64_t dwords = radix_tiles(n) * 4 * kRadix, ewords = emit_tiles(n);
+  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
+  const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
+  if (i0 == 0) counts[GS_COUNT_PAIRS] = 0;  // (no visible record: no emission tile writes it)
+  for (int64_t i = i0; i < a.fixed_words; i += stride) a.fixed[i] = 0u;
+  for (int64_t i = i0; i < dwords; i += stride) a.dstatus[i] = 0u;
+  for (int64_t i = i0; i < ewords; i += stride) a.estatus[i] = 0ull;
+  for (int64_t i = i0; i < a.pstatus_words; i += stride) a.pstatus[i] = 0u;
+  for (int64_t i = i0; i < a.range_words; i += stride) a.ranges[i] = 0u;
+}
+
+// ---------------------------------------------------------------------------
+// 1. histograms of the visible records' depth digits (all four passes); the
+//    work-groups finish together, so their device atomics are spread over
+//    kDepthHistCopies partial copies (copy 0 is the histogram itself; each pass
+//    adds the others to its digit)
 // ---------------------------------------------------------------------------
 constexpr int kDepthHistCopies = 8;
+static_assert(kDepthHistCopies - 1 <= kRadixMaxCopies, "a pass sums them");
 constexpr int64_t kDepthHistWords = 4 * kRadix;
 
 // Histogram adds of a wave whose lanes often share a digit.  Depth keys are
@@ -78,8 +108,7 @@ constexpr int64_t kDepthHistWords = 4 * kRadix;
 // them serialise on one address.  match_add: each lane finds the lanes with its
 // digit with eight ballots (a fixed cost whatever the distribution) and the
 // lowest of them adds their count.  top_add: one round per distinct top digit
-// in the wave (sign and exponent of depths within a wave: one or two values),
-// adding the lanes' count and their tiles_touched sum.
+// in the wave (sign and exponent of depths within a wave: one or two values).
 __device__ __forceinline__ void match_add(bool valid, uint32_t d, uint32_t* h) {
   uint64_t peers = __ballot(valid);
 #pragma unroll
@@ -91,21 +120,14 @@ __device__ __forceinline__ void match_add(bool valid, uint32_t d, uint32_t* h) {
   if (valid && lanemask_lt_count(peers) == 0) atomicAdd(&h[d], (uint32_t)__popcll(peers));
 }
 
-__device__ __forceinline__ void top_add(bool valid, uint32_t d, uint32_t tt, uint32_t* h, uint64_t* wh) {
+__device__ __forceinline__ void top_add(bool valid, uint32_t d, uint32_t* h) {
   const int lane = threadIdx.x & 63;
   uint64_t left = __ballot(valid);
   while (left) {
     const int leader = (int)__builtin_ctzll(left);
     const uint32_t dl = (uint32_t)__builtin_amdgcn_readlane((int)d, leader);
-    const bool mine = valid && d == dl;
-    const uint64_t m = __ballot(mine);
-    uint64_t v = mine ? (uint64_t)tt : 0ull;  // 64 lanes of tiles_touched may pass 2^32
-#pragma unroll
-    for (int off = 32; off > 0; off >>= 1) v += __shfl_xor(v, off);
-    if (lane == leader) {
-      atomicAdd(&h[dl], (uint32_t)__popcll(m));
-      atomicAdd((unsigned long long*)&wh[dl], (unsigned long long)v);
-    }
+    const uint64_t m = __ballot(valid && d == dl);
+    if (lane == leader) atomicAdd(&h[dl], (uint32_t)__popcll(m));
     left &= ~m;
   }
 }
@@ -113,31 +135,34 @@ __device__ __forceinline__ void top_add(bool valid, uint32_t d, uint32_t tt, uin
 __global__ void __launch_bounds__(kThreads) depth_hist_kernel(const int32_t* __restrict__ tiles_touched,
                                                               const uint32_t* __restrict__ depth_keys, int64_t cap,
                                                               const int64_t* counts, uint32_t* __restrict__ hist,
-                                                              uint32_t* __restrict__ hist_extra,
-                                                              uint64_t* __restrict__ whist) {
+                                                              uint32_t* __restrict__ hist_extra) {
   __shared__ uint32_t s_hist[4][kRadix];
-  __shared__ uint64_t s_whist[kRadix];  // tiles_touched summed by the top depth digit
   const int64_t n = count_clamped(counts, GS_COUNT_RECORDS, cap);
-  const int64_t per_block = (int64_t)kThreads * kItems;
+  const int64_t per_block = (int64_t)kThreads * kHistItems;
   const int64_t nblocks = (n + per_block - 1) / per_block;
   if ((int64_t)blockIdx.x >= nblocks) return;
   for (int i = threadIdx.x; i < 4 * kRadix; i += kThreads) (&s_hist[0][0])[i] = 0u;
-  s_whist[threadIdx.x] = 0ull;
   __syncthreads();
   for (int64_t b = blockIdx.x; b < nblocks; b += gridDim.x) {
+    // every load of the block's share in flight together (a culled record's key is read and dropped)
+    int32_t tt[kHistItems];
+    uint32_t key[kHistItems];
 #pragma unroll
-    for (int k = 0; k < kItems; ++k) {
+    for (int k = 0; k < kHistItems; ++k) {
       const int64_t idx = b * per_block + (int64_t)k * kThreads + threadIdx.x;  // coalesced
-      const int32_t tt = idx < n ? tiles_touched[idx] : 0;
-      const bool vis = tt > 0;
+      tt[k] = idx < n ? tiles_touched[idx] : 0;
+      key[k] = idx < n ? depth_keys[idx] : 0u;
+    }
+#pragma unroll
+    for (int k = 0; k < kHistItems; ++k) {
+      const bool vis = tt[k] > 0;
       if (__ballot(vis) == 0) continue;  // a wave of culled records (neighbours are culled together)
-      const uint32_t key = vis ? depth_keys[idx] : 0u;
       if (vis) {
-        atomicAdd(&s_hist[0][key & 255u], 1u);
-        atomicAdd(&s_hist[1][(key >> 8) & 255u], 1u);
+        atomicAdd(&s_hist[0][key[k] & 255u], 1u);
+        atomicAdd(&s_hist[1][(key[k] >> 8) & 255u], 1u);
       }
-      match_add(vis, (key >> 16) & 255u, s_hist[2]);
-      top_add(vis, key >> 24, vis ? (uint32_t)tt : 0u, s_hist[3], s_whist);
+      match_add(vis, (key[k] >> 16) & 255u, s_hist[2]);
+      top_add(vis, key[k] >> 24, s_hist[3]);
     }
   }
   __syncthreads();
@@ -147,121 +172,212 @@ __global__ void __launch_bounds__(kThreads) depth_hist_kernel(const int32_t* __r
     const uint32_t c = (&s_hist[0][0])[i];
     if (c) atomicAdd(&h[i], c);
   }
-  const uint64_t wv = s_whist[threadIdx.x];
-  if (wv) atomicAdd((unsigned long long*)&whist[copy * kRadix + threadIdx.x], (unsigned long long)wv);
 }
 
 // ---------------------------------------------------------------------------
 // 3. pair emission
 // ---------------------------------------------------------------------------
-__global__ void __launch_bounds__(kThreads) emit_kernel(const uint32_t* __restrict__ tile_first,
-                                                        const uint32_t* __restrict__ tile_extent,
-                                                        const uint32_t* __restrict__ sorted_records,
-                                                        const uint32_t* __restrict__ pair_off, int64_t cap,
-                                                        const int64_t* counts, int64_t pair_cap, int tw, int th,
-                                                        int tiles_x_n, int tiles_per_view,
-                                                        uint32_t* __restrict__ out_tiles,
-                                                        uint32_t* __restrict__ out_records, int tpasses,
-                                                        uint32_t* __restrict__ hist, uint32_t* __restrict__ pstatus,
-                                                        uint32_t* __restrict__ ranges, int64_t range_words,
-                                                        uint32_t* __restrict__ big_list,
-                                                        uint32_t* __restrict__ big_count,
-                                                        uint32_t* __restrict__ hist_extra) {
-  __shared__ uint32_t s_hist[kMaxPasses][kRadix];
-  const int64_t stride = (int64_t)gridDim.x * blockDim.x;
-  const int64_t gtid = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  // zero the look-back words of the tile passes (sized by the pair count) and the ranges
+struct EmitArgs {
+  const uint4* rec_words;        // records as 16-byte words, kRecordWords per record
+  const uint32_t* sorted;        // visible records in depth order
+  int64_t* counts;
+  int64_t cap, pair_cap;
+  int tw_shift, th_shift;        // log2 of the tile shape (every supported shape is a power of two)
+  int tiles_x, tiles_per_view;
+  uint32_t* out_tiles;
+  uint32_t* out_records;
+  int passes, bits;              // tile digits and their width
+  uint32_t* hist;                // tile-digit histograms, [passes][kTileDigits]
+  uint32_t* hist_extra;
+  uint64_t* status;              // look-back words
+  uint32_t* tile_counter;
+  uint32_t* big_rec;             // records with many tiles and their first pair
+  uint32_t* big_off;
+  uint32_t* big_count;
+};
+
+// first tile id and extent in tiles (columns | rows << 16) of a record
+struct TileRect {
+  uint32_t first, extent;
+  __device__ __forceinline__ uint32_t columns() const { return extent & 0xFFFFu; }
+  __device__ __forceinline__ uint32_t tiles() const { return columns() * (extent >> 16); }
+};
+__device__ __forceinline__ TileRect tile_rect(const EmitArgs& a, const uint4& w0) {
+  const uint32_t i0 = w0.z & 0xFFFFu, i1 = i0 + (w0.z >> 16);
+  const uint32_t j0 = w0.w & 0xFFFFu, j1 = j0 + (w0.w >> 16);
+  const uint32_t tx0 = i0 >> a.tw_shift, ty0 = j0 >> a.th_shift;
+  const uint32_t ntx = (i1 >> a.tw_shift) - tx0 + 1u, nty = (j1 >> a.th_shift) - ty0 + 1u;
+  return TileRect{w0.y * (uint32_t)a.tiles_per_view + ty0 * (uint32_t)a.tiles_x + tx0, ntx | (nty << 16)};
+}
+
+__device__ __forceinline__ void count_tile(const EmitArgs& a, uint32_t (*s_hist)[kTileDigits], uint32_t key) {
+  const uint32_t mask = (1u << a.bits) - 1u;
+  for (int p = 0; p < a.passes; ++p) atomicAdd(&s_hist[p][(key >> (a.bits * p)) & mask], 1u);
+}
+
+// One work-group tile of kThreads * ITEMS sorted records: gather, scan, write.
+template <int ITEMS>
+__device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t t, int64_t ntiles,
+                                          uint32_t (*s_hist)[kTileDigits], uint64_t* s_wave64, uint64_t* s_base) {
+  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+  // item k of lane l is element k*64 + l of the wave's contiguous slice
+  const int64_t base = t * kThreads * ITEMS + (int64_t)wid * 64 * ITEMS + lane;
+  uint32_t rid[ITEMS];
+  TileRect rect[ITEMS];
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) rid[k] = base + k * 64 < n ? a.sorted[base + k * 64] : 0u;
   {
-    const int64_t m = count_clamped(counts, GS_COUNT_PAIRS, pair_cap);
-    const int64_t words = ((m + kRadixTile - 1) / kRadixTile) * (int64_t)tpasses * kRadix;
-    for (int64_t i = gtid; i < words; i += stride) pstatus[i] = 0u;
-    for (int64_t i = gtid; i < range_words; i += stride) ranges[i] = 0u;
-  }
-  for (int i = threadIdx.x; i < tpasses * kRadix; i += kThreads) (&s_hist[0][0])[i] = 0u;
-  __syncthreads();
-  const int64_t n = count_clamped(counts, GS_COUNT_VISIBLE, cap);
-  for (int64_t j = gtid; j < n; j += stride) {
-    // the record's tile rectangle, written in this (depth) order by the last depth pass
-    const uint32_t first = tile_first[j], ext = tile_extent[j];
-    const int ntx = (int)(ext & 0xFFFFu), nty = (int)(ext >> 16);
-    if (ntx * nty > kBigFootprint) {  // many tiles: left to emit_big_kernel
-      big_list[atomicAdd(big_count, 1u)] = (uint32_t)j;
-      continue;
+    uint4 w0[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k)
+      w0[k] = base + k * 64 < n ? a.rec_words[(size_t)kRecordWords * rid[k]] : make_uint4(0u, 0u, 0u, 0u);
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      rect[k] = tile_rect(a, w0[k]);
+      if (base + k * 64 >= n) rect[k].extent = 0u;
     }
-    const uint32_t rid = sorted_records[j];
-    int64_t o = pair_off[j];
-    for (int ty = 0; ty < nty; ++ty)
-      for (int tx = 0; tx < ntx; ++tx) {
-        if (o < pair_cap) {
-          const uint32_t key = first + (uint32_t)(ty * tiles_x_n + tx);
-          out_tiles[o] = key;
-          out_records[o] = rid;
-          for (int p = 0; p < tpasses; ++p) atomicAdd(&s_hist[p][(key >> (8 * p)) & 255u], 1u);
+  }
+  // exclusive prefix of the tile counts in slice order; a count may pass 2^25 and 64 of them 2^31, so
+  // the halves are scanned apart
+  uint64_t off[ITEMS], run = 0;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const uint32_t c = rect[k].tiles();
+    uint64_t inc = (uint32_t)wave_incl_scan((int)(c & 0xFFFFu));
+    if (__ballot(c > 0xFFFFu)) inc += (uint64_t)(uint32_t)wave_incl_scan((int)(c >> 16)) << 16;
+    off[k] = run + inc - c;
+    run += ((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(inc >> 32), 63) << 32) |
+           (uint32_t)__builtin_amdgcn_readlane((int)(uint32_t)inc, 63);
+  }
+  if (lane == 0) s_wave64[wid] = run;
+  __syncthreads();
+  uint64_t before = 0, total = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) {
+    const uint64_t v = s_wave64[w];
+    before += w < wid ? v : 0ull;
+    total += v;
+  }
+  if (wid == 0) {
+    const uint64_t ex = lookback64_wave(a.status, t, total, a.counts);
+    if (lane == 0) {
+      *s_base = ex;
+      if (t == ntiles - 1) {
+        a.counts[GS_COUNT_PAIRS] = (int64_t)(ex + total);
+        if ((int64_t)(ex + total) > a.pair_cap) raise_flag(a.counts, GS_FLAG_PAIRS);
+      }
+    }
+  }
+  __syncthreads();
+  const uint64_t tile_base = *s_base + before;
+#pragma unroll
+  for (int k = 0; k < ITEMS; ++k) {
+    const TileRect r = rect[k];  // (no tiles past the end)
+    int64_t o = (int64_t)(tile_base + off[k]);
+    const bool many = r.tiles() > kBigFootprint;
+    const bool big = many && o < a.pair_cap;  // left to emit_big_kernel
+    const uint64_t bm = __ballot(big);
+    if (bm) {  // one device atomic for the wave's
+      uint32_t at = 0;
+      if (lane == __builtin_ctzll(bm)) at = atomicAdd(a.big_count, (uint32_t)__popcll(bm));
+      at = (uint32_t)__builtin_amdgcn_readlane((int)at, __builtin_ctzll(bm)) + (uint32_t)lanemask_lt_count(bm);
+      if (big) {
+        a.big_rec[at] = rid[k];
+        a.big_off[at] = (uint32_t)o;
+      }
+    }
+    if (many) continue;
+    for (uint32_t ty = 0; ty < r.extent >> 16; ++ty)
+      for (uint32_t tx = 0; tx < r.columns(); ++tx) {
+        if (o < a.pair_cap) {
+          const uint32_t key = r.first + ty * (uint32_t)a.tiles_x + tx;
+          a.out_tiles[o] = key;
+          a.out_records[o] = rid[k];
+          count_tile(a, s_hist, key);
         }
         ++o;
       }
   }
-  __syncthreads();
-  const int copy = (int)(blockIdx.x % kTileHistCopies);
-  uint32_t* h = copy == 0 ? hist : hist_extra + (int64_t)(copy - 1) * kTileHistWords;
-  for (int i = threadIdx.x; i < tpasses * kRadix; i += kThreads) {
-    const uint32_t c = (&s_hist[0][0])[i];
-    if (c) atomicAdd(&h[i], c);
+}
+
+// The gather of one 16-byte word per visible record in depth order bounds it: a
+// line of 128 B per record (437 MB for 4M records, 3.8 TB/s), ITEMS gathers of a
+// thread in flight.  Scan and emission in one kernel write the rectangles and
+// offsets nowhere: 4M records 117 us, where a depth pass that gathered and scanned
+// (118 against 52 for a plain one) and the emission (33) took 99 more than the
+// plain pass; what is won is the passes' uniform shape and three arrays.
+__global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
+  __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
+  __shared__ uint64_t s_wave64[kThreads / 64], s_base;
+  __shared__ uint32_t s_tile;
+  const int64_t n = count_clamped(a.counts, GS_COUNT_VISIBLE, a.cap);
+  const int items = emit_items(count_clamped(a.counts, GS_COUNT_RECORDS, a.cap));
+  const int64_t ntiles = (n + (int64_t)kThreads * items - 1) / ((int64_t)kThreads * items);
+  if ((int64_t)blockIdx.x >= ntiles) return;
+  for (int p = 0; p < a.passes; ++p)
+    for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
+  for (;;) {
+    if (threadIdx.x == 0) s_tile = atomicAdd(a.tile_counter, 1u);
+    __syncthreads();
+    const int64_t t = s_tile;
+    if (t >= ntiles) break;
+    if (items == 1) emit_tile<1>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    else if (items == 4) emit_tile<4>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    else emit_tile<kEmitMaxItems>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    __syncthreads();
   }
+  const int copy = (int)(blockIdx.x % kTileHistCopies);
+  uint32_t* h = copy == 0 ? a.hist : a.hist_extra + (int64_t)(copy - 1) * kTileHistWords;
+  for (int p = 0; p < a.passes; ++p)
+    for (int i = threadIdx.x; i < kTileDigits; i += kThreads) {
+      const uint32_t c = s_hist[p][i];
+      if (c) atomicAdd(&h[p * kTileDigits + i], c);
+    }
 }
 
 // Records whose footprint covers many tiles (a Gaussian close to the camera):
 // one work-group per record, its tiles strided over the threads, written to
 // the same slots (row-major tile order) the serial loop would use.
-__global__ void __launch_bounds__(kThreads) emit_big_kernel(const uint32_t* __restrict__ tile_first,
-                                                            const uint32_t* __restrict__ tile_extent,
-                                                            const uint32_t* __restrict__ sorted_records,
-                                                            const uint32_t* __restrict__ pair_off,
-                                                            const uint32_t* __restrict__ big_list,
-                                                            const uint32_t* __restrict__ big_count, int64_t pair_cap,
-                                                            int tw, int th, int tiles_x_n, int tiles_per_view,
-                                                            uint32_t* __restrict__ out_tiles,
-                                                            uint32_t* __restrict__ out_records, int tpasses,
-                                                            uint32_t* __restrict__ hist,
-                                                            const uint32_t* __restrict__ hist_extra) {
-  __shared__ uint32_t s_hist[kMaxPasses][kRadix];
-  for (int i = threadIdx.x; i < tpasses * kRadix; i += kThreads) (&s_hist[0][0])[i] = 0u;
+__global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
+  __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
+  const uint32_t nbig = *a.big_count;
   // emit_kernel has finished (same stream): its partial histograms are final
   if (blockIdx.x == 0) {
-    for (int i = threadIdx.x; i < tpasses * kRadix; i += kThreads) {
+    for (int i = threadIdx.x; i < a.passes * kTileDigits; i += kThreads) {
       uint32_t part[kTileHistCopies - 1];
 #pragma unroll
-      for (int c = 0; c < kTileHistCopies - 1; ++c) part[c] = hist_extra[c * kTileHistWords + i];
+      for (int c = 0; c < kTileHistCopies - 1; ++c) part[c] = a.hist_extra[c * kTileHistWords + i];
       uint32_t sum = 0;
 #pragma unroll
       for (int c = 0; c < kTileHistCopies - 1; ++c) sum += part[c];
-      if (sum) atomicAdd(&hist[i], sum);
+      if (sum) atomicAdd(&a.hist[i], sum);
     }
   }
+  if (blockIdx.x >= nbig) return;
+  for (int p = 0; p < a.passes; ++p)
+    for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
   __syncthreads();
-  const uint32_t nbig = *big_count;
   for (uint32_t k = blockIdx.x; k < nbig; k += gridDim.x) {
-    const uint32_t j = big_list[k];
-    const uint32_t rid = sorted_records[j];
-    const uint32_t first = tile_first[j], ext = tile_extent[j];
-    const int ntx = (int)(ext & 0xFFFFu), nty = (int)(ext >> 16);
-    const int64_t o0 = pair_off[j];
-    for (int q = threadIdx.x; q < ntx * nty; q += kThreads) {
+    const uint32_t rid = a.big_rec[k];
+    const TileRect r = tile_rect(a, a.rec_words[(size_t)kRecordWords * rid]);
+    const int64_t o0 = a.big_off[k];
+    for (uint32_t q = threadIdx.x; q < r.tiles(); q += kThreads) {
       const int64_t o = o0 + q;
-      if (o < pair_cap) {
-        const int ty = q / ntx, tx = q % ntx;
-        const uint32_t key = first + (uint32_t)(ty * tiles_x_n + tx);
-        out_tiles[o] = key;
-        out_records[o] = rid;
-        for (int p = 0; p < tpasses; ++p) atomicAdd(&s_hist[p][(key >> (8 * p)) & 255u], 1u);
+      if (o < a.pair_cap) {
+        const uint32_t ty = q / r.columns(), tx = q % r.columns();
+        const uint32_t key = r.first + ty * (uint32_t)a.tiles_x + tx;
+        a.out_tiles[o] = key;
+        a.out_records[o] = rid;
+        count_tile(a, s_hist, key);
       }
     }
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < tpasses * kRadix; i += kThreads) {
-    const uint32_t c = (&s_hist[0][0])[i];
-    if (c) atomicAdd(&hist[i], c);
-  }
+  for (int p = 0; p < a.passes; ++p)
+    for (int i = threadIdx.x; i < kTileDigits; i += kThreads) {
+      const uint32_t c = s_hist[p][i];
+      if (c) atomicAdd(&a.hist[p * kTileDigits + i], c);
+    }
 }
 
 // ---------------------------------------------------------------------------
@@ -342,32 +458,29 @@ __global__ void queue_scatter_kernel(const uint32_t* __restrict__ ranges, int64_
 // ---------------------------------------------------------------------------
 // workspace layout
 // ---------------------------------------------------------------------------
-// tile counters [64], depth + tile digit histograms [2][kMaxPasses][256], queue histogram and cursors
-// [2][40], partial tile-digit histograms of emit_kernel [kTileHistCopies - 1][kMaxPasses][256], partial
-// depth-digit histograms of depth_hist_kernel [kDepthHistCopies - 1][4][256]
+// counters [64], depth digit histograms [4][256], tile digit histograms, queue histogram and cursors
+// [2][40], partial tile-digit histograms of emit_kernel [kTileHistCopies - 1], partial depth-digit
+// histograms of depth_hist_kernel [kDepthHistCopies - 1][4][256]
 constexpr int64_t kQueueWords = 2 * 40;
-constexpr int64_t kTileExtraAt = 64 + 2 * kMaxPasses * kRadix + kQueueWords;
+constexpr int64_t kTileHistAt = 64 + kDepthHistWords;
+constexpr int64_t kQueueAt = kTileHistAt + kTileHistWords;
+constexpr int64_t kTileExtraAt = kQueueAt + kQueueWords;
 constexpr int64_t kDepthExtraAt = kTileExtraAt + (kTileHistCopies - 1) * kTileHistWords;
-// partial histograms of tiles_touched by the top depth digit, u64 [kDepthHistCopies][256] (the last
-// depth pass sums the copies)
-constexpr int64_t kWhistAt = ((kDepthExtraAt + (kDepthHistCopies - 1) * kDepthHistWords) + 1) & ~(int64_t)1;
-constexpr int64_t kFixedWords = kWhistAt + 2 * kDepthHistCopies * kRadix;
+constexpr int64_t kFixedWords = kDepthExtraAt + (kDepthHistCopies - 1) * kDepthHistWords;
 
 struct SortWs {
-  uint32_t* dkeys_a;      // [rc]
-  uint32_t* dvals_a;      // [rc]
-  uint32_t* dkeys_b;      // [rc]
-  uint32_t* dvals_b;      // [rc]
-  uint32_t* pair_off;     // [rc]
-  uint32_t* big_list;     // [rc] visible records with large footprints
-  uint32_t* tile_extent;  // [rc] tile columns | rows << 16 per visible record, depth order
-                          // (its first tile id goes to dkeys_a, free in the last depth pass)
-  uint32_t* ptiles_alt;   // [pc]
-  uint32_t* precs_alt;    // [pc]
-  uint32_t* fixed;        // counters [64], hist [2][kMaxPasses][256], queue words, partial tile hists
-  uint32_t* dstatus;      // [radix tiles][4][256] (tile-major so a prefix covers every pass; slot 3 unused)
-  uint64_t* p3status;     // [radix tiles][256]: last depth pass, record count and pair sum per word
-  uint32_t* pstatus;      // [ptiles][kMaxPasses][256]
+  uint32_t* dkeys_a;     // [rc]
+  uint32_t* dvals_a;     // [rc]
+  uint32_t* dkeys_b;     // [rc]
+  uint32_t* dvals_b;     // [rc]
+  uint32_t* big_rec;     // [rc] visible records with large footprints
+  uint32_t* big_off;     // [rc] their first pair
+  uint32_t* ptiles_alt;  // [pc]
+  uint32_t* precs_alt;   // [pc]
+  uint32_t* fixed;       // see above
+  uint32_t* dstatus;     // [radix tiles][4][256]
+  uint64_t* estatus;     // [emission tiles]
+  uint32_t* pstatus;     // [radix tiles][kTileHistWords]
   size_t bytes;
 };
 
@@ -381,21 +494,18 @@ SortWs sort_ws_layout(char* base, int64_t rc, int64_t pc) {
     off = align_up(off + bytes);
     return p;
   };
-  const int64_t drtiles = (rc + kRadixTile - 1) / kRadixTile + 1;  // radix tiles over records
-  const int64_t ptiles = (pc + kRadixTile - 1) / kRadixTile + 1;   // radix tiles over pairs
   w.dkeys_a = (uint32_t*)take(4 * (size_t)rc);
   w.dvals_a = (uint32_t*)take(4 * (size_t)rc);
   w.dkeys_b = (uint32_t*)take(4 * (size_t)rc);
   w.dvals_b = (uint32_t*)take(4 * (size_t)rc);
-  w.pair_off = (uint32_t*)take(4 * (size_t)rc);
-  w.big_list = (uint32_t*)take(4 * (size_t)rc);
-  w.tile_extent = (uint32_t*)take(4 * (size_t)rc);
+  w.big_rec = (uint32_t*)take(4 * (size_t)rc);
+  w.big_off = (uint32_t*)take(4 * (size_t)rc);
   w.ptiles_alt = (uint32_t*)take(4 * (size_t)pc);
   w.precs_alt = (uint32_t*)take(4 * (size_t)pc);
   w.fixed = (uint32_t*)take(4 * (size_t)kFixedWords);
-  w.dstatus = (uint32_t*)take(4 * 4 * (size_t)drtiles * kRadix);
-  w.p3status = (uint64_t*)take(8 * (size_t)drtiles * kRadix);
-  w.pstatus = (uint32_t*)take(4 * (size_t)kMaxPasses * (size_t)ptiles * kRadix);
+  w.dstatus = (uint32_t*)take(4 * (size_t)radix_tiles_bound(rc) * 4 * kRadix);
+  w.estatus = (uint64_t*)take(8 * (size_t)emit_tiles_bound(rc));
+  w.pstatus = (uint32_t*)take(4 * (size_t)radix_tiles_bound(pc) * kTileHistWords);
   w.bytes = off;
   return w;
 }
@@ -434,80 +544,93 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   const int64_t n_tile_ids = tiles_per_view * n_views;
   if (n_tile_ids >= ((int64_t)1 << 31)) return GS_ERR_INVALID_ARG;
   const int tbits = tile_bits(n_tile_ids);
-  const int tpasses = tbits == 0 ? 0 : (tbits + 7) / 8;
+  // tile digits of up to 9 bits, as few passes as that allows and of equal width
+  const int tpasses = (tbits + 8) / 9;
+  const int tdigit = tpasses ? (tbits + tpasses - 1) / tpasses : 0;
   hipStream_t s = (hipStream_t)stream;
   const dim3 blk(kThreads);
   auto grid_for = [](int64_t items) {
     int64_t g = (items + kThreads - 1) / kThreads;
     return dim3((unsigned)(g < 1 ? 1 : (g > 2048 ? 2048 : g)));
   };
-  auto persistent_radix = [](int64_t cap) {
-    int64_t g = (cap + kRadixTile - 1) / kRadixTile;
-    return dim3((unsigned)(g < 1 ? 1 : (g > kPersistentBlocks ? kPersistentBlocks : g)));
-  };
   uint32_t* counters = w.fixed;
   uint32_t* dhist = w.fixed + 64;
-  uint32_t* thist = w.fixed + 64 + kMaxPasses * kRadix;
-  uint64_t* whist = (uint64_t*)(w.fixed + kWhistAt);
+  uint32_t* thist = w.fixed + kTileHistAt;
   uint32_t* dhist_extra = w.fixed + kDepthExtraAt;
-  // 0. zero the counters, histograms and the depth passes' look-back words
+  const int trb = tdigit == 9 ? 9 : 8;               // digit bits of the pass's instance (a word per value)
+  const int64_t prow = (int64_t)tpasses << trb;  // look-back words of a radix tile over all tile passes
+  // 0. zero the counters, histograms, look-back words and ranges
   {
-    const int64_t drt = (record_capacity + kRadixTile - 1) / kRadixTile;
-    hipLaunchKernelGGL(clear_front_kernel, grid_for(kFixedWords + drt * 5 * kRadix), blk, 0, s, w.fixed,
-                       kFixedWords, counts, record_capacity, w.dstatus, w.p3status);
+    const ClearArgs c{w.fixed, kFixedWords, w.dstatus, w.estatus, w.pstatus, radix_tiles_bound(pair_capacity) * prow,
+                      tile_ranges, 2 * n_tile_ids};
+    const int64_t drt = radix_tiles_bound(record_capacity) * 4 * kRadix;
+    const int64_t most = drt > c.pstatus_words ? drt : c.pstatus_words;
+    hipLaunchKernelGGL(clear_front_kernel, grid_for(most > kFixedWords ? most : kFixedWords), blk, 0, s, c, counts,
+                       record_capacity);
   }
   GS_LAUNCH_CHECK();
-  // 1. histograms of the four depth digits and of the pairs by the top digit
-  hipLaunchKernelGGL(depth_hist_kernel, grid_for((record_capacity + kItems - 1) / kItems), blk, 0, s, tiles_touched,
-                     depth_keys, record_capacity, counts, dhist, dhist_extra, whist);
+  // 1. histograms of the four depth digits
+  hipLaunchKernelGGL(depth_hist_kernel, grid_for((record_capacity + kHistItems - 1) / kHistItems), blk, 0, s,
+                     tiles_touched, depth_keys, record_capacity, counts, dhist, dhist_extra);
   GS_LAUNCH_CHECK();
   // 2. depth sort, 4 passes of 8 bits: selected records -> b -> a -> b -> a.  The first pass keeps
-  //    the visible records (index order within a digit) and writes counts[GS_COUNT_VISIBLE]; the
-  //    last also writes the pair offsets (exclusive prefix of tiles_touched in depth order) and
-  //    counts[GS_COUNT_PAIRS].  Each pass adds the partial copies of its digit histogram.
-  const int tw_shift = __builtin_ctz((unsigned)tw), th_shift = __builtin_ctz((unsigned)th);  // powers of two
-  auto extra = [&](int p, const uint64_t* wh, uint64_t* pst, uint32_t* poff) {
-    return PairPass{tiles_touched, (const uint4*)records, tw_shift, th_shift, tx_n, (int)tiles_per_view,
-                    w.dkeys_a, w.tile_extent, wh, kDepthHistCopies, pst, poff, pair_capacity,
-                    dhist_extra + p * kRadix, kDepthHistCopies - 1, kDepthHistWords};
+  //    the visible records (index order within a digit) and writes counts[GS_COUNT_VISIBLE].  Each
+  //    pass adds the partial copies of its digit histogram.
+  auto depth_pass = [&](int p, const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout) {
+    return RadixPass{kin, vin, kout, vout, counts, p == 0 ? GS_COUNT_RECORDS : GS_COUNT_VISIBLE, GS_COUNT_RECORDS,
+                     record_capacity, 8 * p, 8, dhist + p * kRadix, dhist_extra + p * kRadix,
+                     kDepthHistCopies - 1, kDepthHistWords, w.dstatus + p * kRadix, (int64_t)4 * kRadix,
+                     counters + 1 + p, counts, tiles_touched};
   };
-  hipLaunchKernelGGL((radix_pass_kernel<kPassCompact>), persistent_radix(record_capacity), blk, 0, s, depth_keys,
-                     nullptr, w.dkeys_b, w.dvals_b, counts, GS_COUNT_RECORDS, record_capacity, 0, dhist,
-                     w.dstatus, (int64_t)4 * kRadix, counters + 1, counts, extra(0, nullptr, nullptr, nullptr));
-  hipLaunchKernelGGL((radix_pass_kernel<kPassPlain>), persistent_radix(record_capacity), blk, 0, s, w.dkeys_b,
-                     w.dvals_b, w.dkeys_a, w.dvals_a, counts, GS_COUNT_VISIBLE, record_capacity, 8, dhist + kRadix,
-                     w.dstatus + kRadix, (int64_t)4 * kRadix, counters + 2, counts, extra(1, nullptr, nullptr, nullptr));
-  hipLaunchKernelGGL((radix_pass_kernel<kPassPlain>), persistent_radix(record_capacity), blk, 0, s, w.dkeys_a,
-                     w.dvals_a, w.dkeys_b, w.dvals_b, counts, GS_COUNT_VISIBLE, record_capacity, 16,
-                     dhist + 2 * kRadix, w.dstatus + 2 * kRadix, (int64_t)4 * kRadix, counters + 3, counts,
-                     extra(2, nullptr, nullptr, nullptr));
-  hipLaunchKernelGGL((radix_pass_kernel<kPassPairs>), persistent_radix(record_capacity), blk, 0, s, w.dkeys_b,
-                     w.dvals_b, w.dkeys_a, w.dvals_a, counts, GS_COUNT_VISIBLE, record_capacity, 24,
-                     dhist + 3 * kRadix, nullptr, (int64_t)0, counters + 4, counts,
-                     extra(3, whist, w.p3status, w.pair_off));
+  const dim3 dgrid = radix_grid(record_capacity), rblk(kRadixThreads);
+  hipLaunchKernelGGL((radix_pass_kernel<8, true>), dgrid, rblk, 0, s,
+                     depth_pass(0, depth_keys, nullptr, w.dkeys_b, w.dvals_b));
+  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                     depth_pass(1, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
+  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                     depth_pass(2, w.dkeys_a, w.dvals_a, w.dkeys_b, w.dvals_b));
+  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                     depth_pass(3, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
   GS_LAUNCH_CHECK();
-  // 3. emission (+ tile-digit histograms, + zeroing of the tile-pass state and ranges), into the
-  //    buffer that the last tile pass will read last
-  uint32_t* em_tiles = (tpasses % 2 == 0) ? pair_tiles : w.ptiles_alt;
-  uint32_t* em_recs = (tpasses % 2 == 0) ? pair_records : w.precs_alt;
-  uint32_t* big_count = counters + 32;
-  uint32_t* thist_extra = w.fixed + kTileExtraAt;
-  hipLaunchKernelGGL(emit_kernel, grid_for(record_capacity), blk, 0, s, w.dkeys_a, w.tile_extent, w.dvals_a, w.pair_off,
-                     record_capacity, counts, pair_capacity, tw, th, tx_n, (int)tiles_per_view, em_tiles, em_recs,
-                     tpasses, thist, w.pstatus, tile_ranges, 2 * n_tile_ids, w.big_list, big_count, thist_extra);
-  hipLaunchKernelGGL(emit_big_kernel, dim3(256), blk, 0, s, w.dkeys_a, w.tile_extent, w.dvals_a, w.pair_off, w.big_list,
-                     big_count, pair_capacity, tw, th, tx_n, (int)tiles_per_view, em_tiles, em_recs, tpasses, thist,
-                     thist_extra);
+  // 3. emission (+ tile-digit histograms), into the buffer from which the last tile pass ends in the
+  //    caller's arrays
+  EmitArgs e{};
+  e.rec_words = (const uint4*)records;
+  e.sorted = w.dvals_a;
+  e.counts = counts;
+  e.cap = record_capacity;
+  e.pair_cap = pair_capacity;
+  e.tw_shift = __builtin_ctz((unsigned)tw);
+  e.th_shift = __builtin_ctz((unsigned)th);
+  e.tiles_x = tx_n;
+  e.tiles_per_view = (int)tiles_per_view;
+  e.out_tiles = (tpasses % 2 == 0) ? pair_tiles : w.ptiles_alt;
+  e.out_records = (tpasses % 2 == 0) ? pair_records : w.precs_alt;
+  e.passes = tpasses;
+  e.bits = tdigit;
+  e.hist = thist;
+  e.hist_extra = w.fixed + kTileExtraAt;
+  e.status = w.estatus;
+  e.tile_counter = counters + 24;
+  e.big_rec = w.big_rec;
+  e.big_off = w.big_off;
+  e.big_count = counters + 32;
+  const int64_t eg = emit_tiles_bound(record_capacity);
+  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(eg < 2048 ? eg : 2048)), blk, 0, s, e);
+  hipLaunchKernelGGL(emit_big_kernel, dim3(256), blk, 0, s, e);
   GS_LAUNCH_CHECK();
   // 4. tile passes
-  uint32_t* kin = em_tiles;
-  uint32_t* vin = em_recs;
+  uint32_t* kin = e.out_tiles;
+  uint32_t* vin = e.out_records;
   for (int p = 0; p < tpasses; ++p) {
     uint32_t* kout = (kin == pair_tiles) ? w.ptiles_alt : pair_tiles;
     uint32_t* vout = (vin == pair_records) ? w.precs_alt : pair_records;
-    hipLaunchKernelGGL((radix_pass_kernel<kPassPlain>), persistent_radix(pair_capacity), blk, 0, s, kin, vin, kout, vout,
-                       counts, GS_COUNT_PAIRS, pair_capacity, 8 * p, thist + p * kRadix, w.pstatus + p * kRadix,
-                       (int64_t)tpasses * kRadix, counters + 16 + p, counts, PairPass{});
+    const RadixPass a{kin, vin, kout, vout, counts, GS_COUNT_PAIRS, GS_COUNT_PAIRS, pair_capacity, tdigit * p,
+                      tdigit, thist + p * kTileDigits, nullptr, 0, 0,
+                      w.pstatus + ((int64_t)p << trb), prow, counters + 16 + p, counts, nullptr};
+    const dim3 pgrid = radix_grid(pair_capacity);
+    if (trb == 9) hipLaunchKernelGGL((radix_pass_kernel<9, false>), pgrid, rblk, 0, s, a);
+    else hipLaunchKernelGGL((radix_pass_kernel<8, false>), pgrid, rblk, 0, s, a);
     GS_LAUNCH_CHECK();
     kin = kout;
     vin = vout;
@@ -518,7 +641,7 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   GS_LAUNCH_CHECK();
   // 6. work queue
   if ((tuning->flags & GS_TUNE_WORK_QUEUE) && tile_queue) {
-    uint32_t* qhist = w.fixed + 64 + 2 * kMaxPasses * kRadix;
+    uint32_t* qhist = w.fixed + kQueueAt;
     uint32_t* qcur = qhist + 40;
     hipLaunchKernelGGL(queue_hist_kernel, grid_for(n_tile_ids), blk, 0, s, tile_ranges, n_tile_ids, qhist);
     hipLaunchKernelGGL(queue_scatter_kernel, grid_for(n_tile_ids), blk, 0, s, tile_ranges, n_tile_ids, qhist, qcur,
