@@ -7,9 +7,9 @@
 // keeps its own depth-ordered list of the staged records whose footprint meets
 // it, and the groups walk their lists side by side (a lane reads the record of
 // its group), so a small footprint occupies one group's step rather than a
-// whole wave's.  A lane leaves the loop when its transmittance would drop below
-// 1e-4; a wave leaves when all its lanes have, the work-group when all waves
-// have (block-wide vote before each batch).
+// whole wave's.  A lane is done when its transmittance would drop below 1e-4 (its
+// x becomes NaN, on which every footprint test fails); a wave leaves when all its
+// lanes are, the work-group when all waves have (block-wide vote before each batch).
 //
 // Compiled with -ffp-contract=off: alpha is computed by exactly the same
 // operations as in the adjoint (explicit fmaf), so the backward's recomputed
@@ -29,7 +29,7 @@ template <int TW, int TH, int BATCH>
 struct FwdLds {
   float4 w0[BATCH], w1[BATCH], w2[BATCH];
   float4 f[BATCH];  // footprint as floats: i0, j0, i1 - i0, j1 - j0
-  uint8_t list[(TW * TH) / 64][kFwdGroups][kListStride<BATCH>];
+  alignas(16) uint8_t list[(TW * TH) / 64][kFwdGroups][kListStride<BATCH>];
   uint8_t cand[(TW * TH) / 64][BATCH];
 };
 
@@ -52,17 +52,22 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
   const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const LaneMap<TW, TH, kFwdGW, kFwdGH> qb(txi, tyi, wid);
   const int i = qb.i, j = qb.j;
-  const float fi = (float)i, fj = (float)j;
   const bool inside = (i < W) && (j < H);
+  // a pixel that is done has no x: every footprint test fails on it (a NaN's bits are above any float's)
+  float fi = inside ? (float)i : __builtin_nanf("");
+  const float fj = (float)j;
   const uint32_t start = ranges[2 * tile_g], end = ranges[2 * tile_g + 1];
   float T = 1.0f, C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
   int last = 0;
-  bool done = !inside;
   uint8_t(*lists)[kListStride<BATCH>] = lds.list[wid];
   const uint8_t* my_list = lists[qb.g];
-  for (uint32_t b = start; b < end; b += BATCH) {
-    if (__syncthreads_and(done)) break;
-    const int nb = (int)min((uint32_t)BATCH, end - b);
+  if (threadIdx.x == 0) {
+    const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    s_w0[BATCH - 1] = s_w1[BATCH - 1] = s_w2[BATCH - 1] = s_f[BATCH - 1] = zero;  // the null record
+  }
+  for (uint32_t b = start; b < end; b += BATCH - 1) {
+    if (__syncthreads_and(!(fi == fi))) break;
+    const int nb = (int)min((uint32_t)(BATCH - 1), end - b);
     for (int k = threadIdx.x; k < nb; k += NT) {
       const float4* r = reinterpret_cast<const float4*>(&records[pair_records[b + k]]);
       float4 a = r[0];
@@ -73,37 +78,36 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
       s_w2[k] = r[2];
       s_f[k] = footprint_floats(a);
     }
-    // list entries past a group's count read stale indices that may land on
-    // unstaged slots: their colour must be finite (it is multiplied by 0)
-    for (int k = nb + threadIdx.x; k < BATCH; k += NT) s_w2[k] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    clear_lists<BATCH, kFwdGroups>(lists);
     __syncthreads();
-    const Counts8 cnt = wave_compact8<BATCH>(s_w0, s_f, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
-    const int max_cnt = cnt.max();
-    const int my_cnt = cnt.of(qb.g);
+    const int max_cnt =
+        wave_compact8<BATCH>(s_w0, s_f, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
     const int base_idx = (int)(b - start);
     int last_k = -1;  // 16 x the batch index of the last entry used in this batch
-    auto blend = [&](int k, bool valid, float du, const float4& f, const float4& w1, const float4& w2) {
+    auto blend = [&](int k, float du, const float4& f, const float4& w1, const float4& w2) {
       Eval e;
       const bool in_fp = evaluate_f(fi, fj, f, du, w2.w, w1, e);
-      bool use = valid && !done && in_fp && (e.alpha >= kAlphaMin);
-      const float Tn = T * (1.0f - e.alpha);
-      const bool stop = use && (Tn < kTMin);
-      done = done || stop;
-      use = use && !stop;
-      // an unused entry adds colour * 0 (colours are finite): C is unchanged bit for bit
-      const float aT = use ? e.alpha * T : 0.0f;
-      C0 = fmaf(w2.x, aT, C0);
+      bool use = in_fp & (e.alpha >= kAlphaMin);
+      float alpha = use ? e.alpha : 0.0f;  // an entry that is not used leaves T and C as they are
+      float Tn = T * (1.0f - alpha);
+      const bool stop = Tn < kTMin;  // (T is not below it: only an entry in use takes it there)
+      if (__ballot(stop)) {  // once per pixel
+        alpha = stop ? 0.0f : alpha;
+        Tn = stop ? T : Tn;
+        use = use & !stop;
+        fi = stop ? __builtin_nanf("") : fi;
+      }
+      const float aT = alpha * T;
+      C0 = fmaf(w2.x, aT, C0);  // (colours are finite)
       C1 = fmaf(w2.y, aT, C1);
       C2 = fmaf(w2.z, aT, C2);
-      T = use ? Tn : T;
+      T = Tn;
       last_k = use ? k : last_k;
     };
     // four entries of the lane's group list per trip: one LDS read for the
-    // four byte indices, all records' words in flight together, one vote per
-    // trip (entries past the group's count are read from stale list bytes,
-    // masked into the staged range and not used)
+    // four byte indices, all records' words in flight together (past the
+    // group's count: the null record)
     for (int t = 0; t < max_cnt; t += 4) {
-      if (__ballot(!done && t < my_cnt) == 0) break;
       // byte offsets (index * 16) of the four entries into the staged arrays
       const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
       const uint32_t o0 = (pk & (BATCH - 1)) << 4, o1 = ((pk >> 8) & (BATCH - 1)) << 4;
@@ -119,10 +123,11 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
       const float4 bf = at(s_f, o1), b1 = at(s_w1, o1), b2 = at(s_w2, o1);
       const float4 cf = at(s_f, o2), c1 = at(s_w1, o2), c2 = at(s_w2, o2);
       const float4 df = at(s_f, o3), d1 = at(s_w1, o3), d2 = at(s_w2, o3);
-      blend((int)o0, t < my_cnt, au, af, a1, a2);
-      blend((int)o1, t + 1 < my_cnt, bu, bf, b1, b2);
-      blend((int)o2, t + 2 < my_cnt, cu, cf, c1, c2);
-      blend((int)o3, t + 3 < my_cnt, du, df, d1, d2);
+      blend((int)o0, au, af, a1, a2);
+      blend((int)o1, bu, bf, b1, b2);
+      blend((int)o2, cu, cf, c1, c2);
+      blend((int)o3, du, df, d1, d2);
+      if (__ballot(fi == fi) == 0) break;  // every pixel of the wave is done
     }
     if (last_k >= 0) last = base_idx + (last_k >> 4) + 1;
     __syncthreads();
@@ -139,9 +144,13 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
   }
 }
 
-// Six waves per SIMD for the multi-wave tiles: at 80 registers the compiler
-// spills six of them, and the sixth wave is still worth more than the freer
-// allocation (one 8-view city call: 0.367 ms at six waves, 0.408 ms at five).
+// Bound by VALU issue (with the groups' lists, about 24 instructions and an
+// exponential per entry).  Measured, us per call: eight 1600x900 views of the 20M
+// city 384 before the lists left out unreachable groups, 374 with that, 337 with the
+// loop free of per-entry count, done and stop selects; 16 views of a 2M block 1977,
+// 1514, 1348; 4096 Gaussians at 256x256 53, 35, 30.  Six waves per SIMD for the
+// multi-wave tiles (the compiler spills a dozen registers outside the loop): 1348 for
+// the block, 1448 at five, 1440 at seven.
 template <int TW, int TH, int BATCH>
 __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(TW * TH >= 128 ? 6 : 1))) raster_fwd_kernel(TileArgs ta, uint32_t* queue, float bg0, float bg1,
                                                             float bg2, float* __restrict__ rgb,

@@ -35,7 +35,7 @@ __device__ __forceinline__ bool evaluate_f(float fi, float fj, const float4& f, 
   e.dx = fdi - du;
   e.dy = fdj - dv;
   evaluate_at(w1, e);
-  return (__float_as_uint(fdi) <= __float_as_uint(f.z)) && (__float_as_uint(fdj) <= __float_as_uint(f.w));
+  return (__float_as_uint(fdi) <= __float_as_uint(f.z)) & (__float_as_uint(fdj) <= __float_as_uint(f.w));
 }
 
 // Lane -> pixel map of the tile kernels: the tile is cut into 8x8 pixel
@@ -73,22 +73,22 @@ __device__ __forceinline__ float4 footprint_floats(const float4& w0) {
   return make_float4((float)(px & 0xFFFFu), (float)(py & 0xFFFFu), (float)(px >> 16), (float)(py >> 16));
 }
 
-// Per-group lists: list[g][0 .. cnt[g]) receives, in ascending (= depth) order,
-// the staged records that may contribute to a pixel of group g of the wave's
-// block.  The counts are a struct of named scalars (arrays of them end up in
-// scratch memory).
-struct Counts8 {
-  int c0, c1, c2, c3, c4, c5, c6, c7;
-  __device__ __forceinline__ int max() const {
-    return ::max(::max(::max(c0, c1), ::max(c2, c3)), ::max(::max(c4, c5), ::max(c6, c7)));
-  }
-  __device__ __forceinline__ int of(int g) const {
-    const int lo = g == 0 ? c0 : g == 1 ? c1 : g == 2 ? c2 : c3;
-    const int hi = g == 4 ? c4 : g == 5 ? c5 : g == 6 ? c6 : c7;
-    return g < 4 ? lo : hi;
-  }
-};
+// All entries of a wave's group lists to BATCH - 1, the place of a null record
+// (opacity 0: never blended) after the records of a round, so a group whose list is
+// shorter than the wave's longest walks the null record instead of testing its
+// position against its count at each entry (16-byte stores; the lists of a wave are
+// contiguous).
+template <int BATCH, int GROUPS>
+__device__ __forceinline__ void clear_lists(uint8_t (*list)[kListStride<BATCH>]) {
+  constexpr uint32_t kFill = 0x01010101u * (uint32_t)(BATCH - 1);
+  static_assert(GROUPS * kListStride<BATCH> % 16 == 0, "whole 16-byte words");
+  uint4* p = reinterpret_cast<uint4*>(&list[0][0]);
+  for (int k = threadIdx.x & 63; k < GROUPS * kListStride<BATCH> / 16; k += 64)
+    p[k] = make_uint4(kFill, kFill, kFill, kFill);
+}
 
+// Per-group lists: list[g][0 .. count) receives, in ascending (= depth) order, the
+// staged records that may contribute to a pixel of group g of the wave's block.
 __device__ __forceinline__ void append_if(bool h, uint8_t* list, int& c, int k) {
   const uint64_t m = __ballot(h);
   if (h) list[c + (int)lanemask_lt_count(m)] = (uint8_t)k;
@@ -171,14 +171,15 @@ __device__ __forceinline__ int wave_candidates(const float4* s_w0, int nb, int x
 }
 
 // 4x2 groups (two columns of four pixels, four rows of two; row-major).  s_w0[k].y
-// holds q_limit of the record (its view is not needed once staged).
+// holds q_limit of the record (its view is not needed once staged).  Returns the
+// length of the longest list.
 template <int BATCH>
-__device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float4* s_f, const float4* s_w1,
+__device__ __forceinline__ int wave_compact8(const float4* s_w0, const float4* s_f, const float4* s_w1,
                                                  const float4* s_w2, int nb, int x0, int y0, uint8_t* cand,
                                                  uint8_t (*list)[kListStride<BATCH>]) {
   const int lane = threadIdx.x & 63;
   const int nc = wave_candidates<BATCH>(s_w0, nb, x0, y0, cand);
-  Counts8 c{0, 0, 0, 0, 0, 0, 0, 0};
+  int c0 = 0, c1 = 0, c2 = 0, c3 = 0, c4 = 0, c5 = 0, c6 = 0, c7 = 0;
   for (int base = 0; base < nc; base += 64) {
     const bool in = base + lane < nc;
     const int k = in ? (int)cand[base + lane] : 0;
@@ -192,12 +193,12 @@ __device__ __forceinline__ Counts8 wave_compact8(const float4* s_w0, const float
       append_if(xa & y & t.reach(0.0f, r, r2), la, ca, k);
       append_if(xb & y & t.reach(4.0f, r, r2), lb, cb, k);
     };
-    rows(0.0f, list[0], c.c0, list[1], c.c1);
-    rows(2.0f, list[2], c.c2, list[3], c.c3);
-    rows(4.0f, list[4], c.c4, list[5], c.c5);
-    rows(6.0f, list[6], c.c6, list[7], c.c7);
+    rows(0.0f, list[0], c0, list[1], c1);
+    rows(2.0f, list[2], c2, list[3], c3);
+    rows(4.0f, list[4], c4, list[5], c5);
+    rows(6.0f, list[6], c6, list[7], c7);
   }
-  return c;
+  return max(max(max(c0, c1), max(c2, c3)), max(max(c4, c5), max(c6, c7)));
 }
 
 struct TileArgs {
