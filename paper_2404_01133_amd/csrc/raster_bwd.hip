@@ -87,7 +87,13 @@ __device__ __forceinline__ bool quad_writes(int r) { return !(r & 1) || r == 1; 
 // (dG/dQ = -ln2 G); the flush applies it once.
 constexpr int kG = 9;
 constexpr int kGQ = 4;  // first partial with that factor
-__device__ __forceinline__ float q_scale(int q, float opac) { return q >= kGQ ? -0.69314718055994531f * opac : 1.0f; }
+// Partial q of a staged record as it leaves the tile: second moments scaled, colour partials of a
+// clamped channel (record colour exactly 0) dropped, so that the projection adjoint reads no records.
+__device__ __forceinline__ float flush_value(uint32_t q, float v, const float4& w1, const float4& w2) {
+  const float f = *(q < 3 ? &w2.x + q : &w1.w);  // the channel's colour or the opacity
+  const float scaled = q >= kGQ ? v * (-0.69314718055994531f * f) : v;
+  return (q < 3) & !(f > 0.0f) ? 0.0f : scaled;
+}
 constexpr int kBwdLdsOffsets = 1024;  // segment offsets staged in LDS by the view-major adjoint up to this many
 
 // LDS of one tile.  Up to BATCH - 1 records are staged at a time (the last place is
@@ -348,9 +354,10 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
         if constexpr (DET) {
           const float4 f = s_f[k];
           const int64_t slot = det_slot<TW, TH>(det, s_rec[k], (int)f.x, (int)(f.x + f.z), (int)f.y, txi, tyi);
-          if (slot < det.slots) det.partial[slot * kG + q] = v * q_scale((int)q, s_w1[k].w);
+          if (slot < det.slots) det.partial[slot * kG + q] = flush_value(q, v, s_w1[k], s_w2[k]);
         } else {
-          if (v != 0.0f) unsafeAtomicAdd(&grad2d[(int64_t)s_rec[k] * kG + q], v * q_scale((int)q, s_w1[k].w));
+          v = flush_value(q, v, s_w1[k], s_w2[k]);
+          if (v != 0.0f) unsafeAtomicAdd(&grad2d[(int64_t)s_rec[k] * kG + q], v);
         }
       }
       used = end_used;
@@ -488,24 +495,147 @@ struct BwdArgs {
   int32_t packed;  // gather entries are level << GS_PACKED_INDEX_BITS | index (refined selection)
 };
 
-// Destinations of a record's parameter gradients.
-//
-// AtomicSink adds into the level's gradient arrays with no-return FP32 atomics
-// (records of one Gaussian may run concurrently when views share it; with one
-// view each address receives one add, so the result is the plain sum).  The
-// adds do not wait for memory, so a record's 59 updates are all in flight
-// together, where a read-modify-write chain would wait for each load.
-struct AtomicSink {
-  const gs_gaussian_grads& G;
-  int64_t n, gi;
-  __device__ __forceinline__ void sh(int idx, float v) const {
-    if (v != 0.0f) unsafeAtomicAdd(&G.sh[(int64_t)idx * n + gi], v);
+// What the adjoint needs of a view in FP64 and is the same for every record: camera centre and
+// guard-band limits.  A work-group keeps them in LDS for up to kBwdViews views (15 FP64 operations
+// and two divisions less per record).
+struct ViewConst {
+  double C[3], limx, limy;
+  __device__ __forceinline__ void load(const BwdArgs& a, int v) {
+    const gs_camera& cam = a.cams[v];
+    camera_centre(cam, C);
+    limx = 1.3 * ((0.5 * a.W) / cam.fx);
+    limy = 1.3 * ((0.5 * a.H) / cam.fy);
   }
-  __device__ __forceinline__ void mean(int k, float v) const { unsafeAtomicAdd(&G.means[k * n + gi], v); }
-  __device__ __forceinline__ void scale(int k, float v) const { unsafeAtomicAdd(&G.scales[k * n + gi], v); }
-  __device__ __forceinline__ void quat(int k, float v) const { unsafeAtomicAdd(&G.quats[k * n + gi], v); }
-  __device__ __forceinline__ void opac(float v) const { unsafeAtomicAdd(&G.opac[gi], v); }
 };
+constexpr int kBwdViews = 32;
+
+__device__ __forceinline__ void load_views(const BwdArgs& a, ViewConst (&s_view)[kBwdViews]) {
+  if ((int)threadIdx.x < a.V && threadIdx.x < kBwdViews) s_view[threadIdx.x].load(a, threadIdx.x);
+}
+__device__ __forceinline__ ViewConst view_const(const BwdArgs& a, const ViewConst (&s_view)[kBwdViews], int v) {
+  if (a.V <= kBwdViews) return s_view[v];
+  ViewConst c;
+  c.load(a, v);
+  return c;
+}
+
+// The projection adjoint is bound by its reads and writes of whole parameter planes (1M Gaussians,
+// 117K visible in one view: 640 MB of lines touched in 217 us, 46 us of it VALU time).  So:
+//  * a Gaussian's parameters are loaded together, ahead of all arithmetic, and ahead of the first store
+//    or atomic (vector memory operations are waited for in order: a load behind a store waits for it);
+//  * the compositing kernel drops the colour partials of clamped channels, so no record is read here
+//    (16 views x 2M: 1 GB of record lines less);
+//  * in the Gaussian-major kernel the parameters are read once for all views, and the next view's 2D
+//    gradient is in flight during a view's adjoint.
+// 1M: 217 -> 169 us; 16 shared views x 2M (12.6M visible): 1041 -> 646 us (2.5 GB, 3.9 TB/s);
+// four views of 262K visible with atomics: 290 -> 276 us, bound by the 62M memory-side atomic adds.
+// Packing the visible records of 1024 into full waves first measured no gain (171, 290 us).
+//
+// Parameters of one Gaussian, loaded together (the loads are all in flight at once).
+struct GaussianIn {
+  float m[3], q[4], s[3], f[48];  // f: SH coefficient planes of the bands evaluated (f[0..2] unused)
+  int deg;                        // SH bands evaluated
+  template <bool HALF>
+  __device__ __forceinline__ void load(const LevelPtrs& L, int sh_degree, int64_t gi) {
+    deg = sh_degree < L.sh_deg ? sh_degree : L.sh_deg;
+    const int terms = 3 * (deg + 1) * (deg + 1);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k] = L.means[k * L.n + gi];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = attr<HALF>(L.quats, k * L.n + gi);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s[k] = attr<HALF>(L.scales, k * L.n + gi);
+#pragma unroll
+    for (int i = 3; i < 48; ++i) f[i] = i < terms ? attr<HALF>(L.sh, (int64_t)i * L.n + gi) : 0.0f;
+  }
+};
+
+// Gradient of one record's parameters.  The SH part (dL/df_{k,c} = Y_k g_c) is left as its factors:
+// a destination forms the 48 products as it stores or sums them.
+struct RecordGrad {
+  float dir[3], g[3];  // view direction, colour gradient
+  int deg;             // SH bands evaluated
+  float m[3], s[3], q[4], o;
+};
+
+// SH basis up to degree `deg` at a unit direction: f(k, Y_k, dY_k/dx, dY_k/dy, dY_k/dz) per term
+// (what the callback does not use is never computed).
+template <class F>
+__device__ __forceinline__ void sh_terms(float x, float y, float z, int deg, F f) {
+  const float k1 = (float)kSH1, k2a = (float)kSH2a, k2b = (float)kSH2b, k2c = (float)kSH2c;
+  const float k3a = (float)kSH3a, k3b = (float)kSH3b, k3c = (float)kSH3c, k3d = (float)kSH3d, k3e = (float)kSH3e;
+  f(0, (float)kSH00, 0.f, 0.f, 0.f);
+  if (deg < 1) return;
+  f(1, -k1 * y, 0.f, -k1, 0.f);
+  f(2, k1 * z, 0.f, 0.f, k1);
+  f(3, -k1 * x, -k1, 0.f, 0.f);
+  if (deg < 2) return;
+  const float xx = x * x, yy = y * y, zz = z * z;
+  f(4, k2a * x * y, k2a * y, k2a * x, 0.f);
+  f(5, -k2a * y * z, 0.f, -k2a * z, -k2a * y);
+  f(6, k2b * (2.f * zz - xx - yy), -2.f * k2b * x, -2.f * k2b * y, 4.f * k2b * z);
+  f(7, -k2a * x * z, -k2a * z, 0.f, -k2a * x);
+  f(8, k2c * (xx - yy), 2.f * k2c * x, -2.f * k2c * y, 0.f);
+  if (deg < 3) return;
+  f(9, -k3a * y * (3.f * xx - yy), -6.f * k3a * x * y, -3.f * k3a * (xx - yy), 0.f);
+  f(10, k3b * x * y * z, k3b * y * z, k3b * x * z, k3b * x * y);
+  f(11, -k3c * y * (4.f * zz - xx - yy), 2.f * k3c * x * y, -k3c * (4.f * zz - xx - 3.f * yy), -8.f * k3c * y * z);
+  f(12, k3d * z * (2.f * zz - 3.f * xx - 3.f * yy), -6.f * k3d * x * z, -6.f * k3d * y * z,
+    k3d * (6.f * zz - 3.f * xx - 3.f * yy));
+  f(13, -k3c * x * (4.f * zz - xx - yy), -k3c * (4.f * zz - 3.f * xx - yy), 2.f * k3c * x * y, -8.f * k3c * x * z);
+  f(14, k3e * z * (xx - yy), 2.f * k3e * x * z, -2.f * k3e * y * z, k3e * (xx - yy));
+  f(15, -k3a * x * (xx - 3.f * yy), -3.f * k3a * (xx - yy), 6.f * k3a * x * y, 0.f);
+}
+
+// Destinations.  All of a record's loads come before its first store or atomic
+// (vector memory operations are waited for in order, so a load behind a store
+// waits for it): the SH coefficients were read for the direction gradient already
+// and the products need only the direction.
+//
+// add_atomic: no-return FP32 atomics (records of one Gaussian may run
+// concurrently when views share it).
+__device__ __forceinline__ void add_atomic(const gs_gaussian_grads& G, int64_t n, int64_t gi, const RecordGrad& r) {
+  sh_terms(r.dir[0], r.dir[1], r.dir[2], r.deg, [&](int k, float Y, float, float, float) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) unsafeAtomicAdd(&G.sh[(int64_t)(3 * k + c) * n + gi], Y * r.g[c]);
+  });
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    unsafeAtomicAdd(&G.means[k * n + gi], r.m[k]);
+    unsafeAtomicAdd(&G.scales[k * n + gi], r.s[k]);
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) unsafeAtomicAdd(&G.quats[k * n + gi], r.q[k]);
+  unsafeAtomicAdd(&G.opac[gi], r.o);
+}
+
+// add_plain: the only record of its Gaussian in the launch (one view).
+__device__ __forceinline__ void add_plain(const gs_gaussian_grads& G, int64_t n, int64_t gi, const RecordGrad& r) {
+  float cm[3], cs[3], cq[4], csh[48];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    cm[k] = G.means[k * n + gi];
+    cs[k] = G.scales[k * n + gi];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) cq[k] = G.quats[k * n + gi];
+  const float co = G.opac[gi];
+  const int terms = 3 * (r.deg + 1) * (r.deg + 1);
+#pragma unroll
+  for (int i = 0; i < 48; ++i) csh[i] = i < terms ? G.sh[(int64_t)i * n + gi] : 0.0f;
+#pragma unroll
+  for (int k = 0; k < 3; ++k) {
+    G.means[k * n + gi] = cm[k] + r.m[k];
+    G.scales[k * n + gi] = cs[k] + r.s[k];
+  }
+#pragma unroll
+  for (int k = 0; k < 4; ++k) G.quats[k * n + gi] = cq[k] + r.q[k];
+  G.opac[gi] = co + r.o;
+  sh_terms(r.dir[0], r.dir[1], r.dir[2], r.deg, [&](int k, float Y, float, float, float) {
+#pragma unroll
+    for (int c = 0; c < 3; ++c) G.sh[(int64_t)(3 * k + c) * n + gi] = csh[3 * k + c] + Y * r.g[c];
+  });
+}
 
 // RegisterSink sums the gradients of all records of one Gaussian (a thread
 // that owns them, views in order) and adds the totals to memory once.
@@ -520,11 +650,17 @@ struct RegisterSink {
     for (int i = 0; i < 4; ++i) q[i] = 0.0f;
     o = 0.0f;
   }
-  __device__ __forceinline__ void sh(int idx, float v) { shv[idx] += v; }
-  __device__ __forceinline__ void mean(int k, float v) { m[k] += v; }
-  __device__ __forceinline__ void scale(int k, float v) { s[k] += v; }
-  __device__ __forceinline__ void quat(int k, float v) { q[k] += v; }
-  __device__ __forceinline__ void opac(float v) { o += v; }
+  __device__ __forceinline__ void sh(int i, float v) { shv[i] += v; }
+  __device__ __forceinline__ void add(const RecordGrad& r) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      m[k] += r.m[k];
+      s[k] += r.s[k];
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] += r.q[k];
+    o += r.o;
+  }
   // planes: coefficient planes stored per colour channel ((sh_degree + 1)^2).
   // Every current value is loaded before the first store, so the loads are in
   // flight together (in a += chain each load would wait for the previous store).
@@ -554,47 +690,10 @@ struct RegisterSink {
   }
 };
 
-// Adjoint of the SH colour, FP32, one basis term at a time (no basis arrays
-// live): dL/df_{k,c} = Y_k g_c and dL/d(direction) += (sum_c g_c f_{k,c}) grad Y_k.
-template <bool HALF, class Sink>
-__device__ __forceinline__ void sh_adjoint(float x, float y, float z, int deg, const void* __restrict__ sh, int64_t n,
-                                           int64_t gi, const float g[3], Sink& sink, float gdir[3]) {
-  auto term = [&](int k, float Y, float dx, float dy, float dz) {
-    const float f0 = attr<HALF>(sh, (int64_t)(3 * k + 0) * n + gi);
-    const float f1 = attr<HALF>(sh, (int64_t)(3 * k + 1) * n + gi);
-    const float f2 = attr<HALF>(sh, (int64_t)(3 * k + 2) * n + gi);
-    const float w = fmaf(g[0], f0, fmaf(g[1], f1, g[2] * f2));
-    gdir[0] = fmaf(w, dx, gdir[0]);
-    gdir[1] = fmaf(w, dy, gdir[1]);
-    gdir[2] = fmaf(w, dz, gdir[2]);
-    sink.sh(3 * k + 0, Y * g[0]);
-    sink.sh(3 * k + 1, Y * g[1]);
-    sink.sh(3 * k + 2, Y * g[2]);
-  };
-  const float k1 = (float)kSH1, k2a = (float)kSH2a, k2b = (float)kSH2b, k2c = (float)kSH2c;
-  const float k3a = (float)kSH3a, k3b = (float)kSH3b, k3c = (float)kSH3c, k3d = (float)kSH3d, k3e = (float)kSH3e;
-  term(0, (float)kSH00, 0.f, 0.f, 0.f);
-  if (deg < 1) return;
-  term(1, -k1 * y, 0.f, -k1, 0.f);
-  term(2, k1 * z, 0.f, 0.f, k1);
-  term(3, -k1 * x, -k1, 0.f, 0.f);
-  if (deg < 2) return;
-  const float xx = x * x, yy = y * y, zz = z * z;
-  term(4, k2a * x * y, k2a * y, k2a * x, 0.f);
-  term(5, -k2a * y * z, 0.f, -k2a * z, -k2a * y);
-  term(6, k2b * (2.f * zz - xx - yy), -2.f * k2b * x, -2.f * k2b * y, 4.f * k2b * z);
-  term(7, -k2a * x * z, -k2a * z, 0.f, -k2a * x);
-  term(8, k2c * (xx - yy), 2.f * k2c * x, -2.f * k2c * y, 0.f);
-  if (deg < 3) return;
-  term(9, -k3a * y * (3.f * xx - yy), -6.f * k3a * x * y, -3.f * k3a * (xx - yy), 0.f);
-  term(10, k3b * x * y * z, k3b * y * z, k3b * x * z, k3b * x * y);
-  term(11, -k3c * y * (4.f * zz - xx - yy), 2.f * k3c * x * y, -k3c * (4.f * zz - xx - 3.f * yy), -8.f * k3c * y * z);
-  term(12, k3d * z * (2.f * zz - 3.f * xx - 3.f * yy), -6.f * k3d * x * z, -6.f * k3d * y * z,
-       k3d * (6.f * zz - 3.f * xx - 3.f * yy));
-  term(13, -k3c * x * (4.f * zz - xx - yy), -k3c * (4.f * zz - 3.f * xx - yy), 2.f * k3c * x * y, -8.f * k3c * x * z);
-  term(14, k3e * z * (xx - yy), 2.f * k3e * x * z, -2.f * k3e * y * z, k3e * (xx - yy));
-  term(15, -k3a * x * (xx - 3.f * yy), -3.f * k3a * (xx - yy), 6.f * k3a * x * y, 0.f);
-}
+// For destinations that form the SH products themselves (from RecordGrad)
+struct NoSh {
+  __device__ __forceinline__ void sh(int, float) {}
+};
 
 // Record g's 2D gradient (colour, opacity, conic and mean partials); false if
 // it is all zero (a culled record, or one no pixel's loss depends on).
@@ -609,42 +708,49 @@ __device__ __forceinline__ bool load_grad2d(const float* __restrict__ grad2d, in
 }
 
 // One record's adjoint, for a record whose 2D gradient p2 is not all zero.
-template <bool HALF, class Sink>
-__device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const Record* __restrict__ records,
-                                                        const float (&p2)[kG], int64_t g, int v, int l, int64_t gi,
+template <class Sink>
+__device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const GaussianIn& in, const float (&p2)[kG],
+                                                        int v, const ViewConst& vc, RecordGrad& out,
                                                         Sink& sink) {
-  const LevelPtrs& L = a.lv[l];
-  const int64_t n = L.n;
   const gs_camera& cam = a.cams[v];
   // A record with a non-zero 2D gradient was visible in the forward pass, so
   // the projection below (same code, same inputs) takes the same decisions.
-  // ---- colour first (FP32): clamped channels (record colour exactly 0) pass no gradient
+  // ---- colour first (FP32; clamped channels come with no gradient)
   double dm_col[3];
   {
-    const float4 w2 = reinterpret_cast<const float4*>(&records[g])[2];
-    const float grgb[3] = {w2.x > 0.0f ? p2[0] : 0.0f, w2.y > 0.0f ? p2[1] : 0.0f, w2.z > 0.0f ? p2[2] : 0.0f};
-    double C[3];
-    camera_centre(cam, C);
-    const double d0 = (double)L.means[gi] - C[0], d1 = (double)L.means[n + gi] - C[1],
-                 d2 = (double)L.means[2 * n + gi] - C[2];
-    const double dn = sqrt((d0 * d0 + d1 * d1) + d2 * d2);
-    const float dir[3] = {(float)(d0 / dn), (float)(d1 / dn), (float)(d2 / dn)};
+    const double d0 = (double)in.m[0] - vc.C[0], d1 = (double)in.m[1] - vc.C[1], d2 = (double)in.m[2] - vc.C[2];
+    const double rdn = 1.0 / sqrt((d0 * d0 + d1 * d1) + d2 * d2);
+    const float dir[3] = {(float)(d0 * rdn), (float)(d1 * rdn), (float)(d2 * rdn)};
+    const float g[3] = {p2[0], p2[1], p2[2]};
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+      out.dir[k] = dir[k];
+      out.g[k] = g[k];
+    }
+    out.deg = in.deg;
     float gdir[3] = {0.0f, 0.0f, 0.0f};
-    sh_adjoint<HALF>(dir[0], dir[1], dir[2], a.sh_degree < L.sh_deg ? a.sh_degree : L.sh_deg, L.sh, n, gi, grgb, sink,
-                     gdir);
+    sh_terms(dir[0], dir[1], dir[2], in.deg, [&](int k, float Y, float dx, float dy, float dz) {
+      if (k > 0) {  // (the constant term has no derivative)
+        const float w = fmaf(g[0], in.f[3 * k], fmaf(g[1], in.f[3 * k + 1], g[2] * in.f[3 * k + 2]));
+        gdir[0] = fmaf(w, dx, gdir[0]);
+        gdir[1] = fmaf(w, dy, gdir[1]);
+        gdir[2] = fmaf(w, dz, gdir[2]);
+      }
+#pragma unroll
+      for (int c = 0; c < 3; ++c) sink.sh(3 * k + c, Y * g[c]);
+    });
     const float gd = gdir[0] * dir[0] + gdir[1] * dir[1] + gdir[2] * dir[2];
-    for (int k = 0; k < 3; ++k) dm_col[k] = (double)(gdir[k] - dir[k] * gd) / dn;
+    for (int k = 0; k < 3; ++k) dm_col[k] = (double)(gdir[k] - dir[k] * gd) * rdn;
   }
   // ---- geometry adjoint (FP32); the guard-band clamp is decided in FP64 exactly as in the forward pass
   const double* R64 = cam.R;
-  const double m0 = L.means[gi], m1 = L.means[n + gi], m2 = L.means[2 * n + gi];
+  const double m0 = in.m[0], m1 = in.m[1], m2 = in.m[2];
   const double tx64 = ((R64[0] * m0 + R64[1] * m1) + R64[2] * m2) + cam.t[0];
   const double ty64 = ((R64[3] * m0 + R64[4] * m1) + R64[5] * m2) + cam.t[1];
   const double tz64 = ((R64[6] * m0 + R64[7] * m1) + R64[8] * m2) + cam.t[2];
   const double rz64 = 1.0 / tz64;
   const double ux64 = tx64 * rz64, uy64 = ty64 * rz64;
-  const double limx = 1.3 * ((0.5 * a.W) / cam.fx), limy = 1.3 * ((0.5 * a.H) / cam.fy);
-  const double uxc64 = dmin_(limx, dmax_(-limx, ux64)), uyc64 = dmin_(limy, dmax_(-limy, uy64));
+  const double uxc64 = dmin_(vc.limx, dmax_(-vc.limx, ux64)), uyc64 = dmin_(vc.limy, dmax_(-vc.limy, uy64));
   const bool clamp_x = uxc64 != ux64, clamp_y = uyc64 != uy64;
   const float tx = (float)tx64, ty = (float)ty64, rz = (float)rz64;
   const float uxc = (float)uxc64, uyc = (float)uyc64;
@@ -653,8 +759,7 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
 #pragma unroll
   for (int k = 0; k < 9; ++k) Rc[k] = (float)R64[k];
   // rotation of the normalised quaternion, scales
-  const float qa = attr<HALF>(L.quats, gi), qb = attr<HALF>(L.quats, n + gi), qc = attr<HALF>(L.quats, 2 * n + gi),
-              qd_ = attr<HALF>(L.quats, 3 * n + gi);
+  const float qa = in.q[0], qb = in.q[1], qc = in.q[2], qd_ = in.q[3];
   const float qinv = 1.0f / sqrtf(qa * qa + qb * qb + qc * qc + qd_ * qd_);
   const float w = qa * qinv, x = qb * qinv, y = qc * qinv, z = qd_ * qinv;
   float Rq[3][3];
@@ -667,7 +772,7 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
   Rq[2][0] = 2.f * (x * z - w * y);
   Rq[2][1] = 2.f * (y * z + w * x);
   Rq[2][2] = 1.f - 2.f * (x * x + y * y);
-  const float sc[3] = {attr<HALF>(L.scales, gi), attr<HALF>(L.scales, n + gi), attr<HALF>(L.scales, 2 * n + gi)};
+  const float sc[3] = {in.s[0], in.s[1], in.s[2]};
   float WL[3][3];
 #pragma unroll
   for (int i = 0; i < 3; ++i)
@@ -690,20 +795,21 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
   const float cr2 = M[0][0] * M[1][1] - M[0][1] * M[1][0];
   const float det = cr0 * cr0 + cr1 * cr1 + cr2 * cr2 + 0.3f * (n0 + n1) + 0.09f;
   // ---- 2D mean and conic partials ----
-  const float kS = (float)kConicScale, kS2 = (float)kConicScale2;
-  const float ca = kS * sqrtf(sc2 / det);
-  const float cb = -kS * sb / sqrtf(sc2 * det);
-  const float cc = kS / sqrtf(sc2);
-  const float gu = -2.0f * ca * p2[4];
-  const float gv = -2.0f * (cb * p2[4] + cc * p2[5]);
-  // conic K = Sigma2D^-1 = F^T F / kS2, F = [[ca, cb], [0, cc]]:
-  // dL/dSigma = -K (kS2 sum w d d^T) K = -F^T P F / kS2 with P the second moments of p = F d
+  // F = kS F0 = kS [[ca, cb], [0, cc]]
+  const float kS = (float)kConicScale;
+  const float ca = sqrtf(sc2 / det);
+  const float cb = -sb / sqrtf(sc2 * det);
+  const float cc = 1.0f / sqrtf(sc2);
+  const float gu = -2.0f * kS * (ca * p2[4]);
+  const float gv = -2.0f * kS * (cb * p2[4] + cc * p2[5]);
+  // conic K = Sigma2D^-1 = F0^T F0: dL/dSigma = -K (kS^2 sum w d d^T) K = -F0^T P F0
+  // with P the second moments of p = F d
   const float P11 = p2[6], P12 = p2[7], P22 = p2[8];
   const float h2 = fmaf(cb, P11, cc * P12);
   const float h3 = fmaf(cb, P12, cc * P22);
-  const float S00 = -ca * ca * P11 / kS2;
-  const float S01 = -ca * h2 / kS2;
-  const float S11 = -fmaf(cb, h2, cc * h3) / kS2;
+  const float S00 = -ca * ca * P11;
+  const float S01 = -ca * h2;
+  const float S11 = -fmaf(cb, h2, cc * h3);
   // Sigma2D = M M^T + 0.3 I -> dL/dM = 2 Gs M; M = J WL; WL = R_cam Rq diag(s), one column at a time
   float dJ00 = 0.f, dJ02 = 0.f, dJ11 = 0.f, dJ12 = 0.f;
   float ds[3], dRq[3][3];
@@ -735,9 +841,8 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
           4.f * z * (dRq[0][0] + dRq[1][1]);
   const float qdot = w * dq[0] + x * dq[1] + y * dq[2] + z * dq[3];
   const float qn[4] = {w, x, y, z};
-  float gq[4];
 #pragma unroll
-  for (int k = 0; k < 4; ++k) gq[k] = (dq[k] - qn[k] * qdot) * qinv;
+  for (int k = 0; k < 4; ++k) out.q[k] = (dq[k] - qn[k] * qdot) * qinv;
   // J(t) and (u, v)(t)
   const float rz2 = rz * rz;
   float dt0 = gu * fx * rz, dt1 = gv * fy * rz;
@@ -754,49 +859,45 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
   } else {
     dt2 += dJ12 * fy * uyc * rz2;
   }
-  float dm[3];
-#pragma unroll
-  for (int k = 0; k < 3; ++k) dm[k] = Rc[k] * dt0 + Rc[3 + k] * dt1 + Rc[6 + k] * dt2 + (float)dm_col[k];
 #pragma unroll
   for (int k = 0; k < 3; ++k) {
-    sink.mean(k, dm[k]);
-    sink.scale(k, ds[k]);
+    out.m[k] = Rc[k] * dt0 + Rc[3 + k] * dt1 + Rc[6 + k] * dt2 + (float)dm_col[k];
+    out.s[k] = ds[k];
   }
-#pragma unroll
-  for (int k = 0; k < 4; ++k) sink.quat(k, gq[k]);
-  sink.opac(p2[3]);
-}
-
-template <bool SINGLE>
-__device__ __forceinline__ void preprocess_bwd_record(const BwdArgs& a, const Record* __restrict__ records,
-                                                      const float (&p2)[kG], int64_t g, int v, int l, int64_t gi) {
-  if constexpr (SINGLE) {
-    RegisterSink acc;
-    if (a.lv[l].half) preprocess_bwd_record_t<true>(a, records, p2, g, v, l, gi, acc);
-    else preprocess_bwd_record_t<false>(a, records, p2, g, v, l, gi, acc);
-    acc.flush(a.gr[l], a.lv[l].n, gi, (a.lv[l].sh_deg + 1) * (a.lv[l].sh_deg + 1));
-  } else {
-    AtomicSink sink{a.gr[l], a.lv[l].n, gi};
-    if (a.lv[l].half) preprocess_bwd_record_t<true>(a, records, p2, g, v, l, gi, sink);
-    else preprocess_bwd_record_t<false>(a, records, p2, g, v, l, gi, sink);
-  }
+  out.o = p2[3];
 }
 
 // All records of Gaussian gi (index i in every view's selection), views in
-// order, summed in registers and added to memory once.
+// order, summed in registers and added to memory once.  The Gaussian's
+// parameters are read once; the next view's 2D gradient is in flight while a
+// view's adjoint is computed.
 template <bool HALF>
-__device__ __forceinline__ void preprocess_bwd_gaussian(const BwdArgs& a, const Record* __restrict__ records,
-                                                        const float* __restrict__ grad2d, int64_t n_rec,
-                                                        int64_t n_view, int64_t i, int l, int64_t gi) {
+__device__ __forceinline__ void preprocess_bwd_gaussian(const BwdArgs& a, const float* __restrict__ grad2d,
+                                                        int64_t n_rec, int64_t n_view, int64_t i, int l, int64_t gi,
+                                                        const ViewConst (&s_view)[kBwdViews]) {
+  if (i >= n_rec) return;
+  float p2[kG];
+  bool hit = load_grad2d(grad2d, i, p2);
+  GaussianIn in;
+  in.load<HALF>(a.lv[l], a.sh_degree, gi);
   RegisterSink acc;
   bool any = false;
-  for (int v = 0; v < a.V; ++v) {
-    const int64_t g = (int64_t)v * n_view + i;
+  int64_t g = i;
+  for (int v = 0; v < a.V; ++v, g += n_view) {
     if (g >= n_rec) break;
-    float p2[kG];
-    if (!load_grad2d(grad2d, g, p2)) continue;
-    preprocess_bwd_record_t<HALF>(a, records, p2, g, v, l, gi, acc);
-    any = true;
+    float next[kG] = {};
+    const bool more = v + 1 < a.V && g + n_view < n_rec;
+    bool next_hit = false;
+    if (more) next_hit = load_grad2d(grad2d, g + n_view, next);
+    if (hit) {
+      RecordGrad r;
+      preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, acc);
+      acc.add(r);
+      any = true;
+    }
+    hit = next_hit;
+#pragma unroll
+    for (int q = 0; q < kG; ++q) p2[q] = next[q];
   }
   if (any) acc.flush(a.gr[l], a.lv[l].n, gi, (a.lv[l].sh_deg + 1) * (a.lv[l].sh_deg + 1));
 }
@@ -805,8 +906,7 @@ __device__ __forceinline__ void preprocess_bwd_gaussian(const BwdArgs& a, const 
 // (SINGLE: one view, each Gaussian has at most one record: register sums
 // flushed with all loads ahead of the stores).
 template <bool SINGLE>
-__global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const Record* __restrict__ records,
-                                                             const float* __restrict__ grad2d,
+__global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const float* __restrict__ grad2d,
                                                              const int64_t* __restrict__ counts) {
   int64_t n_rec = counts[GS_COUNT_RECORDS];
   if (n_rec > a.capacity) n_rec = a.capacity;
@@ -814,6 +914,8 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const Re
   // segment offsets staged in LDS when they fit; a record is looked up only
   // once its 2D gradient is known to be non-zero (most selected records were culled)
   __shared__ int64_t s_off[kBwdLdsOffsets];
+  __shared__ ViewConst s_view[kBwdViews];
+  load_views(a, s_view);
   const bool lds_off = nseg < kBwdLdsOffsets;
   if (lds_off)
     for (int k = threadIdx.x; k <= nseg; k += blockDim.x) s_off[k] = a.offsets[k];
@@ -821,41 +923,50 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const Re
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t g = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; g < n_rec; g += stride) {
     float p2[kG];
+    const uint32_t entry = a.gather ? a.gather[g] : 0u;  // (in flight with the gradient)
     if (!load_grad2d(grad2d, g, p2)) continue;
     const int p = lds_off ? find_segment(s_off, nseg, g) : find_segment(a.offsets, nseg, g);
     const int v = p / a.segs, b = p - v * a.segs;
     int l;
     int64_t gi;
     if (a.packed) {  // refined selection: the entry names the level and the index
-      const uint32_t e = a.gather[g];
-      l = (int)(e >> GS_PACKED_INDEX_BITS);
-      gi = (int64_t)(e & ((1u << GS_PACKED_INDEX_BITS) - 1u));
+      l = (int)(entry >> GS_PACKED_INDEX_BITS);
+      gi = (int64_t)(entry & ((1u << GS_PACKED_INDEX_BITS) - 1u));
       if (l >= a.L || gi >= a.lv[l].n) continue;  // not a stored Gaussian (the forward culled it)
     } else {
       l = a.gather ? b : a.level[p];
       const int64_t seg0 = lds_off ? s_off[p] : a.offsets[p];
-      gi = a.gather ? (int64_t)a.gather[g] : a.lvl_off[(int64_t)b * a.L + l] + (g - seg0);
+      gi = a.gather ? (int64_t)entry : a.lvl_off[(int64_t)b * a.L + l] + (g - seg0);
     }
-    preprocess_bwd_record<SINGLE>(a, records, p2, g, v, l, gi);
+    GaussianIn in;
+    if (a.lv[l].half) in.load<true>(a.lv[l], a.sh_degree, gi);
+    else in.load<false>(a.lv[l], a.sh_degree, gi);
+    RecordGrad r;
+    NoSh none;
+    preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, none);
+    if constexpr (SINGLE) add_plain(a.gr[l], a.lv[l].n, gi, r);
+    else add_atomic(a.gr[l], a.lv[l].n, gi, r);
   }
 }
 
 // Gaussian-major (every view selected the same records): one thread owns a
 // Gaussian's records in all views and sums its gradient in registers.
-__global__ void __launch_bounds__(256) preprocess_bwd_shared_kernel(BwdArgs a, const Record* __restrict__ records,
-                                                                    const float* __restrict__ grad2d,
+__global__ void __launch_bounds__(256) preprocess_bwd_shared_kernel(BwdArgs a, const float* __restrict__ grad2d,
                                                                     const int64_t* __restrict__ counts) {
   if (counts[GS_COUNT_FLAGS] & GS_FLAG_SELECTION) return;  // the forward projected nothing
   int64_t n_rec = counts[GS_COUNT_RECORDS];
   if (n_rec > a.capacity) n_rec = a.capacity;
+  __shared__ ViewConst s_view[kBwdViews];
+  load_views(a, s_view);
+  __syncthreads();
   const int64_t n_view = a.offsets[a.segs];
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t i = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; i < n_view; i += stride) {
     const int b = find_segment(a.offsets, a.segs, i);
     const int l = a.gather ? b : a.level[b];
     const int64_t gi = a.gather ? (int64_t)a.gather[i] : a.lvl_off[(int64_t)b * a.L + l] + (i - a.offsets[b]);
-    if (a.lv[l].half) preprocess_bwd_gaussian<true>(a, records, grad2d, n_rec, n_view, i, l, gi);
-    else preprocess_bwd_gaussian<false>(a, records, grad2d, n_rec, n_view, i, l, gi);
+    if (a.lv[l].half) preprocess_bwd_gaussian<true>(a, grad2d, n_rec, n_view, i, l, gi, s_view);
+    else preprocess_bwd_gaussian<false>(a, grad2d, n_rec, n_view, i, l, gi, s_view);
   }
 }
 
@@ -863,12 +974,14 @@ __global__ void __launch_bounds__(256) preprocess_bwd_shared_kernel(BwdArgs a, c
 // levels (block-wise): one thread per stored Gaussian of every level sums its
 // records over the views in view order (record of view v: the view chose the
 // Gaussian's block at the Gaussian's level) and adds the total once.
-__global__ void __launch_bounds__(256) preprocess_bwd_det_kernel(BwdArgs a, const Record* __restrict__ records,
-                                                                 const float* __restrict__ grad2d,
+__global__ void __launch_bounds__(256) preprocess_bwd_det_kernel(BwdArgs a, const float* __restrict__ grad2d,
                                                                  const int64_t* __restrict__ counts,
                                                                  int64_t n_stored) {
   int64_t n_rec = counts[GS_COUNT_RECORDS];
   if (n_rec > a.capacity) n_rec = a.capacity;
+  __shared__ ViewConst s_view[kBwdViews];
+  load_views(a, s_view);
+  __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_stored; t += stride) {
     int l = 0;
@@ -894,8 +1007,12 @@ __global__ void __launch_bounds__(256) preprocess_bwd_det_kernel(BwdArgs a, cons
       if (g >= n_rec) continue;
       float p2[kG];
       if (!load_grad2d(grad2d, g, p2)) continue;
-      if (a.lv[l].half) preprocess_bwd_record_t<true>(a, records, p2, g, v, l, gi, acc);
-      else preprocess_bwd_record_t<false>(a, records, p2, g, v, l, gi, acc);
+      GaussianIn in;
+      if (a.lv[l].half) in.load<true>(a.lv[l], a.sh_degree, gi);
+      else in.load<false>(a.lv[l], a.sh_degree, gi);
+      RecordGrad r;
+      preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, acc);
+      acc.add(r);
       any = true;
     }
     if (any) acc.flush(a.gr[l], a.lv[l].n, gi, (a.lv[l].sh_deg + 1) * (a.lv[l].sh_deg + 1));
@@ -1073,18 +1190,18 @@ extern "C" gs_status gs_rasterize_bwd(const void* records, const uint32_t* pair_
     if (gather) return GS_ERR_UNSUPPORTED;
     int64_t pv = (record_capacity / n_views + 255) / 256;
     const dim3 gs_grid((unsigned)(pv < 8192 ? (pv < 1 ? 1 : pv) : 8192));
-    hipLaunchKernelGGL(preprocess_bwd_shared_kernel, gs_grid, dim3(256), 0, s, a, rec, grad2d, counts);
+    hipLaunchKernelGGL(preprocess_bwd_shared_kernel, gs_grid, dim3(256), 0, s, a, grad2d, counts);
   } else if (n_views == 1) {
-    hipLaunchKernelGGL(preprocess_bwd_kernel<true>, gbg, dim3(256), 0, s, a, rec, grad2d, counts);
+    hipLaunchKernelGGL(preprocess_bwd_kernel<true>, gbg, dim3(256), 0, s, a, grad2d, counts);
   } else if (det) {
     if (!blocks->lvl_cnt) return GS_ERR_INVALID_ARG;
     int64_t n_stored = 0;
     for (int l = 0; l < blocks->n_levels; ++l) n_stored += levels[l].n;
     int64_t sb = (n_stored + 255) / 256;
     const dim3 sg((unsigned)(sb < 8192 ? (sb < 1 ? 1 : sb) : 8192));
-    hipLaunchKernelGGL(preprocess_bwd_det_kernel, sg, dim3(256), 0, s, a, rec, grad2d, counts, n_stored);
+    hipLaunchKernelGGL(preprocess_bwd_det_kernel, sg, dim3(256), 0, s, a, grad2d, counts, n_stored);
   } else {
-    hipLaunchKernelGGL(preprocess_bwd_kernel<false>, gbg, dim3(256), 0, s, a, rec, grad2d, counts);
+    hipLaunchKernelGGL(preprocess_bwd_kernel<false>, gbg, dim3(256), 0, s, a, grad2d, counts);
   }
   GS_LAUNCH_CHECK();
   return GS_OK;
