@@ -61,13 +61,13 @@ constexpr double kSH3d = 0.3731763325901154;
 constexpr double kSH3e = 1.445305721320277;
 
 // Colour sum_k Y_k f_k (per channel, k ascending) with the basis terms of
-// sh_basis computed one at a time, so no basis array is live.
-template <bool HALF>
-__device__ __forceinline__ void sh_colour(double x, double y, double z, int deg, const void* __restrict__ sh,
-                                          int64_t n, int64_t gi, double col[3]) {
+// sh_basis computed one at a time, so no basis array is live.  coef(i):
+// coefficient plane i of the bands up to deg.
+template <class Coef>
+__device__ __forceinline__ void sh_colour(double x, double y, double z, int deg, Coef coef, double col[3]) {
   auto term = [&](int k, double Yk) {
 #pragma unroll
-    for (int ch = 0; ch < 3; ++ch) col[ch] += Yk * (double)attr<HALF>(sh, (int64_t)(3 * k + ch) * n + gi);
+    for (int ch = 0; ch < 3; ++ch) col[ch] += Yk * (double)coef(3 * k + ch);
   };
   term(0, kSH00);
   if (deg < 1) return;
@@ -91,33 +91,144 @@ __device__ __forceinline__ void sh_colour(double x, double y, double z, int deg,
   term(15, -kSH3a * (x * (xx - 3.0 * yy)));
 }
 
-// Everything the forward projection computes for one Gaussian.
-struct Geo {
-  double m[3];         // centre
-  double tx, ty, tz;   // camera-space centre
-  double rz, ux, uy;   // 1/tz, tx/tz, ty/tz
-  bool clamp_x, clamp_y;
-  double uxc, uyc;     // guard-band clamped tan values
-  double q[4];         // normalised quaternion (w, x, y, z)
-  double qinv;         // 1 / |q|
-  double s[3];
-  double Rq[3][3];
-  double Lm[3][3];     // Rq diag(s)
-  double WL[3][3];     // R_cam Lm
-  double J00, J02, J11, J12;
-  double M[2][3];      // J WL
-  double n0, n1, a, b, c, det;
-  double u, v;
-  float depth;
-  int i0, i1, j0, j1;
-  double opac;
+// Coefficient planes FIRST.. of the bands up to deg, 0 beyond
+template <bool HALF, int FIRST = 0>
+__device__ __forceinline__ void load_sh(const LevelPtrs& L, int64_t gi, int deg, float (&f)[48]) {
+  auto load = [&](int i) { f[i] = attr<HALF>(L.sh, (int64_t)i * L.n + gi); };
+#pragma unroll
+  for (int i = FIRST; i < 48; ++i) f[i] = 0.0f;
+#pragma unroll
+  for (int i = FIRST; i < 3; ++i) load(i);
+  if (deg >= 1) {
+#pragma unroll
+    for (int i = 3; i < 12; ++i) load(i);
+  }
+  if (deg >= 2) {
+#pragma unroll
+    for (int i = 12; i < 27; ++i) load(i);
+  }
+  if (deg >= 3) {
+#pragma unroll
+    for (int i = 27; i < 48; ++i) load(i);
+  }
+}
+
+// Camera centre C = -R^T t.
+__device__ __forceinline__ void camera_centre(const gs_camera& cam, double C[3]) {
+  const double* R = cam.R;
+  C[0] = -((R[0] * cam.t[0] + R[3] * cam.t[1]) + R[6] * cam.t[2]);
+  C[1] = -((R[1] * cam.t[0] + R[4] * cam.t[1]) + R[7] * cam.t[2]);
+  C[2] = -((R[2] * cam.t[0] + R[5] * cam.t[1]) + R[8] * cam.t[2]);
+}
+
+// Camera v, the same v in the whole wave, through the scalar cache: it then takes no vector registers
+// (the cameras are read-only for the kernel, which is what the constant address space says).
+__device__ __forceinline__ gs_camera uniform_camera(const gs_camera* cams, int v) {
+  const auto* p = (const __attribute__((address_space(4))) gs_camera*)cams + v;
+  gs_camera c;
+#pragma unroll
+  for (int k = 0; k < 9; ++k) c.R[k] = p->R[k];
+#pragma unroll
+  for (int k = 0; k < 3; ++k) c.t[k] = p->t[k];
+  c.fx = p->fx;
+  c.fy = p->fy;
+  c.cx = p->cx;
+  c.cy = p->cy;
+  c.znear = p->znear;
+  return c;
+}
+
+// f(key) with the key in a scalar register, once for each key among the wave's active lanes (with
+// the lanes that have it active).  Used for view and level, which almost always are one for the whole
+// wave: the camera and the level's pointers are then scalar.  The loop's condition is the wave's, not a
+// lane's: lanes that left the loop one by one would run f after it, all together, with one lane's key.
+template <class F>
+__device__ __forceinline__ void for_each_key(int key, F f) {
+  for (uint64_t left = __ballot(1); left;) {
+    const int u = __builtin_amdgcn_readlane(key, __builtin_ctzll(left));
+    const bool mine = key == u;
+    if (mine) f(__builtin_amdgcn_readfirstlane(key));
+    left &= ~__ballot(mine);
+  }
+}
+
+// What the projection needs of a view in FP64 and is the same for every record.  A work-group keeps
+// them in LDS for up to kLdsViews views (15 FP64 operations and two divisions less per record).
+struct ViewConst {
+  double C[3], limx, limy;  // camera centre; guard-band limits of x/z and y/z
+  __device__ __forceinline__ void load(const gs_camera& cam, int W, int H) {
+    camera_centre(cam, C);
+    limx = 1.3 * ((0.5 * W) / cam.fx);
+    limy = 1.3 * ((0.5 * H) / cam.fy);
+  }
+};
+constexpr int kLdsViews = 32;
+
+__device__ __forceinline__ void load_views(const gs_camera* cams, int V, int W, int H, ViewConst (&s_view)[kLdsViews]) {
+  if ((int)threadIdx.x < V && threadIdx.x < kLdsViews) s_view[threadIdx.x].load(cams[threadIdx.x], W, H);
+}
+__device__ __forceinline__ ViewConst view_const(const gs_camera* cams, int V, int W, int H,
+                                                const ViewConst (&s_view)[kLdsViews], int v) {
+  if (V <= kLdsViews) return s_view[v];
+  ViewConst c;
+  c.load(cams[v], W, H);
+  return c;
+}
+
+// Stored geometry of one Gaussian, and the part of the projection that no view enters.
+struct Shape {
+  float m[3], s[3], q[4], op;
+  double Lm[3][3];  // Rq diag(s)
+  template <bool HALF>
+  __device__ __forceinline__ void load(const LevelPtrs& L, int64_t gi) {
+#pragma unroll
+    for (int k = 0; k < 3; ++k) m[k] = L.means[k * L.n + gi];
+    op = attr<HALF>(L.opac, gi);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) s[k] = attr<HALF>(L.scales, k * L.n + gi);
+  }
+  template <bool HALF>
+  __device__ __forceinline__ void load_rotation(const LevelPtrs& L, int64_t gi) {
+#pragma unroll
+    for (int k = 0; k < 4; ++k) q[k] = attr<HALF>(L.quats, k * L.n + gi);
+  }
+  // false: no rotation (zero, non-finite or overflowing quaternion), the Gaussian is culled
+  __device__ __forceinline__ bool rotate() {
+    const double q0 = q[0], q1 = q[1], q2 = q[2], q3 = q[3];
+    const double qn2 = ((q0 * q0 + q1 * q1) + q2 * q2) + q3 * q3;
+    if (!(qn2 > 0.0 && qn2 <= 1.0e300)) return false;
+    const double qinv = 1.0 / sqrt(qn2);
+    const double w = q0 * qinv, x = q1 * qinv, y = q2 * qinv, z = q3 * qinv;
+    double Rq[3][3];
+    Rq[0][0] = 1.0 - 2.0 * (y * y + z * z);
+    Rq[0][1] = 2.0 * (x * y - w * z);
+    Rq[0][2] = 2.0 * (x * z + w * y);
+    Rq[1][0] = 2.0 * (x * y + w * z);
+    Rq[1][1] = 1.0 - 2.0 * (x * x + z * z);
+    Rq[1][2] = 2.0 * (y * z - w * x);
+    Rq[2][0] = 2.0 * (x * z - w * y);
+    Rq[2][1] = 2.0 * (y * z + w * x);
+    Rq[2][2] = 1.0 - 2.0 * (x * x + y * y);
+#pragma unroll
+    for (int i = 0; i < 3; ++i)
+#pragma unroll
+      for (int j = 0; j < 3; ++j) Lm[i][j] = Rq[i][j] * (double)s[j];
+    return true;
+  }
 };
 
-// Decides culling and the footprint; returns false if culled.  Two rounds of
-// loads: centre, scale and opacity first (28 B), which decide most culls — the
-// near plane, the opacity threshold, and a footprint that certainly misses the
-// image (below) — and the rotation (16 B) only for the Gaussians left; the SH
-// coefficients are read later, by the caller, only for survivors.
+// What the forward projection hands on for one Gaussian in one view.
+struct Geo {
+  double rz, ux, uy;  // 1/tz, tx/tz, ty/tz in camera space
+  double u, v;
+  double b, c, det;   // of the dilated 2D covariance [[a, b], [b, c]]
+  float depth;
+  int i0, i1, j0, j1;
+};
+
+// Culling and footprint in two parts.  project_front needs centre, scale and opacity (28 B), which decide
+// most culls — the near plane, the opacity threshold, and a footprint that certainly misses the image
+// (below); project_back needs the rotation (16 B) too.  The SH coefficients are read only for survivors.
 //
 // Early footprint test: the projected covariance is J W Rq diag(s)^2 Rq^T W^T J^T
 // with W and Rq rotations, so its trace is at most |J|_F^2 s_max^2, and the
@@ -128,89 +239,60 @@ struct Geo {
 // operations as below, so a centre farther than that outside the image is one
 // the exact test would cull too.  Non-finite values fail every comparison and
 // take the exact path.
-template <bool HALF>
-__device__ __forceinline__ bool project_geo(const LevelPtrs& L, int64_t gi, const gs_camera& cam, int W, int H,
-                                            Geo& o) {
-  const int64_t n = L.n;
+__device__ __forceinline__ bool project_front(const Shape& g, const gs_camera& cam, const ViewConst& vc, int W, int H,
+                                              Geo& o) {
   const double* R = cam.R;
-  o.m[0] = L.means[gi];
-  o.m[1] = L.means[n + gi];
-  o.m[2] = L.means[2 * n + gi];
-  const float op32 = attr<HALF>(L.opac, gi);
-  const float s0f = attr<HALF>(L.scales, gi), s1f = attr<HALF>(L.scales, n + gi),
-              s2f = attr<HALF>(L.scales, 2 * n + gi);
-  o.tx = ((R[0] * o.m[0] + R[1] * o.m[1]) + R[2] * o.m[2]) + cam.t[0];
-  o.ty = ((R[3] * o.m[0] + R[4] * o.m[1]) + R[5] * o.m[2]) + cam.t[1];
-  o.tz = ((R[6] * o.m[0] + R[7] * o.m[1]) + R[8] * o.m[2]) + cam.t[2];
-  if (!(o.tz > cam.znear)) return false;
-  o.opac = op32;
-  if (!(o.opac >= 1.0 / 255.0)) return false;
-  o.depth = (float)o.tz;
-  o.rz = 1.0 / o.tz;
-  o.ux = o.tx * o.rz;
-  o.uy = o.ty * o.rz;
+  const double m0 = g.m[0], m1 = g.m[1], m2 = g.m[2];
+  const double tx = ((R[0] * m0 + R[1] * m1) + R[2] * m2) + cam.t[0];
+  const double ty = ((R[3] * m0 + R[4] * m1) + R[5] * m2) + cam.t[1];
+  const double tz = ((R[6] * m0 + R[7] * m1) + R[8] * m2) + cam.t[2];
+  if (!(tz > cam.znear)) return false;
+  if (!((double)g.op >= 1.0 / 255.0)) return false;
+  o.depth = (float)tz;
+  o.rz = 1.0 / tz;
+  o.ux = tx * o.rz;
+  o.uy = ty * o.rz;
   o.u = cam.fx * o.ux + cam.cx;
   o.v = cam.fy * o.uy + cam.cy;
-  const double tanx = (0.5 * W) / cam.fx, tany = (0.5 * H) / cam.fy;
-  const double limx = 1.3 * tanx, limy = 1.3 * tany;
-  {
-    const double smax = dmax_(fabs((double)s0f), dmax_(fabs((double)s1f), fabs((double)s2f)));
-    const double jx = cam.fx * o.rz, jy = cam.fy * o.rz;
-    const double jf2 = jx * jx * (1.0 + limx * limx) + jy * jy * (1.0 + limy * limy);
-    const double rb = 3.0 * sqrt((jf2 * (smax * smax) + 0.6) * (1.0 + 1e-6)) + 2.0;
-    if ((o.u + rb) - 0.5 < 0.0 || (o.u - rb) - 0.5 > (double)(W - 1) || (o.v + rb) - 0.5 < 0.0 ||
-        (o.v - rb) - 0.5 > (double)(H - 1))
-      return false;
-  }
-  const float q0f = attr<HALF>(L.quats, gi), q1f = attr<HALF>(L.quats, n + gi), q2f = attr<HALF>(L.quats, 2 * n + gi),
-              q3f = attr<HALF>(L.quats, 3 * n + gi);
-  const double q0 = q0f, q1 = q1f, q2 = q2f, q3 = q3f;
-  const double qn2 = ((q0 * q0 + q1 * q1) + q2 * q2) + q3 * q3;
-  if (!(qn2 > 0.0 && qn2 <= 1.0e300)) return false;
-  o.qinv = 1.0 / sqrt(qn2);
-  const double w = q0 * o.qinv, x = q1 * o.qinv, y = q2 * o.qinv, z = q3 * o.qinv;
-  o.q[0] = w; o.q[1] = x; o.q[2] = y; o.q[3] = z;
-  o.Rq[0][0] = 1.0 - 2.0 * (y * y + z * z);
-  o.Rq[0][1] = 2.0 * (x * y - w * z);
-  o.Rq[0][2] = 2.0 * (x * z + w * y);
-  o.Rq[1][0] = 2.0 * (x * y + w * z);
-  o.Rq[1][1] = 1.0 - 2.0 * (x * x + z * z);
-  o.Rq[1][2] = 2.0 * (y * z - w * x);
-  o.Rq[2][0] = 2.0 * (x * z - w * y);
-  o.Rq[2][1] = 2.0 * (y * z + w * x);
-  o.Rq[2][2] = 1.0 - 2.0 * (x * x + y * y);
-  o.s[0] = s0f;
-  o.s[1] = s1f;
-  o.s[2] = s2f;
+  const double smax = dmax_(fabs((double)g.s[0]), dmax_(fabs((double)g.s[1]), fabs((double)g.s[2])));
+  const double jx = cam.fx * o.rz, jy = cam.fy * o.rz;
+  const double jf2 = jx * jx * (1.0 + vc.limx * vc.limx) + jy * jy * (1.0 + vc.limy * vc.limy);
+  const double rb = 3.0 * sqrt((jf2 * (smax * smax) + 0.6) * (1.0 + 1e-6)) + 2.0;
+  return !((o.u + rb) - 0.5 < 0.0 || (o.u - rb) - 0.5 > (double)(W - 1) || (o.v + rb) - 0.5 < 0.0 ||
+           (o.v - rb) - 0.5 > (double)(H - 1));
+}
+
+__device__ __forceinline__ bool project_back(const Shape& g, const gs_camera& cam, const ViewConst& vc, int W, int H,
+                                             Geo& o) {
+  const double* R = cam.R;
+  double WL[3][3];  // R_cam Lm
+#pragma unroll
   for (int i = 0; i < 3; ++i)
-    for (int j = 0; j < 3; ++j) o.Lm[i][j] = o.Rq[i][j] * o.s[j];
-  for (int i = 0; i < 3; ++i)
+#pragma unroll
     for (int j = 0; j < 3; ++j)
-      o.WL[i][j] = (R[3 * i + 0] * o.Lm[0][j] + R[3 * i + 1] * o.Lm[1][j]) + R[3 * i + 2] * o.Lm[2][j];
-  o.uxc = dmin_(limx, dmax_(-limx, o.ux));
-  o.uyc = dmin_(limy, dmax_(-limy, o.uy));
-  o.clamp_x = o.uxc != o.ux;
-  o.clamp_y = o.uyc != o.uy;
-  o.J00 = cam.fx * o.rz;
-  o.J02 = -(cam.fx * o.uxc) * o.rz;
-  o.J11 = cam.fy * o.rz;
-  o.J12 = -(cam.fy * o.uyc) * o.rz;
+      WL[i][j] = (R[3 * i + 0] * g.Lm[0][j] + R[3 * i + 1] * g.Lm[1][j]) + R[3 * i + 2] * g.Lm[2][j];
+  const double uxc = dmin_(vc.limx, dmax_(-vc.limx, o.ux));
+  const double uyc = dmin_(vc.limy, dmax_(-vc.limy, o.uy));
+  const double J00 = cam.fx * o.rz, J02 = -(cam.fx * uxc) * o.rz;
+  const double J11 = cam.fy * o.rz, J12 = -(cam.fy * uyc) * o.rz;
+  double M[2][3];  // J WL
+#pragma unroll
   for (int j = 0; j < 3; ++j) {
-    o.M[0][j] = o.J00 * o.WL[0][j] + o.J02 * o.WL[2][j];
-    o.M[1][j] = o.J11 * o.WL[1][j] + o.J12 * o.WL[2][j];
+    M[0][j] = J00 * WL[0][j] + J02 * WL[2][j];
+    M[1][j] = J11 * WL[1][j] + J12 * WL[2][j];
   }
-  o.n0 = (o.M[0][0] * o.M[0][0] + o.M[0][1] * o.M[0][1]) + o.M[0][2] * o.M[0][2];
-  o.n1 = (o.M[1][0] * o.M[1][0] + o.M[1][1] * o.M[1][1]) + o.M[1][2] * o.M[1][2];
-  o.b = (o.M[0][0] * o.M[1][0] + o.M[0][1] * o.M[1][1]) + o.M[0][2] * o.M[1][2];
-  o.a = o.n0 + 0.3;
-  o.c = o.n1 + 0.3;
-  const double cr0 = o.M[0][1] * o.M[1][2] - o.M[0][2] * o.M[1][1];
-  const double cr1 = o.M[0][2] * o.M[1][0] - o.M[0][0] * o.M[1][2];
-  const double cr2 = o.M[0][0] * o.M[1][1] - o.M[0][1] * o.M[1][0];
-  o.det = (((cr0 * cr0 + cr1 * cr1) + cr2 * cr2) + 0.3 * (o.n0 + o.n1)) + 0.09;
+  const double n0 = (M[0][0] * M[0][0] + M[0][1] * M[0][1]) + M[0][2] * M[0][2];
+  const double n1 = (M[1][0] * M[1][0] + M[1][1] * M[1][1]) + M[1][2] * M[1][2];
+  o.b = (M[0][0] * M[1][0] + M[0][1] * M[1][1]) + M[0][2] * M[1][2];
+  const double a = n0 + 0.3;
+  o.c = n1 + 0.3;
+  const double cr0 = M[0][1] * M[1][2] - M[0][2] * M[1][1];
+  const double cr1 = M[0][2] * M[1][0] - M[0][0] * M[1][2];
+  const double cr2 = M[0][0] * M[1][1] - M[0][1] * M[1][0];
+  o.det = (((cr0 * cr0 + cr1 * cr1) + cr2 * cr2) + 0.3 * (n0 + n1)) + 0.09;
   if (!(o.det > 0.0 && o.det <= 1.0e300)) return false;
-  const double hd = 0.5 * (o.a - o.c);
-  const double lmax = 0.5 * (o.a + o.c) + sqrt(hd * hd + o.b * o.b);
+  const double hd = 0.5 * (a - o.c);
+  const double lmax = 0.5 * (a + o.c) + sqrt(hd * hd + o.b * o.b);
   if (!(lmax <= 1.0e300)) return false;
   const double r = ceil(3.0 * sqrt(lmax));
   const double i0 = dmax_(0.0, ceil((o.u - r) - 0.5));
@@ -223,14 +305,6 @@ __device__ __forceinline__ bool project_geo(const LevelPtrs& L, int64_t gi, cons
   o.j0 = (int)j0;
   o.j1 = (int)j1;
   return true;
-}
-
-// Camera centre C = -R^T t.
-__device__ __forceinline__ void camera_centre(const gs_camera& cam, double C[3]) {
-  const double* R = cam.R;
-  C[0] = -((R[0] * cam.t[0] + R[3] * cam.t[1]) + R[6] * cam.t[2]);
-  C[1] = -((R[1] * cam.t[0] + R[4] * cam.t[1]) + R[7] * cam.t[2]);
-  C[2] = -((R[2] * cam.t[0] + R[5] * cam.t[1]) + R[8] * cam.t[2]);
 }
 
 // sqrt(log2(e) / 2): the conic factor is scaled so the Gaussian is exp2(-Q).

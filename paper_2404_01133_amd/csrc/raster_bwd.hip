@@ -495,30 +495,6 @@ struct BwdArgs {
   int32_t packed;  // gather entries are level << GS_PACKED_INDEX_BITS | index (refined selection)
 };
 
-// What the adjoint needs of a view in FP64 and is the same for every record: camera centre and
-// guard-band limits.  A work-group keeps them in LDS for up to kBwdViews views (15 FP64 operations
-// and two divisions less per record).
-struct ViewConst {
-  double C[3], limx, limy;
-  __device__ __forceinline__ void load(const BwdArgs& a, int v) {
-    const gs_camera& cam = a.cams[v];
-    camera_centre(cam, C);
-    limx = 1.3 * ((0.5 * a.W) / cam.fx);
-    limy = 1.3 * ((0.5 * a.H) / cam.fy);
-  }
-};
-constexpr int kBwdViews = 32;
-
-__device__ __forceinline__ void load_views(const BwdArgs& a, ViewConst (&s_view)[kBwdViews]) {
-  if ((int)threadIdx.x < a.V && threadIdx.x < kBwdViews) s_view[threadIdx.x].load(a, threadIdx.x);
-}
-__device__ __forceinline__ ViewConst view_const(const BwdArgs& a, const ViewConst (&s_view)[kBwdViews], int v) {
-  if (a.V <= kBwdViews) return s_view[v];
-  ViewConst c;
-  c.load(a, v);
-  return c;
-}
-
 // The projection adjoint is bound by its reads and writes of whole parameter planes (1M Gaussians,
 // 117K visible in one view: 640 MB of lines touched in 217 us, 46 us of it VALU time).  So:
 //  * a Gaussian's parameters are loaded together, ahead of all arithmetic, and ahead of the first store
@@ -526,10 +502,11 @@ __device__ __forceinline__ ViewConst view_const(const BwdArgs& a, const ViewCons
 //  * the compositing kernel drops the colour partials of clamped channels, so no record is read here
 //    (16 views x 2M: 1 GB of record lines less);
 //  * in the Gaussian-major kernel the parameters are read once for all views, and the next view's 2D
-//    gradient is in flight during a view's adjoint.
-// 1M: 217 -> 169 us; 16 shared views x 2M (12.6M visible): 1041 -> 646 us (2.5 GB, 3.9 TB/s);
-// four views of 262K visible with atomics: 290 -> 276 us, bound by the 62M memory-side atomic adds.
-// Packing the visible records of 1024 into full waves first measured no gain (171, 290 us).
+//    gradient is in flight during a view's adjoint;
+//  * camera and level pointers are scalar (they are one for nearly every wave).
+// 1M: 217 -> 156 us; 16 shared views x 2M (12.6M visible): 1041 -> 586 us (2.5 GB, 4.3 TB/s; with vector
+// cameras and levels 172 and 637); four views of 262K visible with atomics: 290 -> 270 us, bound by the
+// 62M memory-side atomic adds.  Packing the visible records of 1024 into full waves first measured no gain.
 //
 // Parameters of one Gaussian, loaded together (the loads are all in flight at once).
 struct GaussianIn {
@@ -538,13 +515,13 @@ struct GaussianIn {
   template <bool HALF>
   __device__ __forceinline__ void load(const LevelPtrs& L, int sh_degree, int64_t gi) {
     deg = sh_degree < L.sh_deg ? sh_degree : L.sh_deg;
-    const int terms = 3 * (deg + 1) * (deg + 1);
 #pragma unroll
     for (int k = 0; k < 3; ++k) m[k] = L.means[k * L.n + gi];
 #pragma unroll
     for (int k = 0; k < 4; ++k) q[k] = attr<HALF>(L.quats, k * L.n + gi);
 #pragma unroll
     for (int k = 0; k < 3; ++k) s[k] = attr<HALF>(L.scales, k * L.n + gi);
+    const int terms = 3 * (deg + 1) * (deg + 1);
 #pragma unroll
     for (int i = 3; i < 48; ++i) f[i] = i < terms ? attr<HALF>(L.sh, (int64_t)i * L.n + gi) : 0.0f;
   }
@@ -709,10 +686,9 @@ __device__ __forceinline__ bool load_grad2d(const float* __restrict__ grad2d, in
 
 // One record's adjoint, for a record whose 2D gradient p2 is not all zero.
 template <class Sink>
-__device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const GaussianIn& in, const float (&p2)[kG],
-                                                        int v, const ViewConst& vc, RecordGrad& out,
+__device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const GaussianIn& in, const gs_camera& cam,
+                                                        const float (&p2)[kG], const ViewConst& vc, RecordGrad& out,
                                                         Sink& sink) {
-  const gs_camera& cam = a.cams[v];
   // A record with a non-zero 2D gradient was visible in the forward pass, so
   // the projection below (same code, same inputs) takes the same decisions.
   // ---- colour first (FP32; clamped channels come with no gradient)
@@ -874,7 +850,7 @@ __device__ __forceinline__ void preprocess_bwd_record_t(const BwdArgs& a, const 
 template <bool HALF>
 __device__ __forceinline__ void preprocess_bwd_gaussian(const BwdArgs& a, const float* __restrict__ grad2d,
                                                         int64_t n_rec, int64_t n_view, int64_t i, int l, int64_t gi,
-                                                        const ViewConst (&s_view)[kBwdViews]) {
+                                                        const ViewConst (&s_view)[kLdsViews]) {
   if (i >= n_rec) return;
   float p2[kG];
   bool hit = load_grad2d(grad2d, i, p2);
@@ -891,7 +867,7 @@ __device__ __forceinline__ void preprocess_bwd_gaussian(const BwdArgs& a, const 
     if (more) next_hit = load_grad2d(grad2d, g + n_view, next);
     if (hit) {
       RecordGrad r;
-      preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, acc);
+      preprocess_bwd_record_t(a, in, uniform_camera(a.cams, v), p2, view_const(a.cams, a.V, a.W, a.H, s_view, v), r, acc);
       acc.add(r);
       any = true;
     }
@@ -914,8 +890,8 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const fl
   // segment offsets staged in LDS when they fit; a record is looked up only
   // once its 2D gradient is known to be non-zero (most selected records were culled)
   __shared__ int64_t s_off[kBwdLdsOffsets];
-  __shared__ ViewConst s_view[kBwdViews];
-  load_views(a, s_view);
+  __shared__ ViewConst s_view[kLdsViews];
+  load_views(a.cams, a.V, a.W, a.H, s_view);
   const bool lds_off = nseg < kBwdLdsOffsets;
   if (lds_off)
     for (int k = threadIdx.x; k <= nseg; k += blockDim.x) s_off[k] = a.offsets[k];
@@ -938,14 +914,19 @@ __global__ void __launch_bounds__(256) preprocess_bwd_kernel(BwdArgs a, const fl
       const int64_t seg0 = lds_off ? s_off[p] : a.offsets[p];
       gi = a.gather ? (int64_t)entry : a.lvl_off[(int64_t)b * a.L + l] + (g - seg0);
     }
-    GaussianIn in;
-    if (a.lv[l].half) in.load<true>(a.lv[l], a.sh_degree, gi);
-    else in.load<false>(a.lv[l], a.sh_degree, gi);
-    RecordGrad r;
-    NoSh none;
-    preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, none);
-    if constexpr (SINGLE) add_plain(a.gr[l], a.lv[l].n, gi, r);
-    else add_atomic(a.gr[l], a.lv[l].n, gi, r);
+    for_each_key(v * kMaxLevels + l, [&](int key) {
+      const int uv = key / kMaxLevels, ul = key % kMaxLevels;
+      const LevelPtrs& L = a.lv[ul];
+      GaussianIn in;
+      if (L.half) in.load<true>(L, a.sh_degree, gi);
+      else in.load<false>(L, a.sh_degree, gi);
+      RecordGrad r;
+      NoSh none;
+      preprocess_bwd_record_t(a, in, uniform_camera(a.cams, uv), p2, view_const(a.cams, a.V, a.W, a.H, s_view, uv), r,
+                              none);
+      if constexpr (SINGLE) add_plain(a.gr[ul], L.n, gi, r);
+      else add_atomic(a.gr[ul], L.n, gi, r);
+    });
   }
 }
 
@@ -956,8 +937,8 @@ __global__ void __launch_bounds__(256) preprocess_bwd_shared_kernel(BwdArgs a, c
   if (counts[GS_COUNT_FLAGS] & GS_FLAG_SELECTION) return;  // the forward projected nothing
   int64_t n_rec = counts[GS_COUNT_RECORDS];
   if (n_rec > a.capacity) n_rec = a.capacity;
-  __shared__ ViewConst s_view[kBwdViews];
-  load_views(a, s_view);
+  __shared__ ViewConst s_view[kLdsViews];
+  load_views(a.cams, a.V, a.W, a.H, s_view);
   __syncthreads();
   const int64_t n_view = a.offsets[a.segs];
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
@@ -965,8 +946,10 @@ __global__ void __launch_bounds__(256) preprocess_bwd_shared_kernel(BwdArgs a, c
     const int b = find_segment(a.offsets, a.segs, i);
     const int l = a.gather ? b : a.level[b];
     const int64_t gi = a.gather ? (int64_t)a.gather[i] : a.lvl_off[(int64_t)b * a.L + l] + (i - a.offsets[b]);
-    if (a.lv[l].half) preprocess_bwd_gaussian<true>(a, grad2d, n_rec, n_view, i, l, gi, s_view);
-    else preprocess_bwd_gaussian<false>(a, grad2d, n_rec, n_view, i, l, gi, s_view);
+    for_each_key(l, [&](int u) {
+      if (a.lv[u].half) preprocess_bwd_gaussian<true>(a, grad2d, n_rec, n_view, i, u, gi, s_view);
+      else preprocess_bwd_gaussian<false>(a, grad2d, n_rec, n_view, i, u, gi, s_view);
+    });
   }
 }
 
@@ -979,8 +962,8 @@ __global__ void __launch_bounds__(256) preprocess_bwd_det_kernel(BwdArgs a, cons
                                                                  int64_t n_stored) {
   int64_t n_rec = counts[GS_COUNT_RECORDS];
   if (n_rec > a.capacity) n_rec = a.capacity;
-  __shared__ ViewConst s_view[kBwdViews];
-  load_views(a, s_view);
+  __shared__ ViewConst s_view[kLdsViews];
+  load_views(a.cams, a.V, a.W, a.H, s_view);
   __syncthreads();
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   for (int64_t t = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; t < n_stored; t += stride) {
@@ -1011,7 +994,7 @@ __global__ void __launch_bounds__(256) preprocess_bwd_det_kernel(BwdArgs a, cons
       if (a.lv[l].half) in.load<true>(a.lv[l], a.sh_degree, gi);
       else in.load<false>(a.lv[l], a.sh_degree, gi);
       RecordGrad r;
-      preprocess_bwd_record_t(a, in, p2, v, view_const(a, s_view, v), r, acc);
+      preprocess_bwd_record_t(a, in, a.cams[v], p2, view_const(a.cams, a.V, a.W, a.H, s_view, v), r, acc);
       acc.add(r);
       any = true;
     }
