@@ -183,11 +183,17 @@ def camera_struct(cam) -> gs_camera:
     return c
 
 
+CAMERA_BYTES = ctypes.sizeof(gs_camera)
+
+
+def cameras_bytes(cams) -> bytes:
+    """gs_camera[V]"""
+    return bytes((gs_camera * len(cams))(*[camera_struct(c) for c in cams]))
+
+
 def cameras_to_device(cams, device="cuda") -> torch.Tensor:
     """Pack cameras into a device byte tensor holding gs_camera[V]."""
-    arr = (gs_camera * len(cams))(*[camera_struct(c) for c in cams])
-    host = torch.frombuffer(bytearray(bytes(arr)), dtype=torch.uint8)
-    return host.to(device)
+    return torch.frombuffer(bytearray(cameras_bytes(cams)), dtype=torch.uint8).to(device)
 
 
 SH_PLANES = {1: 0, 4: 1, 9: 2, 16: 3}

@@ -12,6 +12,8 @@ unless a capacity check is requested.
 """
 from __future__ import annotations
 
+import ctypes
+import struct
 from dataclasses import dataclass
 
 import numpy as np
@@ -43,8 +45,10 @@ class DeviceLevel:
 
     def zeros_like(self) -> "DeviceLevel":
         """FP32 gradient buffers shaped like this level (whatever its storage precision)."""
-        return DeviceLevel(*(torch.zeros(t.shape, dtype=torch.float32, device=t.device)
-                             for t in (self.means, self.scales, self.quats, self.opac, self.sh)))
+        out = [torch.empty(t.shape, dtype=torch.float32, device=t.device)
+               for t in (self.means, self.scales, self.quats, self.opac, self.sh)]
+        torch._foreach_zero_(out)  # one launch
+        return DeviceLevel(*out)
 
     def reduced(self, sh_degree: int, half: bool) -> "DeviceLevel":
         """Copy with `sh_degree` SH bands stored and, if `half`, every attribute but
@@ -57,11 +61,14 @@ class DeviceLevel:
 class DeviceScene:
     """Gaussians of every detail level plus the block table, in device memory."""
 
-    def __init__(self, levels, lvl_off, lvl_cnt, cells=None, lo=None, hi=None, device="cuda"):
+    def __init__(self, levels, lvl_off, lvl_cnt, cells=None, lo=None, hi=None, device="cuda", tables=None):
         self.levels = levels
         self.device = device
-        self.lvl_off = torch.as_tensor(np.asarray(lvl_off, np.int64)).to(device)
-        self.lvl_cnt = torch.as_tensor(np.asarray(lvl_cnt, np.int64)).to(device)
+        if tables is None:
+            self.lvl_off = torch.as_tensor(np.asarray(lvl_off, np.int64)).to(device)
+            self.lvl_cnt = torch.as_tensor(np.asarray(lvl_cnt, np.int64)).to(device)
+        else:  # (device int64: lvl_off, then lvl_cnt)
+            self.lvl_off, self.lvl_cnt = tables.view(2, *np.shape(lvl_off))
         self.lvl_cnt_host = np.asarray(lvl_cnt, np.int64)
         self.cells = None if cells is None else torch.as_tensor(np.asarray(cells, np.float64)).to(device)
         self.lo = None if lo is None else torch.as_tensor(np.asarray(lo, np.float64)).to(device)
@@ -329,8 +336,15 @@ def render_frame(scene: DeviceScene, frame: Frame, cams_dev, mode=gs.GS_LOD_BLOC
     chunk boxes are made once per scene: after moving or rescaling Gaussians (an
     optimiser step) call scene.invalidate_chunks(), or the refinement may drop
     Gaussians that have become visible."""
+    return _render(scene, frame, cams_dev, mode, thresholds, sh_degree, bg, stream, check, refine, False)
+
+
+def _render(scene, frame, cams_dev, mode, thresholds, sh_degree, bg, stream, check, refine, copy):
+    """render_frame; copy: returns a copy of the image made on the same stream."""
     if refine and mode == LOD_POINTWISE:
         raise ValueError("the chunk refinement applies to block-wise selections")
+    if stream is None:
+        stream = torch.cuda.current_stream()
     for _ in range(4):
         blocks = scene.blocks_struct()
         levels = [lv.struct() for lv in scene.levels]
@@ -358,8 +372,9 @@ def render_frame(scene: DeviceScene, frame: Frame, cams_dev, mode=gs.GS_LOD_BLOC
                     frame.tile_ranges, frame.counts, frame.sort_ws, stream, frame.tile_queue)
         gs.rasterize_fwd(frame.records, frame.pair_records, frame.tile_ranges, frame.V, frame.W, frame.H, bg,
                          frame.tuning, frame.rgb, frame.T, frame.n_last, stream, frame.tile_queue)
+        rgb = frame.rgb.clone() if copy else frame.rgb  # (before the counts: the host waits for both at once)
         if not check:
-            return frame.rgb
+            return rgb
         c = frame.host_counts()
         if c["flags"] & gs.GS_FLAG_WAIT:
             raise RuntimeError("a device-side wait gave up during the frame (counts=%s)" % c)
@@ -367,7 +382,7 @@ def render_frame(scene: DeviceScene, frame: Frame, cams_dev, mode=gs.GS_LOD_BLOC
             raise RuntimeError("GS_TUNE_SHARED_SELECTION was set but the views selected different records "
                                "(counts=%s)" % c)
         if c["flags"] == 0:
-            return frame.rgb
+            return rgb
         frame.reserve(max(frame.record_capacity, int(c["records"] * 1.1) + 1024),
                       max(frame.pair_capacity, int(c["pairs"] * 1.25) + 4096))
     raise RuntimeError("frame did not fit after growing the buffers: %s" % frame.host_counts())
@@ -393,6 +408,22 @@ def backward_frame(scene: DeviceScene, frame: Frame, cams_dev, d_rgb, grads, sh_
 # ---------------------------------------------------------------------------
 # differentiable render of one Gaussian set
 # ---------------------------------------------------------------------------
+def _single_table(n) -> bytes:
+    """Block table of one set: lvl_off [1, 1] and lvl_cnt [1, 1], int64."""
+    return struct.pack("2q", 0, n)
+
+
+def _stage(data, device) -> torch.Tensor:
+    """Bytes on the device for work on its current stream: copied through pinned
+    memory in stream order, so the host does not wait.  (A pageable copy waits: 15 us
+    each.)  A stream of another device would not be ordered: the host waits then."""
+    if device.type != "cuda" or device.index not in (None, torch.cuda.current_device()):
+        return torch.frombuffer(bytearray(data), dtype=torch.uint8).to(device)
+    host = torch.empty(len(data), dtype=torch.uint8, pin_memory=True)
+    ctypes.memmove(host.data_ptr(), data, len(data))
+    return host.to(device, non_blocking=True)
+
+
 class GaussianRasterize(torch.autograd.Function):
     """image[V,3,H,W] = render(means[3,N], scales[3,N], quats[4,N], opac[N], sh[16,3,N]; cameras).
 
@@ -401,17 +432,25 @@ class GaussianRasterize(torch.autograd.Function):
 
     @staticmethod
     def forward(ctx, means, scales, quats, opac, sh, cams_dev, n_views, width, height, sh_degree, bg, frame):
-        scene = DeviceScene.from_tensors(means.detach().contiguous(), scales.detach().contiguous(),
-                                         quats.detach().contiguous(), opac.detach().contiguous(),
-                                         sh.detach().contiguous())
+        level = DeviceLevel(means.detach().contiguous(), scales.detach().contiguous(), quats.detach().contiguous(),
+                            opac.detach().contiguous(), sh.detach().contiguous())
+        # rasterize() sends the block table behind the cameras; cameras alone are taken too
+        tables = cams_dev[n_views * gs.CAMERA_BYTES:]
+        if tables.numel() == 0:
+            tables = _stage(_single_table(level.n), means.device)
+        scene = DeviceScene([level], [[0]], [[level.n]], device=means.device, tables=tables.view(torch.int64))
+        records = n_views * level.n
         if frame is None:
-            frame = Frame(1, n_views, width, height, n_views * scene.n_finest, max(4096, 4 * n_views * scene.n_finest))
+            # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (36 bytes a pair with
+            # the sort's workspace, 300 MB).  Splats of a small set may cover tens of tiles each, and a guess
+            # that is too low costs a second frame (2 x 70001 records, 5.2M pairs, with gradients: 1287 -> 915 us).
+            frame = Frame(1, n_views, width, height, records, max(4 * records, min(64 * records, 1 << 23), 4096))
         else:
-            frame.reserve(n_views * scene.n_finest, 0)
-        render_frame(scene, frame, cams_dev, mode=gs.GS_LOD_ALL_FINEST, thresholds=(), sh_degree=sh_degree, bg=bg)
+            frame.reserve(records, 0)
+        rgb = _render(scene, frame, cams_dev, gs.GS_LOD_ALL_FINEST, (), sh_degree, bg, None, True, False, True)
         ctx.scene, ctx.frame, ctx.cams = scene, frame, cams_dev
         ctx.sh_degree, ctx.bg = sh_degree, bg
-        return frame.rgb.clone()
+        return rgb
 
     @staticmethod
     def backward(ctx, d_rgb):
@@ -424,6 +463,6 @@ class GaussianRasterize(torch.autograd.Function):
 
 def rasterize(means, scales, quats, opac, sh, cams, sh_degree=3, bg=(0.0, 0.0, 0.0), frame=None):
     """Differentiable render of one Gaussian set for a list of cameras (same size)."""
-    cams_dev = gs.cameras_to_device(cams, means.device)
+    cams_dev = _stage(gs.cameras_bytes(cams) + _single_table(int(opac.shape[0])), means.device)
     W, H = cams[0].width, cams[0].height
     return GaussianRasterize.apply(means, scales, quats, opac, sh, cams_dev, len(cams), W, H, sh_degree, bg, frame)

@@ -40,3 +40,22 @@ def test_gaussian_major_equals_view_major_with_mixed_levels(V):
     for a, b in zip(got, want):
         for x, y in zip(a, b):
             assert np.linalg.norm(x - y) <= 1e-5 * np.linalg.norm(y)
+
+
+@pytest.mark.parametrize("side_stream", [False, True])
+def test_rasterize_equals_apply_with_cameras_alone(side_stream):
+    """rasterize() sends cameras and block table in one copy on the current stream;
+    the function also takes cameras without the table.  Same images, kept apart from the frame's."""
+    g = synth.box_gaussians(3_000, seed=3, extent=((-20, 20), (-20, 20), (0, 8)))
+    cams = synth.orbit_views((0.0, 0.0), n_views=3, radius=30.0, height=25.0, width=90, h_px=50)
+    arrays = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in g.astuple()]
+    cams_dev = gs.cameras_to_device(cams)
+    torch.cuda.synchronize()
+    stream = torch.cuda.Stream() if side_stream else torch.cuda.current_stream()
+    with torch.cuda.stream(stream):
+        frame = render.Frame(1, 3, 90, 50, 3 * 3_000, 1 << 12)  # too few pairs: the frame is rendered again
+        a = render.rasterize(*arrays, cams, frame=frame)
+        b = render.GaussianRasterize.apply(*arrays, cams_dev, 3, 90, 50, 3, (0.0, 0.0, 0.0), None)
+    stream.synchronize()
+    assert frame.pair_capacity > 1 << 12 and float(a.abs().max()) > 0
+    assert torch.equal(a, b) and torch.equal(a, frame.rgb) and a.data_ptr() != frame.rgb.data_ptr()
