@@ -441,8 +441,8 @@ class GaussianRasterize(torch.autograd.Function):
         scene = DeviceScene([level], [[0]], [[level.n]], device=means.device, tables=tables.view(torch.int64))
         records = n_views * level.n
         if frame is None:
-            # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (36 bytes a pair with
-            # the sort's workspace, 300 MB).  Splats of a small set may cover tens of tiles each, and a guess
+            # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (17 bytes a pair with
+            # the sort's workspace, 150 MB).  Splats of a small set may cover tens of tiles each, and a guess
             # that is too low costs a second frame (2 x 70001 records, 5.2M pairs, with gradients: 1287 -> 915 us).
             frame = Frame(1, n_views, width, height, records, max(4 * records, min(64 * records, 1 << 23), 4096))
         else:
