@@ -80,8 +80,9 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     }
     clear_lists<BATCH, kFwdGroups>(lists);
     __syncthreads();
-    const int max_cnt =
-        wave_compact8<BATCH>(s_w0, s_f, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
+    int max_cnt = 0;
+    if (__ballot(fi == fi))  // (a wave whose pixels are all done only stages)
+      max_cnt = wave_compact8<BATCH>(s_w0, s_f, s_w1, s_w2, nb, qb.x0, qb.y0, lds.cand[wid], lists);
     const int base_idx = (int)(b - start);
     int last_k = -1;  // 16 x the batch index of the last entry used in this batch
     auto blend = [&](int k, float du, const float4& f, const float4& w1, const float4& w2) {
@@ -110,6 +111,8 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     for (int t = 0; t < max_cnt; t += 4) {
       // byte offsets (index * 16) of the four entries into the staged arrays
       const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
+      // no pixel is left that is not done and has an entry (else: four null records)
+      if (__ballot((fi == fi) & (pk != (uint32_t)(BATCH - 1) * 0x01010101u)) == 0) break;
       const uint32_t o0 = (pk & (BATCH - 1)) << 4, o1 = ((pk >> 8) & (BATCH - 1)) << 4;
       const uint32_t o2 = ((pk >> 16) & (BATCH - 1)) << 4, o3 = ((pk >> 24) & (BATCH - 1)) << 4;
       auto at = [](const float4* a, uint32_t o) {
@@ -127,7 +130,6 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
       blend((int)o1, bu, bf, b1, b2);
       blend((int)o2, cu, cf, c1, c2);
       blend((int)o3, du, df, d1, d2);
-      if (__ballot(fi == fi) == 0) break;  // every pixel of the wave is done
     }
     if (last_k >= 0) last = base_idx + (last_k >> 4) + 1;
     __syncthreads();
