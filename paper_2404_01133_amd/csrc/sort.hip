@@ -34,7 +34,8 @@ namespace {
 constexpr int kMaxTilePasses = 4;       // digits of a tile id (below 2^31) at up to 9 bits
 constexpr int kTileDigits = 512;        // words of one tile-digit histogram
 constexpr int kHistItems = 8;           // records per thread of the depth histogram
-constexpr uint32_t kBigFootprint = 16;  // records touching more tiles are emitted cooperatively
+constexpr uint32_t kBigFootprint = 16;    // records touching more tiles are emitted by a wave each,
+constexpr uint32_t kHugeFootprint = 512;  // with more than this by a work-group
 // emit_kernel's work-groups all finish at about the same time and each adds its
 // tile-digit histogram to device memory, so a single copy would take ~2000
 // same-address atomics per word in a row.  They add into kTileHistCopies
@@ -191,9 +192,9 @@ struct EmitArgs {
   uint32_t* hist_extra;
   uint64_t* status;              // look-back words
   uint32_t* tile_counter;
-  uint32_t* big_rec;             // records with many tiles and their first pair
-  uint32_t* big_off;
-  uint32_t* big_count;
+  uint32_t* big_rec;             // records with many tiles and their first pair: a wave's from the front,
+  uint32_t* big_off;             // a work-group's from the back ([cap])
+  uint32_t* big_count;           // of each kind
 };
 
 // first tile id and extent in tiles (columns | rows << 16) of a record
@@ -275,7 +276,13 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
     const TileRect r = rect[k];  // (no tiles past the end)
     int64_t o = (int64_t)(tile_base + off[k]);
     const bool many = r.tiles() > kBigFootprint;
-    const bool big = many && o < a.pair_cap;  // left to emit_big_kernel
+    const bool huge = r.tiles() > kHugeFootprint;
+    const bool big = many && !huge && o < a.pair_cap;  // left to emit_big_kernel
+    if (huge && o < a.pair_cap) {
+      const uint32_t at = (uint32_t)a.cap - 1u - atomicAdd(a.big_count + 1, 1u);
+      a.big_rec[at] = rid[k];
+      a.big_off[at] = (uint32_t)o;
+    }
     const uint64_t bm = __ballot(big);
     if (bm) {  // one device atomic for the wave's
       uint32_t at = 0;
@@ -335,12 +342,28 @@ __global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
     }
 }
 
-// Records whose footprint covers many tiles (a Gaussian close to the camera):
-// one work-group per record, its tiles strided over the threads, written to
-// the same slots (row-major tile order) the serial loop would use.
+// Records whose footprint covers many tiles (a Gaussian close to the camera), written to the same slots
+// (row-major tile order) the serial loop would use: a wave per record up to kHugeFootprint tiles, a
+// work-group beyond.  2 x 70001 records of 37 tiles: 263 us with a work-group for every record.
+__device__ __forceinline__ void emit_footprint(const EmitArgs& a, uint32_t i, uint32_t first, uint32_t step,
+                                               uint32_t (*s_hist)[kTileDigits]) {
+  const uint32_t rid = a.big_rec[i];
+  const TileRect r = tile_rect(a, a.rec_words[(size_t)kRecordWords * rid]);
+  const int64_t o0 = a.big_off[i];
+  for (uint32_t q = first; q < r.tiles(); q += step) {
+    const int64_t o = o0 + q;
+    if (o < a.pair_cap) {
+      const uint32_t ty = q / r.columns(), tx = q % r.columns();
+      const uint32_t key = r.first + ty * (uint32_t)a.tiles_x + tx;
+      a.out_tiles[o] = key;
+      a.out_records[o] = rid;
+      count_tile(a, s_hist, key);
+    }
+  }
+}
 __global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
   __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
-  const uint32_t nbig = *a.big_count;
+  const uint32_t nbig = a.big_count[0], nhuge = a.big_count[1];
   // emit_kernel has finished (same stream): its partial histograms are final
   if (blockIdx.x == 0) {
     for (int i = threadIdx.x; i < a.passes * kTileDigits; i += kThreads) {
@@ -353,25 +376,15 @@ __global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
       if (sum) atomicAdd(&a.hist[i], sum);
     }
   }
-  if (blockIdx.x >= nbig) return;
+  constexpr uint32_t kWaves = kThreads / 64;
+  if (blockIdx.x * kWaves >= nbig && blockIdx.x >= nhuge) return;
   for (int p = 0; p < a.passes; ++p)
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
   __syncthreads();
-  for (uint32_t k = blockIdx.x; k < nbig; k += gridDim.x) {
-    const uint32_t rid = a.big_rec[k];
-    const TileRect r = tile_rect(a, a.rec_words[(size_t)kRecordWords * rid]);
-    const int64_t o0 = a.big_off[k];
-    for (uint32_t q = threadIdx.x; q < r.tiles(); q += kThreads) {
-      const int64_t o = o0 + q;
-      if (o < a.pair_cap) {
-        const uint32_t ty = q / r.columns(), tx = q % r.columns();
-        const uint32_t key = r.first + ty * (uint32_t)a.tiles_x + tx;
-        a.out_tiles[o] = key;
-        a.out_records[o] = rid;
-        count_tile(a, s_hist, key);
-      }
-    }
-  }
+  for (uint32_t k = blockIdx.x * kWaves + (threadIdx.x >> 6); k < nbig; k += gridDim.x * kWaves)
+    emit_footprint(a, k, threadIdx.x & 63, 64, s_hist);
+  for (uint32_t k = blockIdx.x; k < nhuge; k += gridDim.x)
+    emit_footprint(a, (uint32_t)a.cap - 1u - k, threadIdx.x, kThreads, s_hist);
   __syncthreads();
   for (int p = 0; p < a.passes; ++p)
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) {
@@ -614,10 +627,10 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   e.tile_counter = counters + 24;
   e.big_rec = w.big_rec;
   e.big_off = w.big_off;
-  e.big_count = counters + 32;
+  e.big_count = counters + 32;  // two
   const int64_t eg = emit_tiles_bound(record_capacity);
   hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(eg < 2048 ? eg : 2048)), blk, 0, s, e);
-  hipLaunchKernelGGL(emit_big_kernel, dim3(256), blk, 0, s, e);
+  hipLaunchKernelGGL(emit_big_kernel, dim3(512), blk, 0, s, e);
   GS_LAUNCH_CHECK();
   // 4. tile passes
   uint32_t* kin = e.out_tiles;
