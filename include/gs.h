@@ -289,9 +289,10 @@ gs_status gs_preprocess(const gs_gaussians* levels, const gs_blocks* blocks, con
  * that cover it in depth order, front to back; this call lists, per screen
  * tile, the visible records whose footprint meets the tile in that order.
  * One (tile, record) pair per tile under each visible record's footprint,
- * sorted by (view*tiles + tile, depth, record index) with a stable LSD radix
- * sort (depth digits on the visible records, tile digits on the pairs), so
- * ties go to the lower record index.
+ * sorted by (view*tiles + tile, depth, record index), so ties go to the lower
+ * record index (stable LSD radix sorts: depth digits on the visible records, then
+ * tile digits on the pairs; or, with few pairs per tile, tile digits on the pairs
+ * and then each tile's list by depth).
  * Inputs: records, depth_keys and tiles_touched as written by gs_preprocess
  * with the same width, height and tile shape (record_capacity entries;
  * counts[GS_COUNT_RECORDS] of them are read; tiles_touched must equal the

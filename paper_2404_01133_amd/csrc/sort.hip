@@ -1,9 +1,10 @@
-// Tile binning: (tile, depth, record) ordering of the projected Gaussians.
+// Tile binning: (tile, depth, record) ordering of the projected Gaussians, in one of two
+// orders of work (lists_by_tile says which, and why).
 //
-// The (tile | depth) key of every (tile, Gaussian) pair is sorted by a stable
-// least-significant-digit radix sort.  Its low (depth) digits do not depend on
+// Depth first.  The (tile | depth) key of every (tile, Gaussian) pair is sorted by a
+// stable least-significant-digit radix sort.  Its low (depth) digits do not depend on
 // the tile, so those passes run once per visible record, before the pairs are
-// duplicated; only the tile digits run over the pairs.  Stages:
+// duplicated; only the tile digits run over the pairs.
 //   1. hist      digit histograms of the visible records' depth keys
 //   2. 4 passes  stable radix sort by the 32-bit depth key (ties keep record order);
 //                the first one reads every selected record and keeps the visible
@@ -14,7 +15,9 @@
 //                footprint, with the histograms of the tile digits
 //   4. passes    stable radix sort by tile id (ceil(bits / 9) passes)
 //   5. ranges    [start, end) of every tile
-// The result equals a sort by (tile, depth, record id).
+// By tile.  Stages 1 and 2 fall away, stage 3 emits in record order, and
+//   6. lists     every list is sorted by (depth, record) for itself
+// Either way the result equals a sort by (tile, depth, record id).
 //
 // The radix passes are single-pass with decoupled
 // look-back: work-groups take tile ids from an atomic counter in launch order,
@@ -26,6 +29,7 @@
 // host synchronisation and the whole stage can be captured in a HIP graph.
 #include <mutex>
 
+#include "list_sort.h"
 #include "radix.h"
 
 namespace gs {
@@ -36,6 +40,7 @@ constexpr int kTileDigits = 512;        // words of one tile-digit histogram
 constexpr int kHistItems = 8;           // records per thread of the depth histogram
 constexpr uint32_t kBigFootprint = 16;    // records touching more tiles are emitted by a wave each,
 constexpr uint32_t kHugeFootprint = 512;  // with more than this by a work-group
+constexpr int kVisibleCopies = 8;
 // emit_kernel's work-groups all finish at about the same time and each adds its
 // tile-digit histogram to device memory, so a single copy would take ~2000
 // same-address atomics per word in a row.  They add into kTileHistCopies
@@ -73,7 +78,7 @@ __host__ __device__ constexpr int64_t emit_tiles_bound(int64_t n) {
 struct ClearArgs {
   uint32_t* fixed;
   int64_t fixed_words;
-  uint32_t* dstatus;  // [tile][4][256]
+  uint32_t* dstatus;  // [tile][4][256]; NULL: no depth passes
   uint64_t* estatus;  // [tile]
   uint32_t* pstatus;
   int64_t pstatus_words;
@@ -82,10 +87,13 @@ struct ClearArgs {
 };
 __global__ void clear_front_kernel(ClearArgs a, int64_t* counts, int64_t cap) {
   const int64_t n = count_clamped(counts, GS_COUNT_RECORDS, cap);
-  const int64_t dwords = radix_tiles(n) * 4 * kRadix, ewords = emit_tiles(n);
+  const int64_t dwords = a.dstatus ? radix_tiles(n) * 4 * kRadix : 0, ewords = emit_tiles(n);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
-  if (i0 == 0) counts[GS_COUNT_PAIRS] = 0;  // (no visible record: no emission tile writes it)
+  if (i0 == 0) {
+    counts[GS_COUNT_VISIBLE] = 0;  // (the emission in record order adds to it)
+    counts[GS_COUNT_PAIRS] = 0;    // (no visible record: no emission tile writes it)
+  }
   for (int64_t i = i0; i < a.fixed_words; i += stride) a.fixed[i] = 0u;
   for (int64_t i = i0; i < dwords; i += stride) a.dstatus[i] = 0u;
   for (int64_t i = i0; i < ewords; i += stride) a.estatus[i] = 0ull;
@@ -180,7 +188,8 @@ __global__ void __launch_bounds__(kThreads) depth_hist_kernel(const int32_t* __r
 // ---------------------------------------------------------------------------
 struct EmitArgs {
   const uint4* rec_words;        // records as 16-byte words, kRecordWords per record
-  const uint32_t* sorted;        // visible records in depth order
+  const uint32_t* sorted;        // visible records in depth order (emission in that order)
+  const int32_t* tiles_touched;  // > 0: visible (emission in record order)
   int64_t* counts;
   int64_t cap, pair_cap;
   int tw_shift, th_shift;        // log2 of the tile shape (every supported shape is a power of two)
@@ -195,6 +204,7 @@ struct EmitArgs {
   uint32_t* big_rec;             // records with many tiles and their first pair: a wave's from the front,
   uint32_t* big_off;             // a work-group's from the back ([cap])
   uint32_t* big_count;           // of each kind
+  uint32_t* visible;             // [kVisibleCopies] partial counts (emission in record order)
 };
 
 // first tile id and extent in tiles (columns | rows << 16) of a record
@@ -216,26 +226,42 @@ __device__ __forceinline__ void count_tile(const EmitArgs& a, uint32_t (*s_hist)
   for (int p = 0; p < a.passes; ++p) atomicAdd(&s_hist[p][(key >> (a.bits * p)) & mask], 1u);
 }
 
-// One work-group tile of kThreads * ITEMS sorted records: gather, scan, write.
-template <int ITEMS>
+// One work-group tile of kThreads * ITEMS records, sorted ones or (BY_RECORD) all in index order: gather,
+// scan, write.
+template <int ITEMS, bool BY_RECORD>
 __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t t, int64_t ntiles,
-                                          uint32_t (*s_hist)[kTileDigits], uint64_t* s_wave64, uint64_t* s_base) {
+                                          uint32_t (*s_hist)[kTileDigits], uint64_t* s_wave64, uint32_t* s_visible,
+                                          uint64_t* s_base) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   // item k of lane l is element k*64 + l of the wave's contiguous slice
   const int64_t base = t * kThreads * ITEMS + (int64_t)wid * 64 * ITEMS + lane;
   uint32_t rid[ITEMS];
   TileRect rect[ITEMS];
 #pragma unroll
-  for (int k = 0; k < ITEMS; ++k) rid[k] = base + k * 64 < n ? a.sorted[base + k * 64] : 0u;
+  for (int k = 0; k < ITEMS; ++k) {
+    if constexpr (BY_RECORD) rid[k] = (uint32_t)(base + k * 64);
+    else rid[k] = base + k * 64 < n ? a.sorted[base + k * 64] : 0u;
+  }
   {
+    bool live[ITEMS];
+#pragma unroll
+    for (int k = 0; k < ITEMS; ++k) {
+      live[k] = base + k * 64 < n;
+      if constexpr (BY_RECORD) live[k] = live[k] && a.tiles_touched[rid[k]] > 0;
+    }
     uint4 w0[ITEMS];
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k)
-      w0[k] = base + k * 64 < n ? a.rec_words[(size_t)kRecordWords * rid[k]] : make_uint4(0u, 0u, 0u, 0u);
+      w0[k] = live[k] ? a.rec_words[(size_t)kRecordWords * rid[k]] : make_uint4(0u, 0u, 0u, 0u);
+    uint32_t visible = 0;
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
       rect[k] = tile_rect(a, w0[k]);
-      if (base + k * 64 >= n) rect[k].extent = 0u;
+      if (!live[k]) rect[k].extent = 0u;
+      visible += (uint32_t)__popcll(__ballot(live[k]));
+    }
+    if constexpr (BY_RECORD) {
+      if (lane == 0) s_visible[wid] = visible;
     }
   }
   // exclusive prefix of the tile counts in slice order; a count may pass 2^25 and 64 of them 2^31, so
@@ -263,6 +289,12 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
     const uint64_t ex = lookback64_wave(a.status, t, total, a.counts);
     if (lane == 0) {
       *s_base = ex;
+      if constexpr (BY_RECORD) {
+        uint32_t visible = 0;
+#pragma unroll
+        for (int w = 0; w < kThreads / 64; ++w) visible += s_visible[w];
+        s_visible[kThreads / 64] += visible;
+      }
       if (t == ntiles - 1) {
         a.counts[GS_COUNT_PAIRS] = (int64_t)(ex + total);
         if ((int64_t)(ex + total) > a.pair_cap) raise_flag(a.counts, GS_FLAG_PAIRS);
@@ -307,31 +339,43 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
   }
 }
 
-// The gather of one 16-byte word per visible record in depth order bounds it: a
+// Depth first, the gather of one 16-byte word per visible record in depth order bounds it: a
 // line of 128 B per record (437 MB for 4M records, 3.8 TB/s), ITEMS gathers of a
 // thread in flight.  Scan and emission in one kernel write the rectangles and
 // offsets nowhere: 4M records 117 us, where a depth pass that gathered and scanned
 // (118 against 52 for a plain one) and the emission (33) took 99 more than the
 // plain pass; what is won is the passes' uniform shape and three arrays.
+// In record order it moves half of that (264 MB) in the same time, 113 us for the 5.7M
+// records with these 4M among them: bound by the chain claim, load, load, scan, look back
+// of each of 2787 work-group tiles.  (Two tiles per claim make every look-back wait for a
+// whole tile before: 18 ms.  The histograms' adds are no part of it: counted by runs of
+// equal tiles, the same.)
+template <bool BY_RECORD>
 __global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
   __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
   __shared__ uint64_t s_wave64[kThreads / 64], s_base;
-  __shared__ uint32_t s_tile;
-  const int64_t n = count_clamped(a.counts, GS_COUNT_VISIBLE, a.cap);
-  const int items = emit_items(count_clamped(a.counts, GS_COUNT_RECORDS, a.cap));
+  __shared__ uint32_t s_tile, s_visible[kThreads / 64 + 1];  // (last: the work-group's sum)
+  const int64_t n_rec = count_clamped(a.counts, GS_COUNT_RECORDS, a.cap);
+  const int64_t n = BY_RECORD ? n_rec : count_clamped(a.counts, GS_COUNT_VISIBLE, a.cap);
+  const int items = emit_items(n_rec);
   const int64_t ntiles = (n + (int64_t)kThreads * items - 1) / ((int64_t)kThreads * items);
   if ((int64_t)blockIdx.x >= ntiles) return;
   for (int p = 0; p < a.passes; ++p)
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
+  if (threadIdx.x == 0) s_visible[kThreads / 64] = 0u;
   for (;;) {
     if (threadIdx.x == 0) s_tile = atomicAdd(a.tile_counter, 1u);
     __syncthreads();
     const int64_t t = s_tile;
     if (t >= ntiles) break;
-    if (items == 1) emit_tile<1>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
-    else if (items == 4) emit_tile<4>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
-    else emit_tile<kEmitMaxItems>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    if (items == 1) emit_tile<1, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
+    else if (items == 4) emit_tile<4, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
+    else emit_tile<kEmitMaxItems, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
     __syncthreads();
+  }
+  if constexpr (BY_RECORD) {
+    if (threadIdx.x == 0 && s_visible[kThreads / 64])
+      atomicAdd(&a.visible[blockIdx.x % kVisibleCopies], s_visible[kThreads / 64]);
   }
   const int copy = (int)(blockIdx.x % kTileHistCopies);
   uint32_t* h = copy == 0 ? a.hist : a.hist_extra + (int64_t)(copy - 1) * kTileHistWords;
@@ -361,11 +405,17 @@ __device__ __forceinline__ void emit_footprint(const EmitArgs& a, uint32_t i, ui
     }
   }
 }
+template <bool BY_RECORD>
 __global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
   __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
   const uint32_t nbig = a.big_count[0], nhuge = a.big_count[1];
-  // emit_kernel has finished (same stream): its partial histograms are final
+  // emit_kernel has finished (same stream): its partial histograms and counts are final
   if (blockIdx.x == 0) {
+    if (BY_RECORD && threadIdx.x == 0) {
+      int64_t visible = 0;
+      for (int c = 0; c < kVisibleCopies; ++c) visible += a.visible[c];
+      a.counts[GS_COUNT_VISIBLE] = visible;
+    }
     for (int i = threadIdx.x; i < a.passes * kTileDigits; i += kThreads) {
       uint32_t part[kTileHistCopies - 1];
 #pragma unroll
@@ -427,7 +477,7 @@ __global__ void ranges_kernel(const uint32_t* __restrict__ tiles, const int64_t*
 }
 
 // ---------------------------------------------------------------------------
-// 6. work queue for the persistent tile kernels: tiles ordered by decreasing
+// 7. work queue for the persistent tile kernels: tiles ordered by decreasing
 //    list length, bucketed by floor(log2(length)) (empty tiles last); the order
 //    inside a bucket is irrelevant because tiles are independent
 // ---------------------------------------------------------------------------
@@ -541,6 +591,24 @@ SortWs sort_ws_layout(char* base, int64_t rc, int64_t pc) {
   return w;
 }
 
+// Order of work: by tile (emit in record order, group by tile, sort each list by depth) or depth first (sort
+// the records, emit, group by tile).  By tile, the depth order costs a sort of every pair in its list, a few
+// instructions per pair up to 1024 and more beyond; depth first, five passes over the records, each a few
+// launch latencies at least.  Decided by what the host knows, the capacities (us of the whole binning, depth
+// first -> by tile, capacity per record 2 if not said):
+//   1M records, 1080p, 44 pairs a tile        145 ->  87     2.4M records, 352 a tile          200 -> 152
+//   1M records, 320x180, 2290 a tile          116 -> 101     2M records, 160x90, 5446 a tile   136 -> 127
+//   4096 records, 16 a record, 172 a tile      63 ->  42     4096 records, 98 a record         93 ->  73
+//   20000 records, 91 a record, 514 a tile    136 -> 160     70001 records, 9 a record, 3204   103 -> 124
+//   140002 records, 42 a record, 2641 a tile  250 -> 382
+// Lists that are longer than their mean suggests are sorted all the same: 1M records in far views, the longest
+// list 5532, 32862, 184409: 195 -> 201, 184 -> 200, 184 -> 415 (the frame's other kernels take 569 and 2616 in
+// the last two).
+bool lists_by_tile(int64_t rc, int64_t pc, int64_t n_tile_ids) {
+  const bool few = pc <= 4 * rc;
+  return pc <= (few ? 4096 : 512) * n_tile_ids && (few || pc <= (int64_t)1 << 20);
+}
+
 int tile_bits(int64_t n_ids) {
   int b = 0;
   while (((int64_t)1 << b) < n_ids) ++b;
@@ -590,44 +658,49 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   uint32_t* dhist_extra = w.fixed + kDepthExtraAt;
   const int trb = tdigit == 9 ? 9 : 8;               // digit bits of the pass's instance (a word per value)
   const int64_t prow = (int64_t)tpasses << trb;  // look-back words of a radix tile over all tile passes
+  const bool by_tile = lists_by_tile(record_capacity, pair_capacity, n_tile_ids);
   // 0. zero the counters, histograms, look-back words and ranges
   {
-    const ClearArgs c{w.fixed, kFixedWords, w.dstatus, w.estatus, w.pstatus, radix_tiles_bound(pair_capacity) * prow,
-                      tile_ranges, 2 * n_tile_ids};
-    const int64_t drt = radix_tiles_bound(record_capacity) * 4 * kRadix;
+    const ClearArgs c{w.fixed, kFixedWords, by_tile ? nullptr : w.dstatus, w.estatus, w.pstatus,
+                      radix_tiles_bound(pair_capacity) * prow, tile_ranges, 2 * n_tile_ids};
+    const int64_t drt = by_tile ? 0 : radix_tiles_bound(record_capacity) * 4 * kRadix;
     const int64_t most = drt > c.pstatus_words ? drt : c.pstatus_words;
     hipLaunchKernelGGL(clear_front_kernel, grid_for(most > kFixedWords ? most : kFixedWords), blk, 0, s, c, counts,
                        record_capacity);
   }
   GS_LAUNCH_CHECK();
-  // 1. histograms of the four depth digits
-  hipLaunchKernelGGL(depth_hist_kernel, grid_for((record_capacity + kHistItems - 1) / kHistItems), blk, 0, s,
-                     tiles_touched, depth_keys, record_capacity, counts, dhist, dhist_extra);
-  GS_LAUNCH_CHECK();
-  // 2. depth sort, 4 passes of 8 bits: selected records -> b -> a -> b -> a.  The first pass keeps
-  //    the visible records (index order within a digit) and writes counts[GS_COUNT_VISIBLE].  Each
-  //    pass adds the partial copies of its digit histogram.
-  auto depth_pass = [&](int p, const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout) {
-    return RadixPass{kin, vin, kout, vout, counts, p == 0 ? GS_COUNT_RECORDS : GS_COUNT_VISIBLE, GS_COUNT_RECORDS,
-                     record_capacity, 8 * p, 8, dhist + p * kRadix, dhist_extra + p * kRadix,
-                     kDepthHistCopies - 1, kDepthHistWords, w.dstatus + p * kRadix, (int64_t)4 * kRadix,
-                     counters + 1 + p, counts, tiles_touched};
-  };
-  const dim3 dgrid = radix_grid(record_capacity), rblk(kRadixThreads);
-  hipLaunchKernelGGL((radix_pass_kernel<8, true>), dgrid, rblk, 0, s,
-                     depth_pass(0, depth_keys, nullptr, w.dkeys_b, w.dvals_b));
-  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
-                     depth_pass(1, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
-  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
-                     depth_pass(2, w.dkeys_a, w.dvals_a, w.dkeys_b, w.dvals_b));
-  hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
-                     depth_pass(3, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
-  GS_LAUNCH_CHECK();
+  const dim3 rblk(kRadixThreads);
+  if (!by_tile) {
+    // 1. histograms of the four depth digits
+    hipLaunchKernelGGL(depth_hist_kernel, grid_for((record_capacity + kHistItems - 1) / kHistItems), blk, 0, s,
+                       tiles_touched, depth_keys, record_capacity, counts, dhist, dhist_extra);
+    GS_LAUNCH_CHECK();
+    // 2. depth sort, 4 passes of 8 bits: selected records -> b -> a -> b -> a.  The first pass keeps
+    //    the visible records (index order within a digit) and writes counts[GS_COUNT_VISIBLE].  Each
+    //    pass adds the partial copies of its digit histogram.
+    auto depth_pass = [&](int p, const uint32_t* kin, const uint32_t* vin, uint32_t* kout, uint32_t* vout) {
+      return RadixPass{kin, vin, kout, vout, counts, p == 0 ? GS_COUNT_RECORDS : GS_COUNT_VISIBLE, GS_COUNT_RECORDS,
+                       record_capacity, 8 * p, 8, dhist + p * kRadix, dhist_extra + p * kRadix,
+                       kDepthHistCopies - 1, kDepthHistWords, w.dstatus + p * kRadix, (int64_t)4 * kRadix,
+                       counters + 1 + p, counts, tiles_touched};
+    };
+    const dim3 dgrid = radix_grid(record_capacity);
+    hipLaunchKernelGGL((radix_pass_kernel<8, true>), dgrid, rblk, 0, s,
+                       depth_pass(0, depth_keys, nullptr, w.dkeys_b, w.dvals_b));
+    hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                       depth_pass(1, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
+    hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                       depth_pass(2, w.dkeys_a, w.dvals_a, w.dkeys_b, w.dvals_b));
+    hipLaunchKernelGGL((radix_pass_kernel<8, false>), dgrid, rblk, 0, s,
+                       depth_pass(3, w.dkeys_b, w.dvals_b, w.dkeys_a, w.dvals_a));
+    GS_LAUNCH_CHECK();
+  }
   // 3. emission (+ tile-digit histograms), into the buffer from which the last tile pass ends in the
   //    caller's arrays
   EmitArgs e{};
   e.rec_words = (const uint4*)records;
   e.sorted = w.dvals_a;
+  e.tiles_touched = tiles_touched;
   e.counts = counts;
   e.cap = record_capacity;
   e.pair_cap = pair_capacity;
@@ -646,9 +719,13 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   e.big_rec = w.big_rec;
   e.big_off = w.big_off;
   e.big_count = counters + 32;  // two
+  e.visible = counters + 48;
   const int64_t eg = emit_tiles_bound(record_capacity);
-  hipLaunchKernelGGL(emit_kernel, dim3((unsigned)(eg < 2048 ? eg : 2048)), blk, 0, s, e);
-  hipLaunchKernelGGL(emit_big_kernel, dim3(512), blk, 0, s, e);
+  const dim3 egrid((unsigned)(eg < 2048 ? eg : 2048));
+  if (by_tile) hipLaunchKernelGGL(emit_kernel<true>, egrid, blk, 0, s, e);
+  else hipLaunchKernelGGL(emit_kernel<false>, egrid, blk, 0, s, e);
+  if (by_tile) hipLaunchKernelGGL(emit_big_kernel<true>, dim3(512), blk, 0, s, e);
+  else hipLaunchKernelGGL(emit_big_kernel<false>, dim3(512), blk, 0, s, e);
   GS_LAUNCH_CHECK();
   // 4. tile passes
   uint32_t* kin = e.out_tiles;
@@ -670,7 +747,21 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   hipLaunchKernelGGL(ranges_kernel, dim3(2048), blk, 0, s, pair_tiles, counts, pair_capacity, n_tile_ids,
                      tile_ranges);
   GS_LAUNCH_CHECK();
-  // 6. work queue
+  // 6. depth order inside the lists
+  if (by_tile) {
+    // (the tile passes' look-back words are free by now: at least a word for every eight pairs of capacity,
+    // the chunks need four for every 1024)
+    const ListArgs l{tile_ranges, depth_keys, pair_records, w.precs_alt, pair_tiles, w.ptiles_alt,
+                     (uint2*)w.pstatus, counters + 40, n_tile_ids, (uint32_t)(record_capacity - 1)};
+    const int64_t lg = (n_tile_ids + 3) / 4;
+    hipLaunchKernelGGL(list_sort_kernel, dim3((unsigned)(lg < 65536 ? lg : 65536)), dim3(256), 0, s, l);
+    if (pair_capacity > kListWave) hipLaunchKernelGGL(list_chunk_kernel, dim3(256), rblk, 0, s, l);
+    int p = 0;
+    for (int64_t run = kListChunk; run < pair_capacity; run *= kListFan)
+      hipLaunchKernelGGL(list_merge_kernel, dim3(1024), dim3(256), 0, s, l, p++);
+    GS_LAUNCH_CHECK();
+  }
+  // 7. work queue
   if ((tuning->flags & GS_TUNE_WORK_QUEUE) && tile_queue) {
     uint32_t* qhist = w.fixed + kQueueAt;
     uint32_t* qcur = qhist + 40;
