@@ -15,7 +15,8 @@
 //                footprint, with the histograms of the tile digits
 //   4. passes    stable radix sort by tile id (ceil(bits / 9) passes)
 //   5. ranges    [start, end) of every tile
-// By tile.  Stages 1 and 2 fall away, stage 3 emits in record order, and
+// By tile.  Stages 1 and 2 fall away, stage 3 emits in record order (the zero fill in
+// front of it sums the records' tile counts, so there is no look-back), and
 //   6. lists     every list is sorted by (depth, record) for itself
 // Either way the result equals a sort by (tile, depth, record id).
 //
@@ -40,7 +41,6 @@ constexpr int kTileDigits = 512;        // words of one tile-digit histogram
 constexpr int kHistItems = 8;           // records per thread of the depth histogram
 constexpr uint32_t kBigFootprint = 16;    // records touching more tiles are emitted by a wave each,
 constexpr uint32_t kHugeFootprint = 512;  // with more than this by a work-group
-constexpr int kVisibleCopies = 8;
 // emit_kernel's work-groups all finish at about the same time and each adds its
 // tile-digit histogram to device memory, so a single copy would take ~2000
 // same-address atomics per word in a row.  They add into kTileHistCopies
@@ -78,27 +78,81 @@ __host__ __device__ constexpr int64_t emit_tiles_bound(int64_t n) {
 struct ClearArgs {
   uint32_t* fixed;
   int64_t fixed_words;
-  uint32_t* dstatus;  // [tile][4][256]; NULL: no depth passes
+  uint32_t* dstatus;  // [tile][4][256]
   uint64_t* estatus;  // [tile]
   uint32_t* pstatus;
   int64_t pstatus_words;
   uint32_t* ranges;
   int64_t range_words;
+  // by tile: pairs of every emission tile (into estatus) and, per group of tiles, pairs and visible records
+  const int32_t* tiles_touched;
+  uint64_t* group_pairs;
+  uint32_t* group_visible;
 };
-__global__ void clear_front_kernel(ClearArgs a, int64_t* counts, int64_t cap) {
+
+// Groups of emission tiles, at most kEmitGroups of equal size.
+constexpr int64_t kEmitGroups = 2048;
+__device__ __forceinline__ int64_t emit_group_tiles(int64_t ntiles) { return (ntiles + kEmitGroups - 1) / kEmitGroups; }
+
+// sum of x over the work-group, to every thread; s: a word per wave
+__device__ __forceinline__ uint64_t group_sum(uint64_t x, uint64_t* s) {
+#pragma unroll
+  for (int d = 32; d > 0; d >>= 1) x += (uint64_t)__shfl_xor((unsigned long long)x, d, 64);
+  if ((threadIdx.x & 63) == 0) s[threadIdx.x >> 6] = x;
+  __syncthreads();
+  uint64_t sum = 0;
+#pragma unroll
+  for (int w = 0; w < kThreads / 64; ++w) sum += s[w];
+  __syncthreads();
+  return sum;
+}
+
+// What the emission in record order needs to know of the records in front of a tile: read once here, beside
+// the zero fill, so that no emission tile waits for another.
+__device__ __forceinline__ void emit_sums(const ClearArgs& a, int64_t n, uint64_t* s) {
+  const int items = emit_items(n);
+  const int64_t ntiles = emit_tiles(n), per = emit_group_tiles(ntiles);
+  for (int64_t g = blockIdx.x; g * per < ntiles; g += gridDim.x) {
+    uint64_t pairs = 0, visible = 0;
+    for (int64_t t = g * per; t < (g + 1) * per && t < ntiles; ++t) {
+      uint64_t sum = 0;
+      for (int k = 0; k < items; ++k) {
+        const int64_t i = (t * items + k) * kThreads + threadIdx.x;
+        const int32_t c = i < n ? a.tiles_touched[i] : 0;
+        sum += c > 0 ? (uint64_t)c : 0ull;
+        visible += c > 0 ? 1ull : 0ull;
+      }
+      sum = group_sum(sum, s);
+      if (threadIdx.x == 0) a.estatus[t] = sum;
+      pairs += sum;
+    }
+    visible = group_sum(visible, s);
+    if (threadIdx.x == 0) {
+      a.group_pairs[g] = pairs;
+      a.group_visible[g] = (uint32_t)visible;
+    }
+  }
+}
+
+template <bool BY_TILE>
+__global__ void __launch_bounds__(kThreads) clear_front_kernel(ClearArgs a, int64_t* counts, int64_t cap) {
   const int64_t n = count_clamped(counts, GS_COUNT_RECORDS, cap);
-  const int64_t dwords = a.dstatus ? radix_tiles(n) * 4 * kRadix : 0, ewords = emit_tiles(n);
+  const int64_t dwords = BY_TILE ? 0 : radix_tiles(n) * 4 * kRadix, ewords = BY_TILE ? 0 : emit_tiles(n);
   const int64_t stride = (int64_t)gridDim.x * blockDim.x;
   const int64_t i0 = (int64_t)blockIdx.x * blockDim.x + threadIdx.x;
   if (i0 == 0) {
-    counts[GS_COUNT_VISIBLE] = 0;  // (the emission in record order adds to it)
-    counts[GS_COUNT_PAIRS] = 0;    // (no visible record: no emission tile writes it)
+    counts[GS_COUNT_VISIBLE] = 0;  // (no record: no tile writes them)
+    counts[GS_COUNT_PAIRS] = 0;
   }
   for (int64_t i = i0; i < a.fixed_words; i += stride) a.fixed[i] = 0u;
   for (int64_t i = i0; i < dwords; i += stride) a.dstatus[i] = 0u;
   for (int64_t i = i0; i < ewords; i += stride) a.estatus[i] = 0ull;
   for (int64_t i = i0; i < a.pstatus_words; i += stride) a.pstatus[i] = 0u;
   for (int64_t i = i0; i < a.range_words; i += stride) a.ranges[i] = 0u;
+  if constexpr (BY_TILE) {
+    __shared__ uint64_t s_sum[kThreads / 64];
+    emit_sums(a, n, s_sum);
+  }
 }
 
 // ---------------------------------------------------------------------------
@@ -204,7 +258,8 @@ struct EmitArgs {
   uint32_t* big_rec;             // records with many tiles and their first pair: a wave's from the front,
   uint32_t* big_off;             // a work-group's from the back ([cap])
   uint32_t* big_count;           // of each kind
-  uint32_t* visible;             // [kVisibleCopies] partial counts (emission in record order)
+  const uint64_t* group_pairs;   // emission in record order: see ClearArgs (the tiles' pairs are in `status`)
+  const uint32_t* group_visible;
 };
 
 // first tile id and extent in tiles (columns | rows << 16) of a record
@@ -230,38 +285,39 @@ __device__ __forceinline__ void count_tile(const EmitArgs& a, uint32_t (*s_hist)
 // scan, write.
 template <int ITEMS, bool BY_RECORD>
 __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t t, int64_t ntiles,
-                                          uint32_t (*s_hist)[kTileDigits], uint64_t* s_wave64, uint32_t* s_visible,
-                                          uint64_t* s_base) {
+                                          uint32_t (*s_hist)[kTileDigits], uint64_t* s_wave64, uint64_t* s_base) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   // item k of lane l is element k*64 + l of the wave's contiguous slice
   const int64_t base = t * kThreads * ITEMS + (int64_t)wid * 64 * ITEMS + lane;
-  uint32_t rid[ITEMS];
+  uint32_t rid[ITEMS], cnt[ITEMS];  // records and their tiles
   TileRect rect[ITEMS];
+  uint64_t front = 0;  // the thread's share of the pairs in front of the tile
+  if constexpr (BY_RECORD) {
+    const int64_t per = emit_group_tiles(ntiles), g = t / per;
+    for (int64_t i = threadIdx.x; i < g; i += kThreads) front += a.group_pairs[i];
+    for (int64_t i = g * per + threadIdx.x; i < t; i += kThreads) front += a.status[i];
+  }
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    if constexpr (BY_RECORD) rid[k] = (uint32_t)(base + k * 64);
-    else rid[k] = base + k * 64 < n ? a.sorted[base + k * 64] : 0u;
+    const int64_t at = base + k * 64;
+    if constexpr (BY_RECORD) {
+      rid[k] = (uint32_t)at;
+      cnt[k] = (uint32_t)max(at < n ? a.tiles_touched[at] : 0, 0);
+    } else {
+      rid[k] = at < n ? a.sorted[at] : 0u;
+    }
   }
   {
-    bool live[ITEMS];
-#pragma unroll
-    for (int k = 0; k < ITEMS; ++k) {
-      live[k] = base + k * 64 < n;
-      if constexpr (BY_RECORD) live[k] = live[k] && a.tiles_touched[rid[k]] > 0;
-    }
     uint4 w0[ITEMS];
 #pragma unroll
-    for (int k = 0; k < ITEMS; ++k)
-      w0[k] = live[k] ? a.rec_words[(size_t)kRecordWords * rid[k]] : make_uint4(0u, 0u, 0u, 0u);
-    uint32_t visible = 0;
+    for (int k = 0; k < ITEMS; ++k) {
+      const bool live = BY_RECORD ? cnt[k] > 0 : base + k * 64 < n;
+      w0[k] = live ? a.rec_words[(size_t)kRecordWords * rid[k]] : make_uint4(0u, 0u, 0u, 0u);
+    }
 #pragma unroll
     for (int k = 0; k < ITEMS; ++k) {
       rect[k] = tile_rect(a, w0[k]);
-      if (!live[k]) rect[k].extent = 0u;
-      visible += (uint32_t)__popcll(__ballot(live[k]));
-    }
-    if constexpr (BY_RECORD) {
-      if (lane == 0) s_visible[wid] = visible;
+      if constexpr (!BY_RECORD) cnt[k] = base + k * 64 < n ? rect[k].tiles() : 0u;
     }
   }
   // exclusive prefix of the tile counts in slice order; a count may pass 2^25 and 64 of them 2^31, so
@@ -269,7 +325,7 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
   uint64_t off[ITEMS], run = 0;
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const uint32_t c = rect[k].tiles();
+    const uint32_t c = cnt[k];
     uint64_t inc = (uint32_t)wave_incl_scan((int)(c & 0xFFFFu));
     if (__ballot(c > 0xFFFFu)) inc += (uint64_t)(uint32_t)wave_incl_scan((int)(c >> 16)) << 16;
     off[k] = run + inc - c;
@@ -285,30 +341,40 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
     before += w < wid ? v : 0ull;
     total += v;
   }
-  if (wid == 0) {
+  auto finish = [&](uint64_t ex) {  // the pairs up to the last tile
+    a.counts[GS_COUNT_PAIRS] = (int64_t)(ex + total);
+    if ((int64_t)(ex + total) > a.pair_cap) raise_flag(a.counts, GS_FLAG_PAIRS);
+  };
+  if constexpr (BY_RECORD) {
+    __syncthreads();
+    const uint64_t ex = group_sum(front, s_wave64);
+    if (threadIdx.x == 0) *s_base = ex;
+    if (t == ntiles - 1) {
+      const int64_t per = emit_group_tiles(ntiles);
+      uint64_t visible = 0;
+      for (int64_t i = threadIdx.x; i * per < ntiles; i += kThreads) visible += a.group_visible[i];
+      visible = group_sum(visible, s_wave64);
+      if (threadIdx.x == 0) {
+        finish(ex);
+        a.counts[GS_COUNT_VISIBLE] = (int64_t)visible;
+      }
+    }
+  } else if (wid == 0) {
     const uint64_t ex = lookback64_wave(a.status, t, total, a.counts);
     if (lane == 0) {
       *s_base = ex;
-      if constexpr (BY_RECORD) {
-        uint32_t visible = 0;
-#pragma unroll
-        for (int w = 0; w < kThreads / 64; ++w) visible += s_visible[w];
-        s_visible[kThreads / 64] += visible;
-      }
-      if (t == ntiles - 1) {
-        a.counts[GS_COUNT_PAIRS] = (int64_t)(ex + total);
-        if ((int64_t)(ex + total) > a.pair_cap) raise_flag(a.counts, GS_FLAG_PAIRS);
-      }
+      if (t == ntiles - 1) finish(ex);
     }
   }
   __syncthreads();
   const uint64_t tile_base = *s_base + before;
 #pragma unroll
   for (int k = 0; k < ITEMS; ++k) {
-    const TileRect r = rect[k];  // (no tiles past the end)
+    const TileRect r = rect[k];
+    const uint32_t c = cnt[k];
     int64_t o = (int64_t)(tile_base + off[k]);
-    const bool many = r.tiles() > kBigFootprint;
-    const bool huge = r.tiles() > kHugeFootprint;
+    const bool many = c > kBigFootprint;
+    const bool huge = c > kHugeFootprint;
     const bool big = many && !huge && o < a.pair_cap;  // left to emit_big_kernel
     if (huge && o < a.pair_cap) {
       const uint32_t at = (uint32_t)a.cap - 1u - atomicAdd(a.big_count + 1, 1u);
@@ -326,16 +392,17 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
       }
     }
     if (many) continue;
-    for (uint32_t ty = 0; ty < r.extent >> 16; ++ty)
-      for (uint32_t tx = 0; tx < r.columns(); ++tx) {
-        if (o < a.pair_cap) {
-          const uint32_t key = r.first + ty * (uint32_t)a.tiles_x + tx;
-          a.out_tiles[o] = key;
-          a.out_records[o] = rid[k];
-          count_tile(a, s_hist, key);
-        }
-        ++o;
+    uint32_t key = r.first, column = 0;
+    for (uint32_t q = 0; q < c; ++q, ++o) {
+      if (o < a.pair_cap) {
+        a.out_tiles[o] = key;
+        a.out_records[o] = rid[k];
+        count_tile(a, s_hist, key);
       }
+      const bool wrap = ++column == r.columns();
+      key += wrap ? (uint32_t)a.tiles_x - r.columns() + 1u : 1u;
+      column = wrap ? 0u : column;
+    }
   }
 }
 
@@ -345,16 +412,16 @@ __device__ __forceinline__ void emit_tile(const EmitArgs& a, int64_t n, int64_t 
 // offsets nowhere: 4M records 117 us, where a depth pass that gathered and scanned
 // (118 against 52 for a plain one) and the emission (33) took 99 more than the
 // plain pass; what is won is the passes' uniform shape and three arrays.
-// In record order it moves half of that (264 MB) in the same time, 113 us for the 5.7M
-// records with these 4M among them: bound by the chain claim, load, load, scan, look back
-// of each of 2787 work-group tiles.  (Two tiles per claim make every look-back wait for a
-// whole tile before: 18 ms.  The histograms' adds are no part of it: counted by runs of
-// equal tiles, the same.)
+// In record order it moves half of that (264 MB for the 5.7M records with these 4M among them) and no tile
+// waits for another: the pairs in front of a tile are sums the zero fill has made of the tile counts.
+// 75 us and 10 more in the zero fill, where claim and look-back of 2787 tiles took 113 (two tiles per claim
+// make every look-back wait for a whole tile before: 18 ms); 32M records 309 and 53 against 434; 675K 18
+// and 1 against 26.  (The histograms' adds are no part of it: counted by runs of equal tiles, the same.)
 template <bool BY_RECORD>
 __global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
   __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
   __shared__ uint64_t s_wave64[kThreads / 64], s_base;
-  __shared__ uint32_t s_tile, s_visible[kThreads / 64 + 1];  // (last: the work-group's sum)
+  __shared__ uint32_t s_tile;
   const int64_t n_rec = count_clamped(a.counts, GS_COUNT_RECORDS, a.cap);
   const int64_t n = BY_RECORD ? n_rec : count_clamped(a.counts, GS_COUNT_VISIBLE, a.cap);
   const int items = emit_items(n_rec);
@@ -362,20 +429,17 @@ __global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
   if ((int64_t)blockIdx.x >= ntiles) return;
   for (int p = 0; p < a.passes; ++p)
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
-  if (threadIdx.x == 0) s_visible[kThreads / 64] = 0u;
-  for (;;) {
-    if (threadIdx.x == 0) s_tile = atomicAdd(a.tile_counter, 1u);
-    __syncthreads();
-    const int64_t t = s_tile;
+  for (int64_t t = blockIdx.x;; t += gridDim.x) {
+    if constexpr (!BY_RECORD) {  // (a look-back waits for the tiles in front: taken in launch order)
+      if (threadIdx.x == 0) s_tile = atomicAdd(a.tile_counter, 1u);
+      __syncthreads();
+      t = s_tile;
+    }
     if (t >= ntiles) break;
-    if (items == 1) emit_tile<1, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
-    else if (items == 4) emit_tile<4, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
-    else emit_tile<kEmitMaxItems, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, s_visible, &s_base);
+    if (items == 1) emit_tile<1, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    else if (items == 4) emit_tile<4, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
+    else emit_tile<kEmitMaxItems, BY_RECORD>(a, n, t, ntiles, s_hist, s_wave64, &s_base);
     __syncthreads();
-  }
-  if constexpr (BY_RECORD) {
-    if (threadIdx.x == 0 && s_visible[kThreads / 64])
-      atomicAdd(&a.visible[blockIdx.x % kVisibleCopies], s_visible[kThreads / 64]);
   }
   const int copy = (int)(blockIdx.x % kTileHistCopies);
   uint32_t* h = copy == 0 ? a.hist : a.hist_extra + (int64_t)(copy - 1) * kTileHistWords;
@@ -389,12 +453,14 @@ __global__ void __launch_bounds__(kThreads) emit_kernel(EmitArgs a) {
 // Records whose footprint covers many tiles (a Gaussian close to the camera), written to the same slots
 // (row-major tile order) the serial loop would use: a wave per record up to kHugeFootprint tiles, a
 // work-group beyond.  2 x 70001 records of 37 tiles: 263 us with a work-group for every record.
+template <bool BY_RECORD>
 __device__ __forceinline__ void emit_footprint(const EmitArgs& a, uint32_t i, uint32_t first, uint32_t step,
                                                uint32_t (*s_hist)[kTileDigits]) {
   const uint32_t rid = a.big_rec[i];
   const TileRect r = tile_rect(a, a.rec_words[(size_t)kRecordWords * rid]);
   const int64_t o0 = a.big_off[i];
-  for (uint32_t q = first; q < r.tiles(); q += step) {
+  const uint32_t c = BY_RECORD ? (uint32_t)a.tiles_touched[rid] : r.tiles();
+  for (uint32_t q = first; q < c; q += step) {
     const int64_t o = o0 + q;
     if (o < a.pair_cap) {
       const uint32_t ty = q / r.columns(), tx = q % r.columns();
@@ -409,13 +475,8 @@ template <bool BY_RECORD>
 __global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
   __shared__ uint32_t s_hist[kMaxTilePasses][kTileDigits];
   const uint32_t nbig = a.big_count[0], nhuge = a.big_count[1];
-  // emit_kernel has finished (same stream): its partial histograms and counts are final
+  // emit_kernel has finished (same stream): its partial histograms are final
   if (blockIdx.x == 0) {
-    if (BY_RECORD && threadIdx.x == 0) {
-      int64_t visible = 0;
-      for (int c = 0; c < kVisibleCopies; ++c) visible += a.visible[c];
-      a.counts[GS_COUNT_VISIBLE] = visible;
-    }
     for (int i = threadIdx.x; i < a.passes * kTileDigits; i += kThreads) {
       uint32_t part[kTileHistCopies - 1];
 #pragma unroll
@@ -432,9 +493,9 @@ __global__ void __launch_bounds__(kThreads) emit_big_kernel(EmitArgs a) {
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) s_hist[p][i] = 0u;
   __syncthreads();
   for (uint32_t k = blockIdx.x * kWaves + (threadIdx.x >> 6); k < nbig; k += gridDim.x * kWaves)
-    emit_footprint(a, k, threadIdx.x & 63, 64, s_hist);
+    emit_footprint<BY_RECORD>(a, k, threadIdx.x & 63, 64, s_hist);
   for (uint32_t k = blockIdx.x; k < nhuge; k += gridDim.x)
-    emit_footprint(a, (uint32_t)a.cap - 1u - k, threadIdx.x, kThreads, s_hist);
+    emit_footprint<BY_RECORD>(a, (uint32_t)a.cap - 1u - k, threadIdx.x, kThreads, s_hist);
   __syncthreads();
   for (int p = 0; p < a.passes; ++p)
     for (int i = threadIdx.x; i < kTileDigits; i += kThreads) {
@@ -548,6 +609,7 @@ constexpr int64_t kQueueAt = kTileHistAt + kTileHistWords;
 constexpr int64_t kTileExtraAt = kQueueAt + kQueueWords;
 constexpr int64_t kDepthExtraAt = kTileExtraAt + (kTileHistCopies - 1) * kTileHistWords;
 constexpr int64_t kFixedWords = kDepthExtraAt + (kDepthHistCopies - 1) * kDepthHistWords;
+static_assert(kDepthExtraAt % 2 == 0 && 3 * kEmitGroups <= (kDepthHistCopies - 1) * kDepthHistWords, "the groups' sums fit");
 
 struct SortWs {
   uint32_t* dkeys_a;     // [rc]
@@ -659,14 +721,24 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   const int trb = tdigit == 9 ? 9 : 8;               // digit bits of the pass's instance (a word per value)
   const int64_t prow = (int64_t)tpasses << trb;  // look-back words of a radix tile over all tile passes
   const bool by_tile = lists_by_tile(record_capacity, pair_capacity, n_tile_ids);
-  // 0. zero the counters, histograms, look-back words and ranges
+  uint64_t* group_pairs = (uint64_t*)(w.fixed + kDepthExtraAt);
+  uint32_t* group_visible = (uint32_t*)(group_pairs + kEmitGroups);
+  // 0. zero the counters, histograms, look-back words and ranges; by tile: the emission tiles' sums
   {
-    const ClearArgs c{w.fixed, kFixedWords, by_tile ? nullptr : w.dstatus, w.estatus, w.pstatus,
-                      radix_tiles_bound(pair_capacity) * prow, tile_ranges, 2 * n_tile_ids};
+    // (by tile, the partial depth histograms' words hold the groups' sums)
+    const ClearArgs c{w.fixed, by_tile ? kDepthExtraAt : kFixedWords, w.dstatus, w.estatus, w.pstatus,
+                      radix_tiles_bound(pair_capacity) * prow, tile_ranges, 2 * n_tile_ids,
+                      tiles_touched, group_pairs, group_visible};
     const int64_t drt = by_tile ? 0 : radix_tiles_bound(record_capacity) * 4 * kRadix;
     const int64_t most = drt > c.pstatus_words ? drt : c.pstatus_words;
-    hipLaunchKernelGGL(clear_front_kernel, grid_for(most > kFixedWords ? most : kFixedWords), blk, 0, s, c, counts,
-                       record_capacity);
+    dim3 grid = grid_for(most > kFixedWords ? most : kFixedWords);
+    if (by_tile) {
+      const int64_t tiles = emit_tiles_bound(record_capacity), groups = tiles < kEmitGroups ? tiles : kEmitGroups;
+      if (grid.x < (unsigned)groups) grid.x = (unsigned)groups;
+      hipLaunchKernelGGL(clear_front_kernel<true>, grid, blk, 0, s, c, counts, record_capacity);
+    } else {
+      hipLaunchKernelGGL(clear_front_kernel<false>, grid, blk, 0, s, c, counts, record_capacity);
+    }
   }
   GS_LAUNCH_CHECK();
   const dim3 rblk(kRadixThreads);
@@ -719,7 +791,8 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   e.big_rec = w.big_rec;
   e.big_off = w.big_off;
   e.big_count = counters + 32;  // two
-  e.visible = counters + 48;
+  e.group_pairs = group_pairs;
+  e.group_visible = group_visible;
   const int64_t eg = emit_tiles_bound(record_capacity);
   const dim3 egrid((unsigned)(eg < 2048 ? eg : 2048));
   if (by_tile) hipLaunchKernelGGL(emit_kernel<true>, egrid, blk, 0, s, e);
