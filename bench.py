@@ -46,8 +46,9 @@ ROOT = os.path.dirname(os.path.abspath(__file__))
 sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
-BIN_SORT_KERNELS = ("clear_front, depth_hist, radix_pass<compact>, 2 radix_pass, radix_pass<pairs>, emit, emit_big, "
-                    "2 tile radix_pass, ranges")
+BIN_SORT_KERNELS = ("clear_front, emit, emit_big, 2 tile radix_pass, ranges, list_sort, list_chunk, list_merge (depth "
+                    "first, where lists are long: clear_front, depth_hist, radix_pass<compact>, 3 radix_pass, emit, "
+                    "emit_big, 2 tile radix_pass, ranges)")
 REFINE_KERNELS = "refine_clear, refine_test, refine_scan, refine_expand"
 # published FP32 vector peak of MI355X (packed FP32); the library is compiled
 # without packed-FP32 instructions, whose ceiling is half of it: 256 CUs x 64 FMA
@@ -58,14 +59,14 @@ VALU_FP32_UNPACKED_TFLOPS = 78.6
 # compositing: 14 FP32 operations and one exponential, counted as 15
 FLOPS_PER_EVAL = 15
 
-# HBM bytes per launch (the binning: its 11 launches; the refinement: its 4) from rocprofv3 FETCH_SIZE /
+# HBM bytes per launch (the binning: all its launches; the refinement: its 4) from rocprofv3 FETCH_SIZE /
 # WRITE_SIZE runs of `bench.py --stages-only` scaled by a 512 MiB copy, for launches of the given views
 # per call, valid for the kernel sources with the given fingerprint only
 MEASURED_TRAFFIC = {
     "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "2f2db44ee46c9077", 8, 1411.33e6),
     "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "6ead4438b5cf0fa1", 8,
                                      667.98e6),
-    "bin_sort": (("sort.hip", "radix.h", "scan.h", "gs_common.h"), "7c172e1976d40684", 8, 1281.02e6),
+    "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "7c172e1976d40684", 8, 1281.02e6),
     "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "d204861f3281dbaa", 8, 35.5e6),
 }
 
@@ -314,6 +315,10 @@ def workload_lod(args, torch, gs, render, synth):
             if key != (best.tile_w, best.tile_h):
                 del frames[key]
     tun = frame.tuning
+    if (tun.tile_w, tun.tile_h) != (16, 16):  # the pairs counted above are those of 16 x 16 tiles
+        for v in range(V):
+            render.render_frame(scene, frame, cam_slot[v], thresholds=thresholds, refine=refine)
+            n_pairs[v] = frame.host_counts()["pairs"]
     tuning_desc = dict(tile_w=tun.tile_w, tile_h=tun.tile_h, batch=tun.batch, flags=tun.flags)
 
     # ---- stages timed with HIP events on the stream they run on, in the call shape of
