@@ -63,11 +63,11 @@ FLOPS_PER_EVAL = 15
 # WRITE_SIZE runs of `bench.py --stages-only` scaled by a 512 MiB copy, for launches of the given views
 # per call, valid for the kernel sources with the given fingerprint only
 MEASURED_TRAFFIC = {
-    "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "2f2db44ee46c9077", 8, 1411.33e6),
-    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "6ead4438b5cf0fa1", 8,
-                                     667.98e6),
-    "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "7c172e1976d40684", 8, 1281.02e6),
-    "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "d204861f3281dbaa", 8, 35.5e6),
+    "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "d6892895bda729d6", 8, 1412.2e6),
+    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "1b5721f4de488a40", 8,
+                                     875.0e6),
+    "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "b3a2d8a78e9dbee4", 8, 669.6e6),
+    "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "c58f5543192a3eee", 8, 35.4e6),
 }
 
 

@@ -2,7 +2,7 @@
 //
 // Sorts of up to 1024 entries run in one wave's registers (bitonic merges, E entries a lane, no LDS and
 // no barrier).  Longer lists are cut into chunks of 16384 that a work-group sorts (stable radix passes over
-// the depth, in LDS), and list_merge_kernel merges up to 64 sorted runs at a time.
+// the depth, in LDS), and list_merge_kernel merges up to 256 sorted runs at a time.
 // Keys are (depth, record), unique, so the result does not depend on the network.
 #pragma once
 
@@ -15,7 +15,7 @@ namespace {
 
 constexpr int kListWave = 1024;   // entries a wave sorts
 constexpr int kListChunk = kRadixThreads * kRadixMaxItems;  // entries a work-group sorts
-constexpr int kListFan = 64;      // runs merged at a time
+constexpr int kListFan = 256;     // runs merged at a time
 
 // value of the lane whose number differs in the bits of M
 template <int M>
@@ -258,13 +258,14 @@ __global__ void __launch_bounds__(kRadixThreads) list_chunk_kernel(ListArgs a) {
 // Merge p: runs of kListChunk * kListFan^p entries, up to kListFan of them into one.  An entry's place is
 // its place in its run plus, for every other run of the group, the entries there that come before it
 // (binary searches).  Lists that are done by then are left.  Bound by the searches' loads; the depths are
-// kept beside the records so that a probe's two loads do not depend on each other (a list of 184409:
-// 648 -> 415 us for the binning).
-__global__ void __launch_bounds__(256) list_merge_kernel(ListArgs a, int p) {
+// kept beside the records so that a probe's two loads do not depend on each other (binning of a list of
+// 184409: 648 -> 415 us), and an entry has a thread of its own (323 us; four entries a thread 415).  256 runs
+// at a time: a launch that finds nothing to do costs 4-5 us of a frame, and one merge covers 4M pairs.
+__global__ void __launch_bounds__(1024) list_merge_kernel(ListArgs a, int p) {
   const uint32_t nc = *a.n_chunks;  // (at most 2^30 / 512)
   uint64_t run = kListChunk;
   for (int q = 0; q < p; ++q) run *= kListFan;
-  constexpr uint32_t kPart = 1024, kParts = kListChunk / kPart;  // entries of a work-group
+  constexpr uint32_t kPart = 1024, kParts = kListChunk / kPart;  // an entry per thread
   for (uint32_t i = blockIdx.x; i < nc * kParts; i += gridDim.x) {
     const uint2 c = a.chunks[i / kParts];
     const uint32_t start = a.ranges[2 * (int64_t)c.x], len = a.ranges[2 * (int64_t)c.x + 1] - start;
@@ -276,7 +277,7 @@ __global__ void __launch_bounds__(256) list_merge_kernel(ListArgs a, int p) {
     uint32_t* dst = (into_list ? a.list : a.alt) + start;
     uint32_t* dst_keys = (into_list ? a.list_keys : a.alt_keys) + start;
     const uint32_t first_at = c.y * (uint32_t)kListChunk + i % kParts * kPart, end = min(len, first_at + kPart);
-    for (uint32_t at = first_at + threadIdx.x; at < end; at += 256) {
+    for (uint32_t at = first_at + threadIdx.x; at < end; at += kPart) {
       const uint32_t rec = src[at], depth = src_keys[at];
       const uint64_t key = ((uint64_t)depth << 32) | rec;
       const uint64_t own = at / run, first = own / kListFan * kListFan;

@@ -664,7 +664,7 @@ SortWs sort_ws_layout(char* base, int64_t rc, int64_t pc) {
 //   20000 records, 91 a record, 514 a tile    136 -> 160     70001 records, 9 a record, 3204   103 -> 124
 //   140002 records, 42 a record, 2641 a tile  250 -> 382
 // Lists that are longer than their mean suggests are sorted all the same: 1M records in far views, the longest
-// list 5532, 32862, 184409: 195 -> 201, 184 -> 200, 184 -> 415 (the frame's other kernels take 569 and 2616 in
+// list 5532, 32862, 184409: 195 -> 194, 184 -> 185, 184 -> 323 (the frame's other kernels take 569 and 2616 in
 // the last two).
 bool lists_by_tile(int64_t rc, int64_t pc, int64_t n_tile_ids) {
   const bool few = pc <= 4 * rc;
@@ -831,7 +831,7 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
     if (pair_capacity > kListWave) hipLaunchKernelGGL(list_chunk_kernel, dim3(256), rblk, 0, s, l);
     int p = 0;
     for (int64_t run = kListChunk; run < pair_capacity; run *= kListFan)
-      hipLaunchKernelGGL(list_merge_kernel, dim3(1024), dim3(256), 0, s, l, p++);
+      hipLaunchKernelGGL(list_merge_kernel, dim3(256), dim3(1024), 0, s, l, p++);
     GS_LAUNCH_CHECK();
   }
   // 7. work queue

@@ -95,7 +95,7 @@ def test_long_lists(hot, depths):
 
 
 def test_list_of_two_merges():
-    _check(1_150_000, 640, 640, 1, 2, 1 << 22, 1, hot=1_100_000, culled=0.0)
+    _check(4_250_000, 640, 640, 1, 2, 1 << 22, 1, hot=4_200_000, culled=0.0)
 
 
 @pytest.mark.parametrize("n,cap_factor", [(20_000, 0.5), (20_000, 0.999), (600_000, 0.7)])
