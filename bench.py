@@ -66,7 +66,7 @@ MEASURED_TRAFFIC = {
     "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "d6892895bda729d6", 8, 1412.2e6),
     "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "1b5721f4de488a40", 8,
                                      875.0e6),
-    "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "b3a2d8a78e9dbee4", 8, 669.6e6),
+    "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "cafb6a7db1a98f11", 8, 670.4e6),
     "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "c58f5543192a3eee", 8, 35.4e6),
 }
 
