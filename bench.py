@@ -63,11 +63,11 @@ FLOPS_PER_EVAL = 15
 # WRITE_SIZE runs of `bench.py --stages-only` scaled by a 512 MiB copy, for launches of the given views
 # per call, valid for the kernel sources with the given fingerprint only
 MEASURED_TRAFFIC = {
-    "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "d6892895bda729d6", 8, 1412.2e6),
-    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "1b5721f4de488a40", 8,
+    "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "90384a20886c9f1f", 8, 1412.2e6),
+    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "a7395ca9900df927", 8,
                                      875.0e6),
     "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "cafb6a7db1a98f11", 8, 670.4e6),
-    "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "c58f5543192a3eee", 8, 35.4e6),
+    "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "72c0a6ebfc2a601a", 8, 35.4e6),
 }
 
 

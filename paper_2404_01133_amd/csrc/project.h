@@ -91,14 +91,15 @@ __device__ __forceinline__ void sh_colour(double x, double y, double z, int deg,
   term(15, -kSH3a * (x * (xx - 3.0 * yy)));
 }
 
-// Coefficient planes FIRST.. of the bands up to deg, 0 beyond
-template <bool HALF, int FIRST = 0>
+// Coefficient planes of the bands up to deg, 0 beyond (one branch per band: a branch per load makes the
+// loads wait for each other)
+template <bool HALF>
 __device__ __forceinline__ void load_sh(const LevelPtrs& L, int64_t gi, int deg, float (&f)[48]) {
   auto load = [&](int i) { f[i] = attr<HALF>(L.sh, (int64_t)i * L.n + gi); };
 #pragma unroll
-  for (int i = FIRST; i < 48; ++i) f[i] = 0.0f;
+  for (int i = 0; i < 48; ++i) f[i] = 0.0f;
 #pragma unroll
-  for (int i = FIRST; i < 3; ++i) load(i);
+  for (int i = 0; i < 3; ++i) load(i);
   if (deg >= 1) {
 #pragma unroll
     for (int i = 3; i < 12; ++i) load(i);
