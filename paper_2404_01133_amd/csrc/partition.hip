@@ -177,17 +177,20 @@ __global__ void part_cells_kernel(int32_t nx, int32_t ny, double* __restrict__ c
 // Measured, 5M Gaussians in 36 blocks (59 planes, 2.36 GB to move): in natural
 // order 4.06 ms; ordered by tiles of 256 to 1024 with a tile per work-group 1.15 ms,
 // whatever the tile and the planes per launch row (each 4-byte load filled a line
-// of its CU's cache: 38 GB from L2); with sixteen wave tiles per work-group see the
-// figure at gather_kernel.
+// of its CU's cache: 38 GB from L2); with groups of tiles see gather_kernel.
 // ---------------------------------------------------------------------------
 constexpr int kGatherTile = 64;
+constexpr int kGatherThreads = 512;
 constexpr int kGatherPerWave = 8;                    // tiles of a wave
-constexpr int kGatherGroup = 4 * kGatherPerWave;     // tiles of a work-group
+constexpr int kGatherGroup = kGatherThreads / 64 * kGatherPerWave;  // tiles of a work-group
+constexpr int kGatherWindow = 8192;                  // source words of a plane staged in LDS
 constexpr int kGatherBuckets = 16384;
-constexpr int kGatherPlanes = 4;  // planes per launch row
+constexpr int kGatherPlanes = 15;  // planes per launch row at most
 constexpr int kXcds = 8;
-// below this the source planes stay in cache whatever the order
-constexpr int64_t kGatherOrdered = (int64_t)1 << 18;
+// Below this the source planes stay in cache whatever the order, and the order's launches cost more than
+// it wins: natural -> by stretches, 262144 Gaussians in random order 99 -> 150 us, in 36 blocks 81 -> 63; 700000
+// 593 -> 481 and 435 -> 118 (already in order 98 -> 103)
+constexpr int64_t kGatherOrdered = (int64_t)1 << 19;
 
 struct GatherArgs {
   const float* src[5];
@@ -195,9 +198,9 @@ struct GatherArgs {
   int comps[5];
   int64_t n_src, n;
   const uint32_t* perm;
-  const uint32_t* order;  // tiles by first source index, or NULL: natural order
+  const uint32_t* order;  // tiles by first source index
   int64_t n_tiles;
-  int planes;
+  int planes, row;  // planes, planes per launch row
 
   __device__ __forceinline__ void plane(int c, const float*& s, float*& d) const {
     int a = 0;
@@ -255,36 +258,106 @@ __host__ __device__ constexpr int64_t gather_order_tiles(int64_t n_tiles) {
   return (n_tiles + kGatherBuckets + kGatherTile - 1) / kGatherTile;
 }
 
-// kGatherGroup tiles per work-group, kGatherPlanes planes per launch row.
-__global__ void __launch_bounds__(256) gather_kernel(GatherArgs a) {
-  const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+// kGatherGroup tiles per work-group, a.row planes per launch row.  In the order above the tiles of a
+// group read one stretch of the source, a few times the group's own length: it is staged in LDS by whole
+// lines and gathered there; what lies beyond (tiles of sparse blocks, permutations without runs) is read from
+// memory.  Read from memory one word per lane, each load took a cycle per lane in the CU's cache (64 lines):
+// 861 us for 5M Gaussians in 36 blocks; from the window 565 (2.36 GB, 4.2 TB/s; with windows of 12288 and 16384
+// words 600 and 668, 128 tiles a work-group 670, 32 tiles 711, 8 planes a row 586).
+__global__ void __launch_bounds__(kGatherThreads) gather_kernel(GatherArgs a) {
+  constexpr int kPer = kGatherWindow / kGatherThreads;
+  __shared__ float s_win[kGatherWindow];
+  __shared__ uint32_t s_lo, s_hi;
+  const int lane = threadIdx.x & 63;
+  const int wid = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
   const int64_t groups = (a.n_tiles + kGatherGroup - 1) / kGatherGroup;
   const int64_t eighth = (groups + kXcds - 1) / kXcds;
   const int64_t p = (int64_t)(blockIdx.x % kXcds) * eighth + blockIdx.x / kXcds;
   if (p >= groups) return;
-  int64_t k[kGatherPerWave];
-  uint32_t idx[kGatherPerWave];
-  bool last[kGatherPerWave];  // the tile's part of the last plane is gathered here
+  if (threadIdx.x == 0) {
+    s_lo = 0xFFFFFFFFu;
+    s_hi = 0u;
+  }
+  uint32_t tile[kGatherPerWave], idx[kGatherPerWave];  // (tile: the wave's)
+  uint32_t live = 0;  // bit i: the lane has an element of tile i
 #pragma unroll
   for (int i = 0; i < kGatherPerWave; ++i) {
-    const int64_t q = p * kGatherGroup + i * 4 + wid;  // neighbours in the order by different waves
-    const int64_t t = q >= a.n_tiles ? a.n_tiles : a.order ? (int64_t)a.order[q] : q;
-    k[i] = t * kGatherTile + lane;
-    idx[i] = k[i] < a.n ? a.perm[k[i]] : 0u;
-    last[i] = !a.order || t >= gather_order_tiles(a.n_tiles);  // (elsewhere the order is still read)
+    const int64_t q = p * kGatherGroup + i * (kGatherThreads / 64) + wid;  // neighbours in the order by different waves
+    const uint32_t t = q >= a.n_tiles ? (uint32_t)a.n_tiles : a.order[q];
+    tile[i] = (uint32_t)__builtin_amdgcn_readfirstlane((int)t);
+    const int64_t k = (int64_t)tile[i] * kGatherTile + lane;
+    idx[i] = k < a.n ? a.perm[k] : 0u;
+    live |= (k < a.n ? 1u : 0u) << i;
   }
-  const int p0 = (int)blockIdx.y * kGatherPlanes;
-  const int p1 = p0 + kGatherPlanes < a.planes ? p0 + kGatherPlanes : a.planes;
+  __syncthreads();
+  uint32_t lo = 0xFFFFFFFFu, hi = 0u;
+#pragma unroll
+  for (int i = 0; i < kGatherPerWave; ++i) lo = (live >> i & 1u) ? min(lo, idx[i]) : lo;
+  atomicMin(&s_lo, lo);
+  __syncthreads();
+  lo = s_lo;
+  uint32_t near = 0;  // bit i: element i is in the window
+#pragma unroll
+  for (int i = 0; i < kGatherPerWave; ++i) {
+    const bool in = (live >> i & 1u) && idx[i] - lo < (uint32_t)kGatherWindow;
+    near |= (in ? 1u : 0u) << i;
+    hi = in ? max(hi, idx[i] - lo + 1u) : hi;
+  }
+  atomicMax(&s_hi, hi);
+  __syncthreads();
+  const int win = __builtin_amdgcn_readfirstlane((int)s_hi);  // words of the window in use
+  const uint32_t far = live & ~near;
+  const int p0 = (int)blockIdx.y * a.row;
+  const int p1 = p0 + a.row < a.planes ? p0 + a.row : a.planes;
   for (int c = p0; c < p1; ++c) {
     const float* s;
     float* d;
     a.plane(c, s, d);
+    if (win > 0) {
+      const float* w = s + lo;
+#pragma unroll
+      for (int h = 0; h < kPer; h += 8) {
+        if (h * kGatherThreads >= win) break;
+        float x[8];
+#pragma unroll
+        for (int i = 0; i < 8; ++i) {
+          const int j = (h + i) * kGatherThreads + (int)threadIdx.x;
+          x[i] = j < win ? w[j] : 0.0f;
+        }
+#pragma unroll
+        for (int i = 0; i < 8; ++i) s_win[(h + i) * kGatherThreads + (int)threadIdx.x] = x[i];
+      }
+      __syncthreads();
+    }
     float v[kGatherPerWave];
 #pragma unroll
-    for (int i = 0; i < kGatherPerWave; ++i) v[i] = k[i] < a.n ? s[idx[i]] : 0.0f;
+    for (int i = 0; i < kGatherPerWave; ++i) v[i] = s_win[near >> i & 1u ? idx[i] - lo : 0u];
+    if (__ballot(far != 0u)) {
+#pragma unroll
+      for (int i = 0; i < kGatherPerWave; ++i)
+        if (far >> i & 1u) v[i] = s[idx[i]];
+    }
 #pragma unroll
     for (int i = 0; i < kGatherPerWave; ++i)
-      if (k[i] < a.n && (c < a.planes - 1 || last[i])) d[k[i]] = v[i];
+      // (the tiles of the last plane that hold the order, which is still read, are gathered at the end)
+      if ((live >> i & 1u) && (c < a.planes - 1 || tile[i] >= gather_order_tiles(a.n_tiles)))
+        d[(int64_t)tile[i] * kGatherTile + lane] = v[i];
+    __syncthreads();  // the window is rewritten
+  }
+}
+
+// In natural order, a thread per element, a.row planes per launch row.
+__global__ void __launch_bounds__(256) gather_plain_kernel(GatherArgs a) {
+  const int64_t k = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (k >= a.n) return;
+  const uint32_t idx = a.perm[k];
+  const int p0 = (int)blockIdx.y * a.row;
+  const int p1 = p0 + a.row < a.planes ? p0 + a.row : a.planes;
+  for (int c = p0; c < p1; ++c) {
+    const float* s;
+    float* d;
+    a.plane(c, s, d);
+    d[k] = s[idx];
   }
 }
 
@@ -430,24 +503,30 @@ extern "C" gs_status gs_gather_gaussians(const gs_gaussians* src, const uint32_t
   a.n = n;
   a.perm = perm;
   a.n_tiles = (n + kGatherTile - 1) / kGatherTile;
+  if (n < kGatherOrdered || src->n <= 0) {
+    a.row = 4;
+    hipLaunchKernelGGL(gather_plain_kernel, dim3((unsigned)((n + 255) / 256), (unsigned)((a.planes + 3) / 4)),
+                       dim3(256), 0, s, a);
+    GS_LAUNCH_CHECK();
+    return GS_OK;
+  }
+  uint32_t* order = reinterpret_cast<uint32_t*>(dst->sh + (int64_t)(3 * planes - 1) * n);
+  uint32_t* at = order + a.n_tiles;
+  const dim3 tg((unsigned)((a.n_tiles + 255) / 256));
+  hipLaunchKernelGGL(gather_clear_kernel, dim3(kGatherBuckets / 256), dim3(256), 0, s, at);
+  hipLaunchKernelGGL(gather_count_kernel, tg, dim3(256), 0, s, perm, src->n, a.n_tiles, at);
+  hipLaunchKernelGGL(gather_scan_kernel, dim3(1), dim3(1024), 0, s, at);
+  hipLaunchKernelGGL(gather_place_kernel, tg, dim3(256), 0, s, perm, src->n, a.n_tiles, at, order);
+  a.order = order;
   const int64_t groups = (a.n_tiles + kGatherGroup - 1) / kGatherGroup;
   const int64_t grid = (groups + kXcds - 1) / kXcds * kXcds;
-  if (n >= kGatherOrdered && src->n > 0) {
-    uint32_t* order = reinterpret_cast<uint32_t*>(dst->sh + (int64_t)(3 * planes - 1) * n);
-    uint32_t* at = order + a.n_tiles;
-    const dim3 tg((unsigned)((a.n_tiles + 255) / 256));
-    hipLaunchKernelGGL(gather_clear_kernel, dim3(kGatherBuckets / 256), dim3(256), 0, s, at);
-    hipLaunchKernelGGL(gather_count_kernel, tg, dim3(256), 0, s, perm, src->n, a.n_tiles, at);
-    hipLaunchKernelGGL(gather_scan_kernel, dim3(1), dim3(1024), 0, s, at);
-    hipLaunchKernelGGL(gather_place_kernel, tg, dim3(256), 0, s, perm, src->n, a.n_tiles, at, order);
-    a.order = order;
-  }
-  hipLaunchKernelGGL(gather_kernel, dim3((unsigned)grid, (unsigned)((a.planes + kGatherPlanes - 1) / kGatherPlanes)),
-                     dim3(256), 0, s, a);
-  if (a.order) {
-    const int64_t rest = gather_order_tiles(a.n_tiles) * kGatherTile;
-    hipLaunchKernelGGL(gather_rest_kernel, dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, s, a);
-  }
+  // planes per row: about 2048 work-groups at least
+  const int64_t row = groups * a.planes / 2048;
+  a.row = (int)(row < 2 ? 2 : row > kGatherPlanes ? kGatherPlanes : row);
+  hipLaunchKernelGGL(gather_kernel, dim3((unsigned)grid, (unsigned)((a.planes + a.row - 1) / a.row)),
+                     dim3(kGatherThreads), 0, s, a);
+  const int64_t rest = gather_order_tiles(a.n_tiles) * kGatherTile;
+  hipLaunchKernelGGL(gather_rest_kernel, dim3((unsigned)((rest + 255) / 256)), dim3(256), 0, s, a);
   GS_LAUNCH_CHECK();
   return GS_OK;
 }
