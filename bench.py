@@ -414,7 +414,9 @@ def workload_lod(args, torch, gs, render, synth):
                          "avg_launch_ms": bin_ms, "algorithmic_bytes_per_launch": bin_bytes, "bytes_per_pair": 32,
                          "sort_design_bytes": sort_bytes,
                          "sort_design_frac": sort_bytes / (bin_ms * 1e-3) / 1e9 / HBM_PEAK_GBS,
-                         "tile_passes": tpasses, "traffic": measured_traffic("bin_sort", P_)},
+                         "tile_passes": tpasses,
+                         # (measured with 16 x 16 tiles: other tiles have other pairs)
+                         "traffic": measured_traffic("bin_sort", P_) if (tun.tile_w, tun.tile_h) == (16, 16) else None},
             "rasterize_fwd": {"bound": "alu", "kernel": ras_name, "unit": "TFLOP/s", "peak": VALU_FP32_PEAK_TFLOPS,
                               "achieved": ras_flops / (ras_ms * 1e-3) / 1e12, "avg_launch_ms": ras_ms,
                               "algorithmic_flops_per_launch": ras_flops, "evals_per_launch": float(np.mean(c_eval)),
