@@ -404,7 +404,9 @@ gs_status gs_mad_bounds(const gs_gaussians* finest, const int64_t* lvl_off, cons
  *   cells: device double[nx*ny][4] or NULL: each block's cell in contracted
  *     x, y (the boundaries above, outermost ends infinite), for gs_blocks.cell
  *     together with gs_blocks.contraction
- *   nx * ny <= 65536; ws: gs_partition_workspace_bytes(n). */
+ *   nx * ny <= 65536; n < 2^32, of which fewer than 2^30 share a value of
+ *     block mod 256, and of block div 256 if there are more than 256 blocks
+ *   ws: gs_partition_workspace_bytes(n). */
 size_t gs_partition_workspace_bytes(int64_t n);
 gs_status gs_partition(const float* means, int64_t n, const double* xy_box, int32_t nx, int32_t ny,
                        uint32_t* block_id, uint32_t* perm, int64_t* block_off, double* cells, void* ws,

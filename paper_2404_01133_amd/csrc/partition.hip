@@ -466,7 +466,7 @@ extern "C" gs_status gs_partition(const float* means, int64_t n, const double* x
     const RadixPass ra{kin, vin, kout, vout, w.counts, GS_COUNT_RECORDS, GS_COUNT_RECORDS, n, 8 * p, 8,
                        w.hist + p * kRadix, nullptr, 0, 0, w.status + (int64_t)p * ntiles * kRadix, (int64_t)kRadix,
                        w.words + 2 + p, w.counts, nullptr};
-    hipLaunchKernelGGL((radix_pass_kernel<8, false>), radix_grid(n), dim3(kRadixThreads), 0, s, ra);
+    hipLaunchKernelGGL((radix_pass_kernel<8, false, true>), radix_grid(n), dim3(kRadixThreads), 0, s, ra);
     GS_LAUNCH_CHECK();
     kin = kout;
     vin = vout;

@@ -19,6 +19,8 @@
 // thread wait for one another (66).
 #pragma once
 
+#include <type_traits>
+
 #include "scan.h"
 
 namespace gs {
@@ -235,12 +237,20 @@ __device__ __forceinline__ uint64_t match_digit(uint32_t d, uint64_t valid) {
   return valid & ~(((uint64_t)hi << 32) | lo);
 }
 
-// element i of an array of fewer than 2^30 words (a 32-bit byte offset beside a uniform base)
+// Byte offset of element i of an array of words: 64 bits (WIDE), or 32, which beside a uniform base cost no
+// address arithmetic, for arrays of fewer than 2^30 words.
+template <bool WIDE>
+__host__ __device__ constexpr std::conditional_t<WIDE, uint64_t, uint32_t> word_offset(uint32_t i) {
+  return (std::conditional_t<WIDE, uint64_t, uint32_t>)i << 2;
+}
+static_assert(word_offset<true>(0xFFFFFFFFu) == 0x3FFFFFFFCull && word_offset<false>((1u << 30) - 1) == 0xFFFFFFFCu,
+              "no offset wraps");
+template <bool WIDE>
 __device__ __forceinline__ uint32_t& word_at(uint32_t* p, uint32_t i) {
-  return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p) + (uint32_t)(i << 2));
+  return *reinterpret_cast<uint32_t*>(reinterpret_cast<char*>(p) + word_offset<WIDE>(i));
 }
 
-template <int RB, int ITEMS, bool COMPACT>
+template <int RB, int ITEMS, bool COMPACT, bool WIDE>
 __device__ __forceinline__ void radix_tile(RadixLds<RB>& lds, const RadixPass& a, int64_t n, int64_t t) {
   using Lds = RadixLds<RB>;
   constexpr int kTileKeys = kRadixThreads * ITEMS;
@@ -335,16 +345,17 @@ __device__ __forceinline__ void radix_tile(RadixLds<RB>& lds, const RadixPass& a
     if (i < tile_total) {
       const uint32_t kk = lds.u.s.keys[i];
       const uint32_t out = lds.delta[digit(kk)] + i;
-      word_at(a.vals_out, out) = lds.u.s.vals[i];
-      word_at(a.keys_out, out) = kk;
+      word_at<WIDE>(a.vals_out, out) = lds.u.s.vals[i];
+      word_at<WIDE>(a.keys_out, out) = kk;
     }
   }
 }
 
 // COMPACT: the least significant depth pass of the binning: reads every selected
 // record's depth key, keeps those with tiles_touched > 0 (values = record index,
-// in index order) and writes the visible count.
-template <int RB, bool COMPACT>
+// in index order) and writes the visible count.  WIDE: 2^30 keys and more (the digits'
+// counts stay below 2^30, what a look-back word holds).
+template <int RB, bool COMPACT, bool WIDE = false>
 __global__ void __launch_bounds__(kRadixThreads) radix_pass_kernel(RadixPass a) {
   using Lds = RadixLds<RB>;
   __shared__ Lds lds;
@@ -378,10 +389,10 @@ __global__ void __launch_bounds__(kRadixThreads) radix_pass_kernel(RadixPass a) 
     __syncthreads();
     const int64_t t = lds.tile;
     if (t >= ntiles) break;
-    if (items == 4) radix_tile<RB, 4, COMPACT>(lds, a, n, t);
-    else if (items == 8) radix_tile<RB, 8, COMPACT>(lds, a, n, t);
-    else if (items == 12) radix_tile<RB, 12, COMPACT>(lds, a, n, t);
-    else radix_tile<RB, kRadixMaxItems, COMPACT>(lds, a, n, t);
+    if (items == 4) radix_tile<RB, 4, COMPACT, WIDE>(lds, a, n, t);
+    else if (items == 8) radix_tile<RB, 8, COMPACT, WIDE>(lds, a, n, t);
+    else if (items == 12) radix_tile<RB, 12, COMPACT, WIDE>(lds, a, n, t);
+    else radix_tile<RB, kRadixMaxItems, COMPACT, WIDE>(lds, a, n, t);
     if (threadIdx.x == 0) claimed = atomicAdd(a.tile_counter, 1u);
     __syncthreads();
   }
