@@ -21,6 +21,8 @@
 // (one work-group per CU: the chain of steps); one 1M-Gaussian 1920x1080 view 102 ->
 // 73 us.  Six waves per SIMD (a few spills outside the loop) against five: 3.88
 // against 4.12 ms.
+#include <type_traits>
+
 #include "scan.h"
 #include "tile.h"
 
@@ -123,6 +125,7 @@ struct BwdLds {
   alignas(4) uint8_t mask[BATCH * kMaskBytes];  // quadrants a record may reach, bit wave * 4 + quadrant
   uint16_t end[BATCH];                          // hits of the staged records up to and with this one
   int quad_last[kQuads < 8 ? 8 : kQuads];  // entries that each quadrant must walk
+  uint32_t odd;                            // a record staged for the tile has a colour that is not finite
 
   __device__ __forceinline__ uint32_t hits(int k) const {
     if constexpr (kMaskBytes == 1) return mask[k];
@@ -195,6 +198,7 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
   if ((lane & 15) == 0) lds.quad_last[threadIdx.x >> 4] = ql;
   if (threadIdx.x == 0) {
     const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+    lds.odd = 0u;
     s_du[BATCH - 1] = 0.0f;
     s_f[BATCH - 1] = s_w1[BATCH - 1] = s_w2[BATCH - 1] = zero;
   }
@@ -228,11 +232,13 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     for (int it = threadIdx.x; it < BATCH * Lds::kMaskBytes; it += NT) {
       const int k = it & (BATCH - 1), part = it >> KB;
       if (k >= nb) continue;
+      const float4 w2 = s_w2[k];
+      if (!((w2.x + w2.y) + w2.z <= 3.0e38f)) lds.odd = 1u;  // (colours are not negative)
       constexpr int kCols = TW >= 16 ? 4 : 2;
       const int x0 = txi * TW + (2 * part % (TW / 8)) * 8, y0 = tyi * TH + (2 * part / (TW / 8)) * 8;
       const float4 f = s_f[k], w1 = s_w1[k];
       GroupTest t;
-      t.load<4, 4>(f, s_du[k], s_w2[k].w, w1, q_limit(w1.w), x0, y0);
+      t.load<4, 4>(f, s_du[k], w2.w, w1, q_limit(w1.w), x0, y0);
       uint32_t m = 0;
 #pragma unroll
       for (int ry = 0; ry < 2; ++ry) {
@@ -265,16 +271,19 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     }
     // one entry of each quadrant's list: the four quadrants step (possibly
     // different) records side by side, each storing its sums to the hit's slot
-    auto step = [&](uint32_t k, uint32_t slot, float du, const float4& f, const float4& w1, const float4& w2) {
+    // (odd: see BwdLds)
+    auto step = [&](auto odd, uint32_t k, uint32_t slot, float du, const float4& f, const float4& w1,
+                    const float4& w2) {
       Eval e;
       const bool in_fp = evaluate_f(fi, fj, f, du, w2.w, w1, e);
       const bool use = ((int)k < my_last) & in_fp & (e.alpha >= kAlphaMin);
-      // an entry that is not used leaves T and the colour in front as they are (colours are finite)
+      // an entry that is not used leaves T and the colour in front as they are: a finite colour times 0
+      // is 0, any other has to be left out
       const float alpha = use ? e.alpha : 0.0f;
       const float aT = alpha * T;
-      A0 = fmaf(w2.x, aT, A0);
-      A1 = fmaf(w2.y, aT, A1);
-      A2 = fmaf(w2.z, aT, A2);
+      A0 = fmaf(odd && !use ? 0.0f : w2.x, aT, A0);
+      A1 = fmaf(odd && !use ? 0.0f : w2.y, aT, A1);
+      A2 = fmaf(odd && !use ? 0.0f : w2.z, aT, A2);
       const float gc = fmaf(g0, w2.x, fmaf(g1, w2.y, g2 * w2.z));
       const float gb = fmaf(g0, out0 - A0, fmaf(g1, out1 - A1, g2 * (out2 - A2)));
       // hardware reciprocal (1 ulp): a correctly rounded division costs ~10 instructions
@@ -333,15 +342,22 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
       const int max_cnt = max(max(c0, c1), max(c2, c3));
       // two entries of the lane's quadrant list per trip, in one LDS read (past the quadrant's count:
       // the null record and its slot)
-      for (int t = 0; t < max_cnt; t += 2) {
-        const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
-        const uint32_t ka = pk & (BATCH - 1), kb = (pk >> 16) & (BATCH - 1);
-        const uint32_t sa = (pk & 0xFFFFu) >> KB, sb = pk >> (16 + KB);
-        const float a0 = s_du[ka], b0 = s_du[kb];
-        const float4 af = s_f[ka], a1 = s_w1[ka], a2 = s_w2[ka];
-        const float4 bf = s_f[kb], b1 = s_w1[kb], b2 = s_w2[kb];
-        step(ka, sa, a0, af, a1, a2);
-        step(kb, sb, b0, bf, b1, b2);
+      if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)lds.odd) == 0, 1)) {
+        for (int t = 0; t < max_cnt; t += 2) {
+          const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
+          const uint32_t ka = pk & (BATCH - 1), kb = (pk >> 16) & (BATCH - 1);
+          const uint32_t sa = (pk & 0xFFFFu) >> KB, sb = pk >> (16 + KB);
+          const float a0 = s_du[ka], b0 = s_du[kb];
+          const float4 af = s_f[ka], a1 = s_w1[ka], a2 = s_w2[ka];
+          const float4 bf = s_f[kb], b1 = s_w1[kb], b2 = s_w2[kb];
+          step(std::false_type{}, ka, sa, a0, af, a1, a2);
+          step(std::false_type{}, kb, sb, b0, bf, b1, b2);
+        }
+      } else {  // one at a time (so that the loop needs no register that the other one does not)
+        for (int t = 0; t < max_cnt; ++t) {
+          const uint32_t e = my_list[t], k = e & (BATCH - 1);
+          step(std::true_type{}, k, e >> KB, s_du[k], s_f[k], s_w1[k], s_w2[k]);
+        }
       }
       __syncthreads();
       const int end_used = lds.end[k1 - 1];
