@@ -96,6 +96,10 @@ __device__ __forceinline__ float flush_value(uint32_t q, float v, const float4& 
   const float scaled = q >= kGQ ? v * (-0.69314718055994531f * f) : v;
   return (q < 3) & !(f > 0.0f) ? 0.0f : scaled;
 }
+// Words of the lists, which hold 16-bit entries (a type of its own kind: by the language's rules stores of
+// entries and loads of uint32_t would be of different objects, which a compiler may reorder).
+typedef uint32_t __attribute__((may_alias)) ListWord;
+typedef uint32_t __attribute__((ext_vector_type(4), may_alias)) ListQuad;
 constexpr int kBwdLdsOffsets = 1024;  // segment offsets staged in LDS by the view-major adjoint up to this many
 
 // LDS of one tile.  Up to BATCH - 1 records are staged at a time (the last place is
@@ -312,9 +316,8 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
     // rounds over the staged records: as many of the next ones as the pool has room for
     for (int k0 = 0, used = 0; k0 < nb;) {
       constexpr uint32_t kNull = (uint32_t)(BATCH - 1) | ((uint32_t)Lds::kPool << KB);
-      uint4* lp = reinterpret_cast<uint4*>(&lds.list[wid][0][0]);
-      for (int k = lane; k < 4 * Lds::kStride * 2 / 16; k += 64)
-        lp[k] = make_uint4(kNull * 0x10001u, kNull * 0x10001u, kNull * 0x10001u, kNull * 0x10001u);
+      ListQuad* lp = reinterpret_cast<ListQuad*>(&lds.list[wid][0][0]);
+      for (int k = lane; k < 4 * Lds::kStride * 2 / 16; k += 64) lp[k] = (ListQuad)(kNull * 0x10001u);
       int k1 = 0;  // end of the round's records
       int c0 = 0, c1 = 0, c2 = 0, c3 = 0;
 #pragma unroll
@@ -344,7 +347,7 @@ __device__ __forceinline__ void raster_bwd_tile(const TileArgs& ta, BwdLds<TW, T
       // the null record and its slot)
       if (__builtin_expect(__builtin_amdgcn_readfirstlane((int)lds.odd) == 0, 1)) {
         for (int t = 0; t < max_cnt; t += 2) {
-          const uint32_t pk = *reinterpret_cast<const uint32_t*>(&my_list[t]);
+          const uint32_t pk = *reinterpret_cast<const ListWord*>(&my_list[t]);
           const uint32_t ka = pk & (BATCH - 1), kb = (pk >> 16) & (BATCH - 1);
           const uint32_t sa = (pk & 0xFFFFu) >> KB, sb = pk >> (16 + KB);
           const float a0 = s_du[ka], b0 = s_du[kb];
