@@ -428,17 +428,18 @@ class GaussianRasterize(torch.autograd.Function):
     """image[V,3,H,W] = render(means[3,N], scales[3,N], quats[4,N], opac[N], sh[16,3,N]; cameras).
 
     Forward runs the library's preprocess, bin_sort and rasterize_fwd; backward
-    runs rasterize_bwd, which recomputes the per-pixel blend state."""
+    runs rasterize_bwd, which recomputes the per-pixel blend state.  cams_dev holds
+    n_views cameras or more; table: the set's block table on the device (rasterize()
+    uploads it with the cameras; made here if it is not given)."""
 
     @staticmethod
-    def forward(ctx, means, scales, quats, opac, sh, cams_dev, n_views, width, height, sh_degree, bg, frame):
+    def forward(ctx, means, scales, quats, opac, sh, cams_dev, n_views, width, height, sh_degree, bg, frame,
+                table=None):
         level = DeviceLevel(means.detach().contiguous(), scales.detach().contiguous(), quats.detach().contiguous(),
                             opac.detach().contiguous(), sh.detach().contiguous())
-        # rasterize() sends the block table behind the cameras; cameras alone are taken too
-        tables = cams_dev[n_views * gs.CAMERA_BYTES:]
-        if tables.numel() == 0:
-            tables = _stage(_single_table(level.n), means.device)
-        scene = DeviceScene([level], [[0]], [[level.n]], device=means.device, tables=tables.view(torch.int64))
+        if table is None:
+            table = _stage(_single_table(level.n), means.device)
+        scene = DeviceScene([level], [[0]], [[level.n]], device=means.device, tables=table.view(torch.int64))
         records = n_views * level.n
         if frame is None:
             # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (17 bytes a pair with
@@ -458,11 +459,13 @@ class GaussianRasterize(torch.autograd.Function):
         grads = [scene.levels[0].zeros_like()]
         backward_frame(scene, frame, ctx.cams, d_rgb, grads, ctx.sh_degree, ctx.bg)
         g = grads[0]
-        return g.means, g.scales, g.quats, g.opac, g.sh, None, None, None, None, None, None, None
+        return g.means, g.scales, g.quats, g.opac, g.sh, None, None, None, None, None, None, None, None
 
 
 def rasterize(means, scales, quats, opac, sh, cams, sh_degree=3, bg=(0.0, 0.0, 0.0), frame=None):
     """Differentiable render of one Gaussian set for a list of cameras (same size)."""
-    cams_dev = _stage(gs.cameras_bytes(cams) + _single_table(int(opac.shape[0])), means.device)
+    staged = _stage(gs.cameras_bytes(cams) + _single_table(int(opac.shape[0])), means.device)  # one upload
+    cams_dev, table = staged[:len(cams) * gs.CAMERA_BYTES], staged[len(cams) * gs.CAMERA_BYTES:]
     W, H = cams[0].width, cams[0].height
-    return GaussianRasterize.apply(means, scales, quats, opac, sh, cams_dev, len(cams), W, H, sh_degree, bg, frame)
+    return GaussianRasterize.apply(means, scales, quats, opac, sh, cams_dev, len(cams), W, H, sh_degree, bg, frame,
+                                   table)
