@@ -113,11 +113,11 @@ struct RadixPass {
   const int32_t* tiles_touched;  // compacting pass
 };
 
-template <int RB>
+template <int RB, int ITEMS = kRadixMaxItems>
 struct RadixLds {
   static constexpr int kDigits = 1 << RB;
   static constexpr int kSegs = kRadixThreads / kDigits;  // look-back threads per digit
-  static constexpr int kMaxTile = kRadixThreads * kRadixMaxItems;
+  static constexpr int kMaxTile = kRadixThreads * ITEMS;
   union {
     struct {
       uint32_t keys[kMaxTile], vals[kMaxTile];
@@ -127,6 +127,7 @@ struct RadixLds {
       uint32_t code[kSegs][kDigits];
       int32_t at[kDigits];
     } look;
+    uint32_t words[2 * kMaxTile];  // (of those who sort a tile for themselves)
   } u;
   uint16_t wave_hist[kRadixWaves][kDigits];  // counts (at most 1024 keys of a wave), then positions in the tile
   uint32_t delta[kDigits];                   // output position less tile position of a digit
@@ -136,8 +137,8 @@ struct RadixLds {
 };
 
 // exclusive prefix over the digits, held by threads 0 .. kDigits - 1 (every thread calls it); total in *total
-template <int RB>
-__device__ __forceinline__ uint32_t digit_excl_scan(RadixLds<RB>& lds, uint32_t x, uint32_t* total) {
+template <int RB, class Lds>
+__device__ __forceinline__ uint32_t digit_excl_scan(Lds& lds, uint32_t x, uint32_t* total) {
   const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
   const uint32_t inc = (uint32_t)wave_incl_scan((int)x);
   if (lane == 63) lds.wave_tot[wid] = inc;

@@ -663,9 +663,10 @@ SortWs sort_ws_layout(char* base, int64_t rc, int64_t pc) {
 //   4096 records, 16 a record, 172 a tile      63 ->  42     4096 records, 98 a record         93 ->  73
 //   20000 records, 91 a record, 514 a tile    136 -> 160     70001 records, 9 a record, 3204   103 -> 124
 //   140002 records, 42 a record, 2641 a tile  250 -> 382
-// Lists that are longer than their mean suggests are sorted all the same: 1M records in far views, the longest
-// list 5532, 32862, 184409: 195 -> 194, 184 -> 185, 184 -> 323 (the frame's other kernels take 569 and 2616 in
-// the last two).
+// Lists that are longer than their mean suggests are sorted all the same, linear in their length: 1M records in
+// far views, the longest list 5532, 32862, 184409, 633173: 191 -> 185, 182 -> 187, 181 -> 258, 184 -> 259 (the frame's
+// other kernels take 259, 563, 2537 and 24081).  Nearly all pairs in one list, 1M, 2M, 4M: 172 -> 217, 257 -> 342,
+// 351 -> 649.
 bool lists_by_tile(int64_t rc, int64_t pc, int64_t n_tile_ids) {
   const bool few = pc <= 4 * rc;
   return pc <= (few ? 4096 : 512) * n_tile_ids && (few || pc <= (int64_t)1 << 20);
@@ -825,13 +826,14 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
     // (the tile passes' look-back words are free by now: at least a word for every eight pairs of capacity,
     // the chunks need four for every 1024)
     const ListArgs l{tile_ranges, depth_keys, pair_records, w.precs_alt, pair_tiles, w.ptiles_alt,
-                     (uint2*)w.pstatus, counters + 40, n_tile_ids, (uint32_t)(record_capacity - 1)};
+                     (uint2*)w.pstatus, counters + 40, (uint32_t)(radix_tiles_bound(pair_capacity) * kTileHistWords / 2),
+                     n_tile_ids, (uint32_t)(record_capacity - 1)};
     const int64_t lg = (n_tile_ids + 3) / 4;
     hipLaunchKernelGGL(list_sort_kernel, dim3((unsigned)(lg < 65536 ? lg : 65536)), dim3(256), 0, s, l);
     if (pair_capacity > kListWave) hipLaunchKernelGGL(list_chunk_kernel, dim3(256), rblk, 0, s, l);
     int p = 0;
     for (int64_t run = kListChunk; run < pair_capacity; run *= kListFan)
-      hipLaunchKernelGGL(list_merge_kernel, dim3(256), dim3(1024), 0, s, l, p++);
+      hipLaunchKernelGGL(list_merge_kernel, dim3(256), rblk, 0, s, l, p++);
     GS_LAUNCH_CHECK();
   }
   // 7. work queue
