@@ -167,8 +167,9 @@ __global__ void __launch_bounds__(256) list_sort_kernel(ListArgs a) {
       uint32_t at = 0;
       if (lane == 0) at = atomicAdd(a.n_chunks + (c == 1), (uint32_t)c);
       at = (uint32_t)__builtin_amdgcn_readfirstlane((int)at);
-      if (c == 1) at = a.max_chunks - 1u - at;
-      for (int i = lane; i < c; i += 64) a.chunks[at + i] = make_uint2((uint32_t)t, (uint32_t)i);
+      // (there is room for all, but if a wait gave up the ranges of several tiles may overlap)
+      for (uint32_t i = lane; i < (uint32_t)c && at + i < a.max_chunks; i += 64)
+        a.chunks[c == 1 ? a.max_chunks - 1u - at : at + i] = make_uint2((uint32_t)t, i);
     }
   }
 }
@@ -247,7 +248,7 @@ __device__ __forceinline__ void group_sort_n(RadixLds<8>& lds, int n, Load load,
 // order, so that stable passes over the depth suffice.
 __global__ void __launch_bounds__(kRadixThreads) list_chunk_kernel(ListArgs a) {
   __shared__ RadixLds<8> lds;
-  const uint32_t several = a.n_chunks[0], nc = several + a.n_chunks[1];
+  const uint32_t several = min(a.n_chunks[0], a.max_chunks), nc = several + min(a.n_chunks[1], a.max_chunks);
   for (uint32_t i = blockIdx.x; i < nc; i += gridDim.x) {
     const uint2 c = a.chunks[i < several ? i : a.max_chunks - 1u - (i - several)];
     const uint32_t start = a.ranges[2 * (int64_t)c.x], len = a.ranges[2 * (int64_t)c.x + 1] - start;
@@ -494,7 +495,7 @@ __device__ __forceinline__ void merge_sorted(MergeLds& lds, uint32_t (*s_at)[kLi
 __global__ void __launch_bounds__(kRadixThreads, 8) list_merge_kernel(ListArgs a, int p) {
   __shared__ MergeLds lds;
   __shared__ uint32_t s_at[2][kListFan];
-  const uint32_t nc = a.n_chunks[0];  // (at most 2^30 / 8192)
+  const uint32_t nc = min(a.n_chunks[0], a.max_chunks);  // (at most 2^30 / 8192)
   uint32_t run = kListChunk;
   for (int q = 0; q < p; ++q) run *= kListFan;
   constexpr uint32_t kEntries = kListChunk / kRadixThreads, kParts = kListChunk / kListPart;

@@ -823,8 +823,9 @@ extern "C" gs_status gs_bin_sort(const void* records, const uint32_t* depth_keys
   GS_LAUNCH_CHECK();
   // 6. depth order inside the lists
   if (by_tile) {
-    // (the tile passes' look-back words are free by now: at least a word for every eight pairs of capacity,
-    // the chunks need four for every 1024)
+    // (the tile passes' look-back words are free by now: kTileHistWords for every 16384 pairs of capacity at least,
+    // of which the chunks need two for every list of more than kListWave and for every 16384 pairs)
+    static_assert(kTileHistWords * kListWave >= 4 * kListChunk, "room for the chunks");
     const ListArgs l{tile_ranges, depth_keys, pair_records, w.precs_alt, pair_tiles, w.ptiles_alt,
                      (uint2*)w.pstatus, counters + 40, (uint32_t)(radix_tiles_bound(pair_capacity) * kTileHistWords / 2),
                      n_tile_ids, (uint32_t)(record_capacity - 1)};
