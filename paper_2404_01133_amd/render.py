@@ -251,6 +251,7 @@ class Frame:
         self.tile_queue = torch.zeros(2 + self.n_tiles, dtype=torch.int32, device=d)
         self.record_capacity = 0
         self.pair_capacity = 0
+        self.pairs = 0            # of the last checked render_frame
         self.gather = None        # point-wise selection buffers, made on first use
         self.pts_offsets = None
         self.pts_ws = None
@@ -280,6 +281,14 @@ class Frame:
                                     self.H, self.tuning)
         if getattr(self, "sort_ws", None) is None or self.sort_ws.numel() < nbytes:
             self.sort_ws = torch.empty(nbytes, dtype=torch.uint8, device=d)
+
+    def keep_for_backward(self):
+        """Frees what backward_frame does not read of the rendered frame (not rendered into again): the
+        binning's inputs and workspace, and room for twice the pairs there are where that is 8 MB and more."""
+        self.sort_ws = self.pair_tiles = self.depth_keys = self.tiles_touched = None
+        if self.pair_capacity - self.pairs > max(self.pairs, 1 << 21):
+            self.pair_capacity = max(1, self.pairs)
+            self.pair_records = self.pair_records[:self.pair_capacity].clone()
 
     def ensure_pointwise(self, scene):
         d = self.device
@@ -381,6 +390,7 @@ def _render(scene, frame, cams_dev, mode, thresholds, sh_degree, bg, stream, che
         if c["flags"] & gs.GS_FLAG_SELECTION:
             raise RuntimeError("GS_TUNE_SHARED_SELECTION was set but the views selected different records "
                                "(counts=%s)" % c)
+        frame.pairs = c["pairs"]
         if c["flags"] == 0:
             return rgb
         frame.reserve(max(frame.record_capacity, int(c["records"] * 1.1) + 1024),
@@ -441,14 +451,18 @@ class GaussianRasterize(torch.autograd.Function):
             table = _stage(_single_table(level.n), means.device)
         scene = DeviceScene([level], [[0]], [[level.n]], device=means.device, tables=table.view(torch.int64))
         records = n_views * level.n
-        if frame is None:
+        kept = frame is not None
+        if not kept:
             # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (17 bytes a pair with
-            # the sort's workspace, 150 MB).  Splats of a small set may cover tens of tiles each, and a guess
-            # that is too low costs a second frame (2 x 70001 records, 5.2M pairs, with gradients: 1287 -> 915 us).
+            # the sort's workspace, 150 MB, most of it freed after the frame).  Splats of a small set may cover tens
+            # of tiles each, and a guess that is too low costs a second frame (2 x 70001 records, 5.2M pairs, with
+            # gradients: 1287 -> 915 us).
             frame = Frame(1, n_views, width, height, records, max(4 * records, min(64 * records, 1 << 23), 4096))
         else:
             frame.reserve(records, 0)
         rgb = _render(scene, frame, cams_dev, gs.GS_LOD_ALL_FINEST, (), sh_degree, bg, None, True, False, True)
+        if not kept and any(ctx.needs_input_grad):
+            frame.keep_for_backward()
         ctx.scene, ctx.frame, ctx.cams = scene, frame, cams_dev
         ctx.sh_degree, ctx.bg = sh_degree, bg
         return rgb

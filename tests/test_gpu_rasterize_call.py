@@ -39,3 +39,34 @@ def test_gradients_through_apply_equal_those_of_rasterize():
         got.append([t.grad.double() for t in p])
     for a, b in zip(*got):  # sums of the same FP32 terms in another order
         assert float(b.norm()) > 0 and float((a - b).norm()) <= 1e-5 * float(b.norm())
+
+
+@pytest.mark.parametrize("n", [500, 100_000])
+def test_memory_held_for_the_backward(n):
+    """Between forward and backward, autograd holds no more of a frame of its own than a frame of 4 pairs a
+    record takes, and up to 8 MB of room for pairs that is not worth a copy; the gradients are those through
+    a kept frame."""
+    g = synth.cube_gaussians(n, 3)
+    g.scales = (g.scales * 0.05).astype(np.float32)
+    cams = [synth.axis_camera(200, 120)] * 2
+    arrays = [torch.from_numpy(np.ascontiguousarray(a)).cuda() for a in g.astuple()]
+    d = torch.from_numpy(np.random.default_rng(1).normal(size=(2, 3, 120, 200)).astype(np.float32)).cuda()
+
+    def allocated():
+        torch.cuda.synchronize()
+        return torch.cuda.memory_allocated()
+    start = allocated()
+    frame = render.Frame(1, 2, 200, 120, 2 * n, max(4096, 8 * n))
+    of_frame = allocated() - start
+    p = [a.clone().requires_grad_() for a in arrays]
+    render.rasterize(*p, cams, frame=frame).backward(d)
+    want = [t.grad.double() for t in p]
+    p = [a.clone().requires_grad_() for a in arrays]
+    start = allocated()
+    img = render.rasterize(*p, cams)
+    held = allocated() - start
+    print("case:", n, "held", held, "frame", of_frame, "pairs", frame.pairs, flush=True)
+    assert frame.pairs <= 8 * n and held <= of_frame + img.numel() * 4 + 4096 + (8 << 20)  # (cameras and table)
+    img.backward(d)
+    for a, t in zip(want, p):  # sums of the same FP32 terms in another order
+        assert float(a.norm()) > 0 and float((a - t.grad.double()).norm()) <= 1e-5 * float(a.norm())
