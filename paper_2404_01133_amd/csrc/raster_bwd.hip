@@ -15,11 +15,12 @@
 //
 // Why slots: the sums used to be added into one row per record with LDS float
 // atomics, and those bounded the kernel (about 50 LDS cycles for the 36 lanes of a
-// step, LDS busy 92 % of the time; a store takes two).  Now VALU issue bounds it.
+// step, LDS busy 92 % of the time; a store takes two).  Now VALU issue bounds it: 76
+// VALU and 5.5 LDS instructions per step of a wave, 21 of the VALU the reduction.
 // Measured, 16 views of a 2M-Gaussian block at 1600x900: 5.16 ms with LDS atomics,
-// 3.75 with slots and the moments below; 4096 Gaussians at 256x256 76 -> 64 us
+// 3.83 with slots and the moments below; 4096 Gaussians at 256x256 76 -> 66 us
 // (one work-group per CU: the chain of steps); one 1M-Gaussian 1920x1080 view 102 ->
-// 73 us.  Six waves per SIMD (a few spills outside the loop) against five: 3.88
+// 75 us.  Six waves per SIMD (a few spills outside the loop) against five: 3.88
 // against 4.12 ms.
 #include <type_traits>
 
@@ -106,8 +107,8 @@ constexpr int kBwdLdsOffsets = 1024;  // segment offsets staged in LDS by the vi
 // the null record) and walked in rounds of as many as have room for all their hits
 // in the pool: small splats reach three to six of a 16x16 tile's sixteen
 // quadrants, so about a hundred records share a round; splats that cover the tile
-// take rounds of 25.  The pool is sized so that five work-groups of a 16x16 tile
-// fit a CU.
+// take rounds of 25.  The pool is sized so that the six work-groups of a 16x16 tile
+// that the kernel's registers allow fit a CU.
 template <int TW, int TH, int BATCH>
 struct BwdLds {
   static constexpr int kQuads = (TW * TH) / 16;
@@ -408,6 +409,7 @@ raster_bwd_kernel(TileArgs ta, uint32_t* queue,
                                                             const float* __restrict__ d_rgb,
                                                             float* __restrict__ grad2d, DetArgs det) {
   __shared__ BwdLds<TW, TH, BATCH> lds;
+  static_assert(TW * TH != 256 || 6 * sizeof(lds) <= 160 * 1024, "six work-groups per CU");
   for_each_tile(ta, queue, 1, [&](int tile_g) {
     raster_bwd_tile<TW, TH, BATCH, DET>(ta, lds, tile_g, rgb, T_final, n_last, d_rgb, grad2d, det);
   });

@@ -456,7 +456,8 @@ class GaussianRasterize(torch.autograd.Function):
             # first guess of the pairs: 4 a record, for small sets up to 64 but not past 8M (17 bytes a pair with
             # the sort's workspace, 150 MB, most of it freed after the frame).  Splats of a small set may cover tens
             # of tiles each, and a guess that is too low costs a second frame (2 x 70001 records, 5.2M pairs, with
-            # gradients: 1287 -> 915 us).
+            # gradients: 1287 -> 915 us).  With more room than 4 a record and 1M the binning goes depth first, also
+            # for sets whose splats cover few tiles: 1M records at 1080p, 58 us of 440.
             frame = Frame(1, n_views, width, height, records, max(4 * records, min(64 * records, 1 << 23), 4096))
         else:
             frame.reserve(records, 0)
