@@ -43,10 +43,6 @@ constexpr float kAlphaMin = 1.0f / 255.0f;
 constexpr float kAlphaMax = 0.99f;
 constexpr float kTMin = 1.0e-4f;
 
-struct DevCounts {
-  int64_t* p;
-};
-
 // Host-side checks --------------------------------------------------------
 inline bool tile_shape_supported(int tw, int th) {
   return (tw == 16 && th == 16) || (tw == 8 && th == 8) || (tw == 16 && th == 8) || (tw == 32 && th == 8) ||

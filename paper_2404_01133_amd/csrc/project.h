@@ -310,6 +310,5 @@ __device__ __forceinline__ bool project_back(const Shape& g, const gs_camera& ca
 
 // sqrt(log2(e) / 2): the conic factor is scaled so the Gaussian is exp2(-Q).
 constexpr double kConicScale = 0.84932180028801907;
-constexpr double kConicScale2 = 0.72134752044448170;  // log2(e) / 2
 
 }  // namespace gs
