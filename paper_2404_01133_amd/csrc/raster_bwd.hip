@@ -94,7 +94,8 @@ constexpr int kGQ = 4;  // first partial with that factor
 // clamped channel (record colour exactly 0) dropped, so that the projection adjoint reads no records.
 __device__ __forceinline__ float flush_value(uint32_t q, float v, const float4& w1, const float4& w2) {
   const float f = *(q < 3 ? &w2.x + q : &w1.w);  // the channel's colour or the opacity
-  const float scaled = q >= kGQ ? v * (-0.69314718055994531f * f) : v;
+  // (an infinite opacity is clamped at every pixel: its moments are 0 and stay 0)
+  const float scaled = (q >= kGQ) & (v != 0.0f) ? v * (-0.69314718055994531f * f) : v;
   return (q < 3) & !(f > 0.0f) ? 0.0f : scaled;
 }
 // Words of the lists, which hold 16-bit entries (a type of its own kind: by the language's rules stores of

@@ -1,4 +1,5 @@
-"""Colours that are not finite reach the gradients of the pixels that show them and no others.
+"""Colours that are not finite reach the gradients of the pixels that show them and no others; an infinite
+opacity is a clamped one.
 
 Two faint splats of under a pixel, one in the upper two rows of a 4x4 quadrant, one in the lower
 two: neither reaches a pixel of the other, while the adjoint walks both for all sixteen pixels.  The
@@ -53,3 +54,25 @@ def test_other_splats_of_the_quadrant_are_untouched(colour, tile, batch, flags):
     assert all(np.abs(want[k]).max() > 0 for k in (0, 1, 3, 4))  # (a round splat's rotation has no gradient)
     for a, b in zip(got, want):  # the same pixels, the same operations: equal bits
         np.testing.assert_array_equal(a[..., 1], b[..., 0])
+
+
+@pytest.mark.parametrize("flags", [0, gs.GS_TUNE_DETERMINISTIC])
+@pytest.mark.parametrize("opacity", [np.inf, 3.0e38])
+def test_opacity_beyond_the_clamp(opacity, flags):
+    """An alpha that is clamped at every pixel of the splat depends on neither opacity nor shape: those gradients
+    are exactly 0, everything else is as with any other opacity that large."""
+    cam = synth.axis_camera(W, H)
+    tuning = gs.tuning_struct(16, 16, 256, flags)
+    d = torch.from_numpy(np.random.default_rng(5).normal(size=(1, 3, H, W)).astype(np.float32)).cuda()
+    arrays = _splats(cam, [(10.0, 9.0), (11.0, 10.0)], [3.0, 4.0])
+    arrays[1][:] = 0.002  # under a pixel: with 0.3 px^2 of dilation exp2(-Q) >= 1e-10 in the 4x4 pixels of the footprint
+    arrays[3][:] = 1.0e30, 0.5
+    _, want = _render(arrays, cam, tuning, d)
+    arrays[3][0] = opacity
+    img, got = _render(arrays, cam, tuning, d)
+    assert np.isfinite(img).all()
+    for a, b in zip(got, want):
+        np.testing.assert_array_equal(a, b)
+    for k in (1, 2, 3):
+        assert np.all(got[k][..., 0] == 0.0) and np.isfinite(got[k]).all()
+    assert np.abs(got[4][..., 0]).max() > 0 and np.abs(got[1][..., 1]).max() > 0
