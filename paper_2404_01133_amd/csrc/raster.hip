@@ -31,7 +31,48 @@ struct FwdLds {
   float4 f[BATCH];  // footprint as floats: i0, j0, i1 - i0, j1 - j0
   alignas(16) uint8_t list[(TW * TH) / 64][kFwdGroups][kListStride<BATCH>];
   uint8_t cand[(TW * TH) / 64][BATCH];
+  uint32_t odd;  // a record staged for the tile has a colour that is not finite
 };
+
+__device__ __forceinline__ bool colour_finite(float c) { return c <= 3.4028235e38f; }  // (colours are not negative)
+
+// Colours that are not finite: times the weight 0 of an entry that is not used, or at a pixel that is done, they
+// would make NaN of the sum.  They are staged as 0, and added to the pixels written that have used them, which
+// is what the weighted sums come to.  Nothing of the walk is live here: a register more in it costs 3 %.  (Sixteen
+// views of the block 1350 -> 1364 us, eight of the city 344 -> 355; as a second walk that selects, 1450 and 414.)
+template <int TW, int TH>
+__device__ __forceinline__ void add_odd_colours(const TileArgs& ta, int tile_g, float* __restrict__ rgb,
+                                                const int32_t* __restrict__ n_last) {
+  uint32_t tid = threadIdx.x;
+  asm volatile("" : "+v"(tid));  // (so that the pixel is found again and not kept)
+  const int view = tile_g / ta.tiles_per_view, tile = tile_g - view * ta.tiles_per_view;
+  const int tyi = tile / ta.tiles_x_n, txi = tile - tyi * ta.tiles_x_n;
+  const LaneMap<TW, TH, kFwdGW, kFwdGH> m(txi, tyi, (int)(tid >> 6), (int)(tid & 63));
+  const bool inside = m.i < ta.W && m.j < ta.H;
+  const int64_t plane = (int64_t)ta.H * ta.W, pix = (int64_t)m.j * ta.W + m.i;
+  const int last = inside ? n_last[(int64_t)view * plane + pix] : 0;
+  const uint32_t start = ta.ranges[2 * tile_g];
+  float C0 = 0.0f, C1 = 0.0f, C2 = 0.0f;
+  for (int k = 0; __ballot(k < last); ++k) {
+    const float4* r = reinterpret_cast<const float4*>(&ta.records[ta.pair_records[start + (uint32_t)k]]);
+    const float4 w2 = r[2];
+    if (colour_finite(w2.x) & colour_finite(w2.y) & colour_finite(w2.z)) continue;
+    const float4 w0 = r[0];
+    Eval e;
+    const bool in_fp = evaluate_f((float)m.i, (float)m.j, footprint_floats(w0), w0.x, w2.w, r[1], e);
+    if ((k < last) & in_fp & (e.alpha >= kAlphaMin)) {
+      C0 += colour_finite(w2.x) ? 0.0f : w2.x;
+      C1 += colour_finite(w2.y) ? 0.0f : w2.y;
+      C2 += colour_finite(w2.z) ? 0.0f : w2.z;
+    }
+  }
+  if (inside) {
+    float* out = rgb + (int64_t)view * 3 * plane + pix;
+    out[0] += C0;
+    out[plane] += C1;
+    out[2 * plane] += C2;
+  }
+}
 
 template <int TW, int TH, int BATCH>
 __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, TH, BATCH>& lds, int tile_g,
@@ -64,6 +105,7 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
   if (threadIdx.x == 0) {
     const float4 zero = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
     s_w0[BATCH - 1] = s_w1[BATCH - 1] = s_w2[BATCH - 1] = s_f[BATCH - 1] = zero;  // the null record
+    lds.odd = 0u;
   }
   for (uint32_t b = start; b < end; b += BATCH - 1) {
     if (__syncthreads_and(!(fi == fi))) break;
@@ -75,7 +117,16 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
       a.y = q_limit(w1.w);
       s_w0[k] = a;
       s_w1[k] = w1;
-      s_w2[k] = r[2];
+      float4 w2 = r[2];
+      // (colours are not negative: their bits grow with them, infinity and NaN above all)
+      const uint32_t top = max(max(__float_as_uint(w2.x), __float_as_uint(w2.y)), __float_as_uint(w2.z));
+      if (__builtin_expect(top >= 0x7F800000u, 0)) {  // added at the end
+        w2.x = colour_finite(w2.x) ? w2.x : 0.0f;
+        w2.y = colour_finite(w2.y) ? w2.y : 0.0f;
+        w2.z = colour_finite(w2.z) ? w2.z : 0.0f;
+        lds.odd = 1u;
+      }
+      s_w2[k] = w2;
       s_f[k] = footprint_floats(a);
     }
     clear_lists<BATCH, kFwdGroups>(lists);
@@ -99,7 +150,7 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
         fi = stop ? __builtin_nanf("") : fi;
       }
       const float aT = alpha * T;
-      C0 = fmaf(w2.x, aT, C0);  // (colours are finite)
+      C0 = fmaf(w2.x, aT, C0);  // (colours are finite here)
       C1 = fmaf(w2.y, aT, C1);
       C2 = fmaf(w2.z, aT, C2);
       T = Tn;
@@ -144,13 +195,15 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     T_final[(int64_t)view * plane + pix] = T;
     n_last[(int64_t)view * plane + pix] = last;
   }
+  if (end > start && lds.odd) add_odd_colours<TW, TH>(ta, tile_g, rgb, n_last);
 }
 
 // Bound by VALU issue (with the groups' lists, about 24 instructions and an
 // exponential per entry).  Measured, us per call: eight 1600x900 views of the 20M
 // city 384 before the lists left out unreachable groups, 374 with that, 337 with the
-// loop free of per-entry count, done and stop selects; 16 views of a 2M block 1977,
-// 1514, 1348; 4096 Gaussians at 256x256 53, 35, 30.  Six waves per SIMD for the
+// loop free of per-entry count, done and stop selects, 348 with the test for colours
+// that are not finite; 16 views of a 2M block 1977, 1514, 1348, 1364; 4096 Gaussians
+// at 256x256 53, 35, 30, 30.  Six waves per SIMD for the
 // multi-wave tiles (the compiler spills a dozen registers outside the loop): 1348 for
 // the block, 1448 at five, 1440 at seven.
 template <int TW, int TH, int BATCH>

@@ -52,8 +52,7 @@ struct LaneMap {
   int i, j;    // this lane's pixel
   int x0, y0;  // first pixel of the wave's block
   int g;       // this lane's group
-  __device__ __forceinline__ LaneMap(int txi, int tyi, int wid) {
-    const int lane = threadIdx.x & 63;
+  __device__ __forceinline__ LaneMap(int txi, int tyi, int wid, int lane = (int)(threadIdx.x & 63)) {
     x0 = txi * TW + (wid % (TW / 8)) * 8;
     y0 = tyi * TH + (wid / (TW / 8)) * 8;
     g = lane / (GW * GH);

@@ -30,7 +30,7 @@ def _splats(cam, px, depth):
 
 def _render(arrays, cam, tuning, d):
     p = [torch.from_numpy(a).cuda().requires_grad_() for a in arrays]
-    frame = render.Frame(1, 1, W, H, 2, 64, tuning)
+    frame = render.Frame(1, 1, W, H, 2, 256, tuning)
     img = render.rasterize(*p, [cam], frame=frame)
     img.backward(d)
     return img.detach().cpu().numpy()[0], [t.grad.cpu().numpy() for t in p]
@@ -76,3 +76,39 @@ def test_opacity_beyond_the_clamp(opacity, flags):
     for k in (1, 2, 3):
         assert np.all(got[k][..., 0] == 0.0) and np.isfinite(got[k]).all()
     assert np.abs(got[4][..., 0]).max() > 0 and np.abs(got[1][..., 1]).max() > 0
+
+
+@pytest.mark.parametrize("tile,batch,flags", [((16, 16), 256, 0), ((8, 8), 64, gs.GS_TUNE_WORK_QUEUE),
+                                              ((32, 16), 128, 0)])
+@pytest.mark.parametrize("colour", [np.inf, np.nan])
+def test_image_shows_it_where_it_is_used_only(colour, tile, batch, flags):
+    """Neither a pixel of the same group that the splat does not reach nor one that is done before it changes."""
+    cam = synth.axis_camera(W, H)
+    tuning = gs.tuning_struct(tile[0], tile[1], batch, flags)
+    d = torch.zeros((1, 3, H, W), device="cuda")
+    faint = _splats(cam, [(10.0, 9.0), (22.0, 21.0)], [3.0, 4.0])
+    want, _ = _render(faint, cam, tuning, d)
+    faint[4][0, 1, 0] = colour
+    got, _ = _render(faint, cam, tuning, d)
+    reached = np.zeros((H, W), bool)
+    reached[8:10, 9:11] = True
+    assert np.all(want[:, reached] > 0) and not np.isfinite(got[1][reached]).any()
+    np.testing.assert_array_equal(got[1][~reached], want[1][~reached])
+    np.testing.assert_array_equal(got[[0, 2]], want[[0, 2]])
+    # 300 splats of every opacity up to the clamp over the left half, one behind them over everything
+    rng = np.random.default_rng(9)
+    px = np.stack([rng.uniform(0, 16, 300), rng.uniform(0, H, 300)], 1)
+    px = np.concatenate([px, [[16.0, 16.0]]])
+    many = _splats(cam, px, np.concatenate([rng.uniform(1.0, 3.0, 300), [4.0]]))
+    many[1][:, :300] = 2.0 / cam.fx
+    many[1][:, 300] = 100.0
+    many[3][:300] = rng.uniform(0.3, 1.0, 300)
+    many[3][300] = 0.5
+    front = [np.ascontiguousarray(a[..., :300]) for a in many]
+    want, _ = _render(many, cam, tuning, d)
+    many[4][0, :, 300] = colour
+    got, _ = _render(many, cam, tuning, d)
+    alone, _ = _render(front, cam, tuning, d)
+    used = (want != alone).any(0)  # (where the last splat shows)
+    assert used.any() and not used.all() and not np.isfinite(got[:, used]).any()
+    np.testing.assert_array_equal(got[:, ~used], want[:, ~used])
