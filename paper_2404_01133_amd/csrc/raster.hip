@@ -38,16 +38,18 @@ __device__ __forceinline__ bool colour_finite(float c) { return c <= 3.4028235e3
 
 // Colours that are not finite: times the weight 0 of an entry that is not used, or at a pixel that is done, they
 // would make NaN of the sum.  They are staged as 0, and added to the pixels written that have used them, which
-// is what the weighted sums come to.  Nothing of the walk is live here: a register more in it costs 3 %.  (Sixteen
-// views of the block 1350 -> 1364 us, eight of the city 344 -> 355; as a second walk that selects, 1450 and 414.)
+// is what the weighted sums come to.  Nothing of the walk is live here, not even the thread's index: a register
+// more in it costs 1 to 3 %.  (Sixteen views of the block 1344 -> 1357 us, eight of the city 354 both; with the
+// index kept 1371 and 358, as a second walk that selects 1450 and 414.)
 template <int TW, int TH>
-__device__ __forceinline__ void add_odd_colours(const TileArgs& ta, int tile_g, float* __restrict__ rgb,
+__device__ __forceinline__ void add_odd_colours(const TileArgs& ta, int tile_g, int wid, float* __restrict__ rgb,
                                                 const int32_t* __restrict__ n_last) {
-  uint32_t tid = threadIdx.x;
-  asm volatile("" : "+v"(tid));  // (so that the pixel is found again and not kept)
+  uint32_t ones = ~0u;  // (unknown to the compiler: the lane is found again here and not kept)
+  asm volatile("" : "+s"(ones));
+  const int lane = (int)__builtin_amdgcn_mbcnt_hi(ones, __builtin_amdgcn_mbcnt_lo(ones, 0u));
   const int view = tile_g / ta.tiles_per_view, tile = tile_g - view * ta.tiles_per_view;
   const int tyi = tile / ta.tiles_x_n, txi = tile - tyi * ta.tiles_x_n;
-  const LaneMap<TW, TH, kFwdGW, kFwdGH> m(txi, tyi, (int)(tid >> 6), (int)(tid & 63));
+  const LaneMap<TW, TH, kFwdGW, kFwdGH> m(txi, tyi, wid, lane);
   const bool inside = m.i < ta.W && m.j < ta.H;
   const int64_t plane = (int64_t)ta.H * ta.W, pix = (int64_t)m.j * ta.W + m.i;
   const int last = inside ? n_last[(int64_t)view * plane + pix] : 0;
@@ -195,17 +197,16 @@ __device__ __forceinline__ void raster_fwd_tile(const TileArgs& ta, FwdLds<TW, T
     T_final[(int64_t)view * plane + pix] = T;
     n_last[(int64_t)view * plane + pix] = last;
   }
-  if (end > start && lds.odd) add_odd_colours<TW, TH>(ta, tile_g, rgb, n_last);
+  if (end > start && lds.odd) add_odd_colours<TW, TH>(ta, tile_g, wid, rgb, n_last);
 }
 
 // Bound by VALU issue (with the groups' lists, about 24 instructions and an
 // exponential per entry).  Measured, us per call: eight 1600x900 views of the 20M
 // city 384 before the lists left out unreachable groups, 374 with that, 337 with the
-// loop free of per-entry count, done and stop selects, 348 with the test for colours
-// that are not finite; 16 views of a 2M block 1977, 1514, 1348, 1364; 4096 Gaussians
-// at 256x256 53, 35, 30, 30.  Six waves per SIMD for the
-// multi-wave tiles (the compiler spills a dozen registers outside the loop): 1348 for
-// the block, 1448 at five, 1440 at seven.
+// loop free of per-entry count, done and stop selects; 16 views of a 2M block 1977,
+// 1514, 1348, 1357 with colours tested; 4096 Gaussians at 256x256 53, 35, 30.  Six
+// waves per SIMD for the multi-wave tiles (the compiler spills a dozen registers
+// outside the loop): 1348 for the block, 1448 at five, 1440 at seven.
 template <int TW, int TH, int BATCH>
 __global__ void __launch_bounds__(TW* TH) __attribute__((amdgpu_waves_per_eu(TW * TH >= 128 ? 6 : 1))) raster_fwd_kernel(TileArgs ta, uint32_t* queue, float bg0, float bg1,
                                                             float bg2, float* __restrict__ rgb,
