@@ -64,8 +64,8 @@ FLOPS_PER_EVAL = 15
 # per call, valid for the kernel sources with the given fingerprint only
 MEASURED_TRAFFIC = {
     "preprocess_kernel": (("preprocess.hip", "project.h", "gs_common.h"), "79759c8c4dc301da", 8, 1412.3e6),
-    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "51ef41605c4bbf97", 8,
-                                     874.5e6),
+    "raster_fwd_kernel<16,16,256>": (("raster.hip", "tile.h", "project.h", "gs_common.h"), "26709957b39e5708", 8,
+                                     874.9e6),
     "bin_sort": (("sort.hip", "list_sort.h", "radix.h", "scan.h", "gs_common.h"), "69415c0db73144c2", 8, 670.0e6),
     "lod_refine": (("refine.hip", "radix.h", "scan.h", "project.h", "gs_common.h"), "302e55cfebee5fa6", 8, 35.5e6),
 }
